@@ -46,17 +46,30 @@ __device__ __forceinline__ void tile_of_block(uint32_t bid, uint32_t n_tiles, ui
     mt = (j / n_tiles) * kXcds + xcd;
 }
 
-// Writes one wave's TM x TN block of 32x32 tiles whose top-left element is (row0, col0).
+// The bias of a tile's BN columns as fp32 in LDS (zero without a bias and past d_out), filled while the
+// first loads of the tile are under way and visible after the K loop's first barrier.  With the
+// operands exchanged a lane of the epilogue needs 16 bias values per MFMA tile; read from global
+// memory there, each under its own bounds check, they were a fifth of the whole kernel (first layers
+// of 170 k rows x 256 columns in fp32 / 106 k x 256 in bf16: 245 / 68 us with a bias, 200 / 47 without).
+template <typename Tr, int BN, int NT>
+__device__ __forceinline__ void stage_bias(float* lds_bias, const typename Tr::store_t* bias, int32_t col0,
+                                           int32_t d_out, int tid) {
+    for (int i = tid; i < BN; i += NT)
+        lds_bias[i] = bias != nullptr && col0 + i < d_out ? Tr::to_f(bias[col0 + i]) : 0.f;
+}
+
+// The epilogues below write one wave's TM x TN block of 32x32 tiles whose top-left element is (row0, col0);
+// `bias` is the block's first column in the staged bias of the tile.
 template <typename Tr, int TM, int TN>
 __device__ __forceinline__ void project_epilogue(floatx16 (&acc)[TM][TN], int64_t row0, int32_t col0,
                                                  int lane, int64_t n_dst, int32_t d_out,
-                                                 const typename Tr::store_t* bias, int relu,
+                                                 const float* bias, int relu,
                                                  typename Tr::store_t* out) {
 #pragma unroll
     for (int tn = 0; tn < TN; ++tn) {
         const int32_t col = col0 + tn * 32 + (lane & 31);
         if (col >= d_out) continue;
-        const float b = bias != nullptr ? Tr::to_f(bias[col]) : 0.f;
+        const float b = bias[tn * 32 + (lane & 31)];
 #pragma unroll
         for (int tm = 0; tm < TM; ++tm) {
 #pragma unroll
@@ -77,12 +90,12 @@ __device__ __forceinline__ void project_epilogue(floatx16 (&acc)[TM][TN], int64_
 template <typename Tr, int TM, int TN>
 __device__ __forceinline__ void project_epilogue_f32out(floatx16 (&acc)[TM][TN], int64_t row0, int32_t col0,
                                                         int lane, int64_t n_dst, int32_t d_out,
-                                                        const typename Tr::store_t* bias, int relu, float* out) {
+                                                        const float* bias, int relu, float* out) {
 #pragma unroll
     for (int tn = 0; tn < TN; ++tn) {
         const int32_t col = col0 + tn * 32 + (lane & 31);
         if (col >= d_out) continue;
-        const float b = bias != nullptr ? Tr::to_f(bias[col]) : 0.f;
+        const float b = bias[tn * 32 + (lane & 31)];
 #pragma unroll
         for (int tm = 0; tm < TM; ++tm) {
 #pragma unroll
@@ -107,7 +120,7 @@ __device__ __forceinline__ void project_epilogue_f32out(floatx16 (&acc)[TM][TN],
 template <typename Tr, int TM, int TN>
 __device__ __forceinline__ void project_epilogue_staged(floatx16 (&acc)[TM][TN], int64_t row0, int32_t col0,
                                                         int lane, int64_t n_dst, int32_t d_out,
-                                                        const typename Tr::store_t* bias, int relu,
+                                                        const float* bias, int relu,
                                                         typename Tr::store_t* out,
                                                         typename Tr::store_t* band) {
     using T = typename Tr::store_t;
@@ -115,10 +128,7 @@ __device__ __forceinline__ void project_epilogue_staged(floatx16 (&acc)[TM][TN],
     constexpr int WORDS = W / 8;                     // 16-byte words per band row
     float b[TN];
 #pragma unroll
-    for (int tn = 0; tn < TN; ++tn) {
-        const int32_t col = col0 + tn * 32 + (lane & 31);
-        b[tn] = (bias != nullptr && col < d_out) ? Tr::to_f(bias[col]) : 0.f;
-    }
+    for (int tn = 0; tn < TN; ++tn) b[tn] = bias[tn * 32 + (lane & 31)];
 #pragma unroll
     for (int tm = 0; tm < TM; ++tm) {
 #pragma unroll
@@ -154,7 +164,7 @@ __device__ __forceinline__ void project_epilogue_staged(floatx16 (&acc)[TM][TN],
 // unrounded result).
 template <typename Tr, typename OutT, int TM, int TN>
 __device__ __forceinline__ void epilogue16_direct(floatx16 (&acc)[TM][TN], int64_t row0, int32_t col0, int lane,
-                                                  int64_t row_end, int32_t d_out, const typename Tr::store_t* bias,
+                                                  int64_t row_end, int32_t d_out, const float* bias,
                                                   int relu, OutT* out) {
 #pragma unroll
     for (int tm = 0; tm < TM; ++tm) {
@@ -166,7 +176,7 @@ __device__ __forceinline__ void epilogue16_direct(floatx16 (&acc)[TM][TN], int64
             for (int i = 0; i < 16; ++i) {
                 const int32_t col = col0 + tn * 32 + 8 * (i / 4) + 4 * (lane >> 5) + (i & 3);
                 if (col < d_out) {
-                    float x = acc[tm][tn][i] + (bias != nullptr ? Tr::to_f(bias[col]) : 0.f);
+                    float x = acc[tm][tn][i] + bias[col - col0];
                     if (relu) x = fmaxf(x, 0.f);
                     if constexpr (sizeof(OutT) == 4) out[row * d_out + col] = x;
                     else out[row * d_out + col] = Tr::from_f(x);
@@ -175,17 +185,15 @@ __device__ __forceinline__ void epilogue16_direct(floatx16 (&acc)[TM][TN], int64
     }
 }
 
-// One run of four consecutive columns of a tile: bias, activation, rounding, packed.
+// One run of four consecutive columns of a tile: bias (the run's four values in LDS), activation,
+// rounding, packed.
 template <typename Tr>
-__device__ __forceinline__ uint2 pack_run(const floatx16& a, int q, const typename Tr::store_t* bias, int32_t col,
-                                          int32_t d_out, int relu) {
-    float x[4];
+__device__ __forceinline__ uint2 pack_run(const floatx16& a, int q, const float* bias4, int relu) {
+    const float4 b = *reinterpret_cast<const float4*>(bias4);
+    float x[4] = {a[4 * q] + b.x, a[4 * q + 1] + b.y, a[4 * q + 2] + b.z, a[4 * q + 3] + b.w};
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        x[e] = a[4 * q + e];
-        if (bias != nullptr && col + e < d_out) x[e] += Tr::to_f(bias[col + e]);
+    for (int e = 0; e < 4; ++e)
         if (relu) x[e] = fmaxf(x[e], 0.f);
-    }
     return make_uint2(Tr::pack2(x[0], x[1]), Tr::pack2(x[2], x[3]));
 }
 
@@ -194,7 +202,7 @@ __device__ __forceinline__ uint2 pack_run(const floatx16& a, int q, const typena
 // LDS traffic has to be waited for.
 template <typename Tr, int TM, int TN>
 __device__ __forceinline__ void epilogue16_staged(floatx16 (&acc)[TM][TN], int64_t row0, int32_t col0, int lane,
-                                                  int64_t row_end, int32_t d_out, const typename Tr::store_t* bias,
+                                                  int64_t row_end, int32_t d_out, const float* bias,
                                                   int relu, typename Tr::store_t* out, typename Tr::store_t* band) {
     constexpr int W = 32 * TN, LDW = W + 8;          // band width in elements, padded row
     constexpr int WORDS = W / 8;                     // 16-byte words per band row
@@ -206,7 +214,7 @@ __device__ __forceinline__ void epilogue16_staged(floatx16 (&acc)[TM][TN], int64
             for (int q = 0; q < 4; ++q) {
                 const int c = tn * 32 + 8 * q + 4 * (lane >> 5);
                 *reinterpret_cast<uint2*>(&band[(lane & 31) * LDW + c]) =
-                    pack_run<Tr>(acc[tm][tn], q, bias, col0 + c, d_out, relu);
+                    pack_run<Tr>(acc[tm][tn], q, bias + c, relu);
             }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 #pragma unroll
@@ -248,7 +256,7 @@ __device__ __forceinline__ bool tree_tile_rows(const TreeTiles& tt, uint32_t mt,
 template <typename Tr, int BM, int BN, int PW, int TM, int TN, int NT, bool SW>
 __device__ __forceinline__ void tree_epilogue(floatx16 (&acc)[TM][TN], void* lds, int wave_row0, int wave_col0, int tid,
                                               int lane, int64_t row0, int64_t row_end, int32_t col0, int32_t d_out,
-                                              const typename Tr::store_t* bias, int relu, typename Tr::store_t* out,
+                                              const float* bias, int relu, typename Tr::store_t* out,
                                               const TreeTiles& tt, int lvl, uint32_t tile_in_level, int32_t my_id) {
     using T = typename Tr::store_t;
     static_assert(BM <= NT, "one validity flag per thread");
@@ -281,24 +289,18 @@ __device__ __forceinline__ void tree_epilogue(floatx16 (&acc)[TM][TN], void* lds
                         const int c = wc + 8 * q + 4 * (lane >> 5);
                         T* dst = &tile[(wave_row0 + tm * 32 + (lane & 31)) * LDT + (c - c_lo)];
                         if constexpr (sizeof(T) == 4) {
-                            float4 v;
-                            float* x = &v.x;
-#pragma unroll
-                            for (int e = 0; e < 4; ++e) {
-                                x[e] = av[4 * q + e];
-                                if (bias != nullptr && col0 + c + e < d_out) x[e] += Tr::to_f(bias[col0 + c + e]);
-                                if (relu) x[e] = fmaxf(x[e], 0.f);
-                            }
+                            const float4 b = *reinterpret_cast<const float4*>(bias + c);
+                            float4 v = make_float4(av[4 * q] + b.x, av[4 * q + 1] + b.y, av[4 * q + 2] + b.z, av[4 * q + 3] + b.w);
+                            if (relu) v = make_float4(fmaxf(v.x, 0.f), fmaxf(v.y, 0.f), fmaxf(v.z, 0.f), fmaxf(v.w, 0.f));
                             *reinterpret_cast<float4*>(dst) = v;
                         } else {
-                            *reinterpret_cast<uint2*>(dst) = pack_run<Tr>(av, q, bias, col0 + c, d_out, relu);
+                            *reinterpret_cast<uint2*>(dst) = pack_run<Tr>(av, q, bias + c, relu);
                         }
                     }
                     __builtin_amdgcn_sched_barrier(0);
                 }
             } else {
-                const int32_t col = col0 + wc + (lane & 31);
-                const float b = (bias != nullptr && col < d_out) ? Tr::to_f(bias[col]) : 0.f;
+                const float b = bias[wc + (lane & 31)];
 #pragma unroll
                 for (int tm = 0; tm < TM; ++tm) {
                     floatx16 av = acc[tm][tn];
@@ -379,6 +381,7 @@ sage_project_f32(const float* __restrict__ Hsrc, const int32_t* __restrict__ sel
     extern __shared__ __attribute__((aligned(16))) float lds_f32[];
     float (*As)[BM][LDA] = reinterpret_cast<float (*)[BM][LDA]>(lds_f32);
     float (*Bs)[BK][LDB] = reinterpret_cast<float (*)[BK][LDB]>(lds_f32 + 2 * BM * LDA);
+    __shared__ __attribute__((aligned(16))) float lds_bias[BN];
 
     uint32_t mt, nt;
     tile_of_block(blockIdx.x, n_tiles_n, mt, nt);
@@ -556,6 +559,7 @@ sage_project_f32(const float* __restrict__ Hsrc, const int32_t* __restrict__ sel
     // so that the stage of an unrolled iteration is a constant.
     Regs r[D];
     load_tile(r[0], 0);
+    stage_bias<TrF32, BN, kProjThreads>(lds_bias, bias, col0, d_out, tid);
     store_tile(r[0], 0);
 #pragma unroll
     for (int j = 1; j < D; ++j) load_tile(r[j], j);
@@ -576,11 +580,11 @@ sage_project_f32(const float* __restrict__ Hsrc, const int32_t* __restrict__ sel
         if (t + i < n_tiles) iter(t + i, i);
     if (TREE)
         tree_epilogue<TrF32, BM, BN, BN, TM, TN, kProjThreads, true>(acc, lds_f32, wm * (BM / 2), wn * (BN / 2), tid, lane, row0,
-                                                               row_end, col0, d_out, bias, relu, out, tt, lvl,
+                                                               row_end, col0, d_out, lds_bias, relu, out, tt, lvl,
                                                                tile_in_level, my_id);
     else
-        project_epilogue<TrF32, TM, TN>(acc, row0 + wm * (BM / 2), col0 + wn * (BN / 2), lane, row_end, d_out, bias, relu,
-                                        out);
+        project_epilogue<TrF32, TM, TN>(acc, row0 + wm * (BM / 2), col0 + wn * (BN / 2), lane, row_end, d_out,
+                                        lds_bias + wn * (BN / 2), relu, out);
 }
 
 // bf16 / fp16: v_mfma_f32_32x32x16_{bf16,f16}.  Lane l feeds 8 consecutive k of row (or
@@ -609,6 +613,7 @@ sage_project_16(const uint16_t* __restrict__ Hsrc, const int32_t* __restrict__ s
     extern __shared__ __attribute__((aligned(16))) uint16_t lds16[];
     uint16_t (*As)[BM][LD] = reinterpret_cast<uint16_t (*)[BM][LD]>(lds16);
     uint16_t (*Bs)[BN][LD] = reinterpret_cast<uint16_t (*)[BN][LD]>(lds16 + 2 * BM * LD);
+    __shared__ __attribute__((aligned(16))) float lds_bias[BN];
 
     uint32_t mt, nt;
     tile_of_block(blockIdx.x, n_tiles_n, mt, nt);
@@ -765,6 +770,7 @@ sage_project_16(const uint16_t* __restrict__ Hsrc, const int32_t* __restrict__ s
     // so that the stage of an unrolled iteration is a constant.
     Regs r[D];
     load_tile(r[0], 0);
+    stage_bias<Tr, BN, NT>(lds_bias, bias, col0, d_out, tid);
     store_tile(r[0], 0);
 #pragma unroll
     for (int j = 1; j < D; ++j) load_tile(r[j], j);
@@ -785,22 +791,23 @@ sage_project_16(const uint16_t* __restrict__ Hsrc, const int32_t* __restrict__ s
         if (t + i < n_tiles) iter(t + i, i);
     const int64_t wrow0 = row0 + wm * (BM / WM);
     const int32_t wcol0 = col0 + wn * (BN / WN);
+    const float* wbias = lds_bias + wn * (BN / WN);
     if (TREE) {
         tree_epilogue<Tr, BM, BN, BN, TM, TN, NT, SW>(acc, lds16, wm * (BM / WM), wn * (BN / WN), tid, lane, row0, row_end, col0,
-                                                      d_out, bias, relu, out, tt, lvl, tile_in_level, my_id);
+                                                      d_out, lds_bias, relu, out, tt, lvl, tile_in_level, my_id);
     } else if (out_f32) {     // `out` is a float array: unrounded result
-        if constexpr (SW) epilogue16_direct<Tr, float, TM, TN>(acc, wrow0, wcol0, lane, row_end, d_out, bias, relu, reinterpret_cast<float*>(out));
-        else project_epilogue_f32out<Tr, TM, TN>(acc, wrow0, wcol0, lane, row_end, d_out, bias, relu, reinterpret_cast<float*>(out));
+        if constexpr (SW) epilogue16_direct<Tr, float, TM, TN>(acc, wrow0, wcol0, lane, row_end, d_out, wbias, relu, reinterpret_cast<float*>(out));
+        else project_epilogue_f32out<Tr, TM, TN>(acc, wrow0, wcol0, lane, row_end, d_out, wbias, relu, reinterpret_cast<float*>(out));
     } else if (VEC && (d_out & 7) == 0) {
         // every wave is past its last LDS read of the tiles: reuse that LDS, one band per wave
         constexpr int BAND = 32 * (32 * TN + 8);
         static_assert((size_t)WM * WN * BAND <= (size_t)2 * (BM + BN) * LD, "epilogue bands exceed the tile LDS");
         typename Tr::store_t* band = reinterpret_cast<typename Tr::store_t*>(lds16) + wave * BAND;
-        if constexpr (SW) epilogue16_staged<Tr, TM, TN>(acc, wrow0, wcol0, lane, row_end, d_out, bias, relu, out, band);
-        else project_epilogue_staged<Tr, TM, TN>(acc, wrow0, wcol0, lane, row_end, d_out, bias, relu, out, band);
+        if constexpr (SW) epilogue16_staged<Tr, TM, TN>(acc, wrow0, wcol0, lane, row_end, d_out, wbias, relu, out, band);
+        else project_epilogue_staged<Tr, TM, TN>(acc, wrow0, wcol0, lane, row_end, d_out, wbias, relu, out, band);
     } else {
-        if constexpr (SW) epilogue16_direct<Tr, typename Tr::store_t, TM, TN>(acc, wrow0, wcol0, lane, row_end, d_out, bias, relu, out);
-        else project_epilogue<Tr, TM, TN>(acc, wrow0, wcol0, lane, row_end, d_out, bias, relu, out);
+        if constexpr (SW) epilogue16_direct<Tr, typename Tr::store_t, TM, TN>(acc, wrow0, wcol0, lane, row_end, d_out, wbias, relu, out);
+        else project_epilogue<Tr, TM, TN>(acc, wrow0, wcol0, lane, row_end, d_out, wbias, relu, out);
     }
 }
 
@@ -835,6 +842,8 @@ sage_project_16_walk(const uint16_t* __restrict__ Hsrc, const int32_t* __restric
     extern __shared__ __attribute__((aligned(16))) uint16_t lds16[];
     auto As = [&](int st) { return reinterpret_cast<uint16_t (*)[LD]>(lds16 + st * STAGE); };
     auto Bs = [&](int st) { return reinterpret_cast<uint16_t (*)[LD]>(lds16 + st * STAGE + BM * LD); };
+    // this tile's bias and the next one's (see stage_bias), requested with the next tile's row indices
+    __shared__ __attribute__((aligned(16))) float lds_bias[2][BN];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave / WN, wn = wave % WN;
     const int nk = (k_total + BK - 1) / BK;
@@ -863,7 +872,7 @@ sage_project_16_walk(const uint16_t* __restrict__ Hsrc, const int32_t* __restric
         int32_t id;              // slot id behind row `tid` of the tile (see tree_epilogue)
     };
     // the indices are requested here and not touched: whoever turns them into offsets waits for them
-    auto load_idx = [&](const Tile& T, int32_t (&sidx)[ITEMS], int32_t& id) {
+    auto load_idx = [&](const Tile& T, int32_t (&sidx)[ITEMS], int32_t& id, typename Tr::store_t& bv) {
 #pragma unroll
         for (int it = 0; it < ITEMS; ++it) {
             const int64_t r = T.row0 + it * SLICE + trow;
@@ -874,6 +883,12 @@ sage_project_16_walk(const uint16_t* __restrict__ Hsrc, const int32_t* __restric
         const bool in = T.row0 + tid < T.row_end;
         const int32_t v = tt.ids[in ? T.row0 + tid : T.row0];
         id = (in && T.lvl >= 1 && tt.mean_next != nullptr) ? v : -1;
+        const int32_t col = T.col0 + (tid & (BN - 1));
+        bv = *(bias != nullptr && col < d_out ? bias + col : reinterpret_cast<const typename Tr::store_t*>(Wt));
+    };
+    auto bias_of = [&](const Tile& T, typename Tr::store_t bv, int par) {
+        const int32_t col = T.col0 + (tid & (BN - 1));
+        if (tid < BN) lds_bias[par][tid] = bias != nullptr && col < d_out ? Tr::to_f(bv) : 0.f;
     };
     auto rows_of = [&](const Tile& T, const int32_t (&sidx)[ITEMS], int32_t id, Rows& R) {
         R.absent = 0u;
@@ -946,8 +961,10 @@ sage_project_16_walk(const uint16_t* __restrict__ Hsrc, const int32_t* __restric
     Rows R;
     {
         int32_t sidx[ITEMS], id;
-        load_idx(cur, sidx, id);
+        typename Tr::store_t bv;
+        load_idx(cur, sidx, id, bv);
         rows_of(cur, sidx, id, R);
+        bias_of(cur, bv, 0);
     }
     // (one struct for everything under way: a weights array of its own ended up in scratch memory)
     struct Ring {
@@ -959,7 +976,7 @@ sage_project_16_walk(const uint16_t* __restrict__ Hsrc, const int32_t* __restric
     store_tile(rg.a[0], rg.b, 0, 0, R);
     load_a(rg.a[1], cur, R, 1);
     lds_barrier();
-    for (;;) {
+    for (int par = 0;; par ^= 1) {
         // Stage 0 holds this tile's first K tile.  The tile after this one (the last tile stands in for
         // its own successor: its first K tile is then re-read at the end and nothing uses it):
         uint32_t nbid = bid + gridDim.x;
@@ -968,7 +985,8 @@ sage_project_16_walk(const uint16_t* __restrict__ Hsrc, const int32_t* __restric
         while (nbid < n_blocks && !(has_next = tile_at(nbid, nxt))) nbid += gridDim.x;
         if (!has_next) nxt = cur;
         int32_t nidx[ITEMS], nid;
-        load_idx(nxt, nidx, nid);
+        typename Tr::store_t nbias;
+        load_idx(nxt, nidx, nid, nbias);
 #pragma unroll
         for (int tm = 0; tm < TM; ++tm)
 #pragma unroll
@@ -995,6 +1013,7 @@ sage_project_16_walk(const uint16_t* __restrict__ Hsrc, const int32_t* __restric
         // until the epilogue has released the LDS.
         Rows N;
         rows_of(nxt, nidx, nid, N);
+        bias_of(nxt, nbias, par ^ 1);
         load_b(rg.b, cur.col0, t + 1);
         load_a(rg.a[0], nxt, N, 0);
         compute(0);
@@ -1013,7 +1032,7 @@ sage_project_16_walk(const uint16_t* __restrict__ Hsrc, const int32_t* __restric
         }
         lds_barrier();     // every wave is past its last read of the K tiles: the epilogue reuses their LDS
         tree_epilogue<Tr, BM, BN, BN, TM, TN, NT, SW>(acc, lds16, wm * (BM / WM), wn * (BN / WN), tid, lane, cur.row0,
-                                                      cur.row_end, cur.col0, d_out, bias, relu, out, tt, cur.lvl, cur.til,
+                                                      cur.row_end, cur.col0, d_out, lds_bias[par], relu, out, tt, cur.lvl, cur.til,
                                                       R.id);
         store_tile(rg.a[0], rg.b, 0, 0, N);      // the next tile's first K tile, which waited in the registers
         lds_barrier();
