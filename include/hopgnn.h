@@ -350,7 +350,9 @@ hopgnn_status hopgnn_sage_fwd(const void *Hsrc, hopgnn_dtype dt, int64_t n_src, 
  * hopgnn_sage_fwd with another neighbour aggregator (the paper's discussion of generality names
  * sum and max beside the mean):  m_r = mean, sum or element-wise maximum of Hsrc[idx[e]] over the
  * valid entries of row r (0 for an empty segment), out[r] = act(x_r W_self + m_r W_neigh + bias).
- * agg is a hopgnn_agg; HOPGNN_AGG_MEAN is hopgnn_sage_fwd itself.  Same arguments, workspace
+ * agg is a hopgnn_agg; HOPGNN_AGG_MEAN is the layer of hopgnn_sage_fwd (whose large fp32 products
+ * are formed from split operands, like hopgnn_batch_fwd's: the rounding differs; this call and _dev
+ * keep one rounding for all sizes, the forward of a training step).  Same arguments, workspace
  * (hopgnn_sage_fwd_ws_bytes) and errors; for 2-byte types m_r is rounded to dt before the product.
  */
 hopgnn_status hopgnn_sage_fwd_agg(const void *Hsrc, hopgnn_dtype dt, int64_t n_src, int32_t d_in,

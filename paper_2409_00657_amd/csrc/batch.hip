@@ -297,7 +297,7 @@ extern "C" hopgnn_status hopgnn_batch_fwd(const hopgnn_batch_plan* p, const int3
                 if (mk && !mark_agg && hipEventRecord(ev_a, st) != hipSuccess) return HOPGNN_EHIP;
                 rc = project_dispatch(p->dt, st, src, k == 1 ? rb : nullptr, mean, p->W_self[k - 1], p->W_neigh[k - 1], Wt,
                                       TW.KP[k - 1], p->bias[k - 1], n_dst, d_in, 2 * d_in, p->d_out[k - 1], k < L ? 1 : 0,
-                                      zero, dst, 0, nullptr, k < L ? &tree : nullptr);
+                                      zero, dst, 0, nullptr, k < L ? &tree : nullptr, true);
                 if (rc != HOPGNN_OK) return rc;
                 if (mk && !mark_agg && hipEventRecord(ev_b, st) != hipSuccess) return HOPGNN_EHIP;
                 src = dst;
@@ -328,7 +328,7 @@ extern "C" hopgnn_status hopgnn_batch_fwd(const hopgnn_batch_plan* p, const int3
                 }
                 rc = sage_fwd_marked(src, p->dt, n_src, d_in, self_idx, p->indptr, nbr, n_dst, nullptr, p->W_self[k - 1],
                                      p->W_neigh[k - 1], p->bias[k - 1], p->d_out[k - 1], HOPGNN_AGG_MEAN, relu, dst,
-                                     p->sage_ws, p->sage_ws_bytes, stream, b == 0 && k == mark_layer ? &lm : nullptr);
+                                     p->sage_ws, p->sage_ws_bytes, stream, b == 0 && k == mark_layer ? &lm : nullptr, true);
             }
             else if (p->layer_kind == 1)
                 rc = hopgnn_gcn_fwd(src, p->dt, n_src, d_in, self_idx, p->indptr, nbr, n_dst, p->W_self[k - 1],

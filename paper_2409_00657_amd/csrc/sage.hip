@@ -587,6 +587,223 @@ sage_project_f32(const float* __restrict__ Hsrc, const int32_t* __restrict__ sel
                                         lds_bias + wn * (BN / 2), relu, out);
 }
 
+// The large tile of the fp32 forward pass.  Bound by the matrix cores: v_mfma_f32_32x32x2_f32 needs 512 cycles per 32 x 32 x 16
+// block, six v_mfma_f32_32x32x16_bf16 of the split operands 192.  Both operands are split on their way
+// to LDS (three pieces each, k contiguous, row stride conflict free for 128-bit reads), the weights in
+// this kernel too, so nothing derived from them outlives the call.
+// A block whose sums are not all finite (an infinity, or a sum past the largest float: the pieces of an
+// infinity are not numbers) is done again with the fp32 instruction straight from memory.
+template <int BM, int BN, int BK, bool VEC, bool TREE>
+__global__ void __launch_bounds__(kProjThreads, 2)
+sage_project_split(const float* __restrict__ Hsrc, const int32_t* __restrict__ self_idx,
+                 const float* __restrict__ Mean, const float* __restrict__ Wself,
+                 const float* __restrict__ Wneigh, const float* __restrict__ bias, int64_t n_dst,
+                 int32_t d_in, int32_t k_total, int32_t d_out, int relu, uint32_t n_tiles_n,
+                 const float* __restrict__ Zero, float* __restrict__ out, const int64_t* __restrict__ n_rows_dev,
+                 TreeTiles tt) {
+    constexpr int LD = BK + 8;                            // LD / 8 odd: conflict-free 128-bit reads
+    static_assert(BK % 16 == 0 && (LD / 8) % 2 == 1, "K tile");
+    constexpr int TM = BM / 64, TN = BN / 64;
+    constexpr int A_ITEMS = BM * BK / 8 / kProjThreads;   // items of eight k per thread
+    constexpr int B_ITEMS = BK * BN / 8 / kProjThreads;
+    static_assert(A_ITEMS >= 1 && B_ITEMS >= 1, "tile too small for 256 threads");
+    constexpr int A_PIECE = BM * LD, B_PIECE = BN * LD;   // elements
+    constexpr int STAGE = 3 * (A_PIECE + B_PIECE);
+    extern __shared__ __attribute__((aligned(16))) uint16_t lds16[];
+    __shared__ __attribute__((aligned(16))) float lds_bias[BN];
+
+    uint32_t mt, nt;
+    tile_of_block(blockIdx.x, n_tiles_n, mt, nt);
+    int64_t row0 = (int64_t)mt * BM, row_end;
+    int lvl = 0;
+    uint32_t tile_in_level = 0;
+    if (TREE) {
+        if (!tree_tile_rows<BM>(tt, mt, lvl, tile_in_level, row0, row_end)) return;
+    } else {
+        if (n_rows_dev != nullptr) {      // the row count lives on the device: rows past it do not exist
+            const int64_t live = *n_rows_dev;
+            n_dst = live < n_dst ? live : n_dst;
+        }
+        if (row0 >= n_dst) return;
+        row_end = n_dst;
+    }
+    const int32_t col0 = nt * BN;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int wm = wave >> 1, wn = wave & 1;
+    const int K = k_total;
+    // the slot id behind this thread's row of the tile (which siblings count in a mean): read here,
+    // used after the K loop
+    int32_t my_id = -1;
+    if (TREE && lvl >= 1 && tt.mean_next != nullptr && row0 + tid < row_end) my_id = tt.ids[row0 + tid];
+
+    // rows this thread stages, fixed for the whole K loop
+    int64_t a_self[A_ITEMS], a_mean[A_ITEMS];
+#pragma unroll
+    for (int it = 0; it < A_ITEMS; ++it) {
+        const int i = it * kProjThreads + tid;
+        const int64_t r = row0 + i / (BK / 8);
+        a_self[it] = -1;
+        a_mean[it] = -1;
+        if (r < row_end) {
+            const int64_t s = self_idx != nullptr ? (int64_t)self_idx[r] : r;
+            a_self[it] = s >= 0 ? s * d_in : -1;
+            a_mean[it] = r * d_in;
+        }
+    }
+
+    floatx16 acc[TM][TN];
+    zero_acc<TM, TN>(acc);
+
+    struct Regs {
+        float a[A_ITEMS][8], b[B_ITEMS][8];
+    };
+    const int n_tiles = (K + BK - 1) / BK;
+
+    // Branch-free addressing for the vector path: rows that do not exist and the K padding
+    // are read from `Zero`, a row of zeros at least one padded K long, so the loop has no
+    // control flow and nothing consumes a loaded value before it is stored to LDS.
+    const float* p_self[A_ITEMS];
+    const float* p_mean[A_ITEMS];
+#pragma unroll
+    for (int it = 0; it < A_ITEMS; ++it) {
+        p_self[it] = a_self[it] >= 0 ? Hsrc + a_self[it] : Zero;
+        p_mean[it] = a_mean[it] >= 0 ? Mean + a_mean[it] - d_in : Zero;   // indexed by the concatenated k
+    }
+    // this thread's weight column by the concatenated k: row k of W_self for k < d_in, row k - d_in of
+    // W_neigh after
+    const float* b_self[B_ITEMS];
+    const float* b_neigh[B_ITEMS];
+    bool b_in[B_ITEMS];
+#pragma unroll
+    for (int it = 0; it < B_ITEMS; ++it) {
+        const int n = col0 + (it * kProjThreads + tid) % BN;
+        b_in[it] = n < d_out;
+        b_self[it] = Wself + n;
+        b_neigh[it] = Wneigh + n - (int64_t)d_in * d_out;
+    }
+    auto a_elem = [&](int it, int k) -> float {   // one element of the concatenated row
+        if (k < d_in) return a_self[it] >= 0 ? Hsrc[a_self[it] + k] : 0.f;
+        if (k < K) return a_mean[it] >= 0 ? Mean[a_mean[it] + (k - d_in)] : 0.f;
+        return 0.f;
+    };
+    auto load_tile = [&](Regs& r, int t) {
+        const int k0 = t * BK;
+#pragma unroll
+        for (int it = 0; it < A_ITEMS; ++it) {
+            const int k = k0 + ((it * kProjThreads + tid) % (BK / 8)) * 8;
+#pragma unroll
+            for (int h = 0; h < 8; h += 4) {
+                if (VEC) {   // d_in % 4 == 0: four k never straddle the self/mean boundary
+                    const float* p = (k + h < d_in ? p_self[it] : p_mean[it]) + k + h;
+                    const float4 v = *reinterpret_cast<const float4*>(k + h < K ? p : Zero);
+                    r.a[it][h] = v.x, r.a[it][h + 1] = v.y, r.a[it][h + 2] = v.z, r.a[it][h + 3] = v.w;
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) r.a[it][h + e] = a_elem(it, k + h + e);
+                }
+            }
+        }
+#pragma unroll
+        for (int it = 0; it < B_ITEMS; ++it) {
+            const int k = k0 + ((it * kProjThreads + tid) / BN) * 8;
+#pragma unroll
+            for (int h = 0; h < 8; h += 4) {
+                if (VEC) {   // four k lie in one weight matrix; selects, no control flow
+                    const bool in = k + h < K && b_in[it];
+                    const float* p = in ? (k + h < d_in ? b_self[it] : b_neigh[it]) + (int64_t)(k + h) * d_out : Zero;
+                    const int64_t step = in ? d_out : 0;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) r.b[it][h + e] = p[e * step];
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const int ke = k + h + e;
+                        r.b[it][h + e] = ke < K && b_in[it] ? (ke < d_in ? b_self[it] : b_neigh[it])[(int64_t)ke * d_out] : 0.f;
+                    }
+                }
+            }
+        }
+    };
+    auto store_tile = [&](const Regs& r, int st) {
+        uint16_t* s = lds16 + st * STAGE;
+#pragma unroll
+        for (int it = 0; it < A_ITEMS; ++it) {
+            const int i = it * kProjThreads + tid;
+            stage_split8<A_PIECE>(r.a[it], s + (i / (BK / 8)) * LD + (i % (BK / 8)) * 8);
+        }
+#pragma unroll
+        for (int it = 0; it < B_ITEMS; ++it) {
+            const int i = it * kProjThreads + tid;
+            stage_split8<B_PIECE>(r.b[it], s + 3 * A_PIECE + (i % BN) * LD + (i / BN) * 8);
+        }
+    };
+    const int fg = lane >> 5, fl32 = lane & 31;
+    auto compute = [&](int st) {      // slot-tree layers: operands exchanged, a lane then holds runs of one row
+        const uint16_t* sa = lds16 + st * STAGE + (wm * (BM / 2) + fl32) * LD + fg * 8;
+        const uint16_t* sb = lds16 + st * STAGE + 3 * A_PIECE + (wn * (BN / 2) + fl32) * LD + fg * 8;
+        mma_split<TM, TN, BK, LD, A_PIECE, B_PIECE, TREE>(acc, sa, sb);
+    };
+
+    // Two register sets and two LDS stages.  Iteration t: the loads of tile t+2 are issued first (into
+    // the set tile t has left), tile t is multiplied from LDS stage t&1, and only then is tile t+1 -
+    // loaded an iteration ago - split and moved to the other stage.  Tiles at or beyond n_tiles load
+    // as zeros and are never multiplied.
+    Regs r[2];
+    load_tile(r[0], 0);
+    stage_bias<TrF32, BN, kProjThreads>(lds_bias, bias, col0, d_out, tid);
+    store_tile(r[0], 0);
+    load_tile(r[1], 1);
+    lds_barrier();
+    auto iter = [&](int t, int i) {     // i = t % 2, a constant after unrolling
+        load_tile(r[i], t + 2);
+        compute(i);
+        store_tile(r[i ^ 1], i ^ 1);
+        lds_barrier();
+    };
+    int t = 0;
+    for (; t + 2 <= n_tiles; t += 2) {
+        iter(t, 0);
+        iter(t + 1, 1);
+    }
+    if (t < n_tiles) iter(t, 0);
+
+    if (!wave_finite<TM, TN>(acc)) {      // v_mfma_f32_32x32x2_f32: lane l feeds A[row l%32][k = l/32], B[k = l/32][col l%32]
+        zero_acc<TM, TN>(acc);
+        int64_t so[TM], mo[TM];
+#pragma unroll
+        for (int tm = 0; tm < TM; ++tm) {
+            const int64_t row = row0 + wm * (BM / 2) + tm * 32 + fl32;
+            const int64_t s = row >= row_end ? -1 : self_idx != nullptr ? (int64_t)self_idx[row] : row;
+            so[tm] = s >= 0 ? s * d_in : -1;
+            mo[tm] = row < row_end ? row * d_in : -1;
+        }
+        for (int k = fg; k - fg < K; k += 2) {
+            float a[TM], b[TN];
+#pragma unroll
+            for (int tm = 0; tm < TM; ++tm)
+                a[tm] = k < d_in ? (so[tm] >= 0 ? Hsrc[so[tm] + k] : 0.f) : (k < K && mo[tm] >= 0 ? Mean[mo[tm] + k - d_in] : 0.f);
+#pragma unroll
+            for (int tn = 0; tn < TN; ++tn) {
+                const int32_t n = col0 + wn * (BN / 2) + tn * 32 + fl32;
+                b[tn] = k < K && n < d_out ? (k < d_in ? Wself + (int64_t)k * d_out : Wneigh + (int64_t)(k - d_in) * d_out)[n] : 0.f;
+            }
+#pragma unroll
+            for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+                for (int tn = 0; tn < TN; ++tn)
+                    acc[tm][tn] = TREE ? __builtin_amdgcn_mfma_f32_32x32x2f32(b[tn], a[tm], acc[tm][tn], 0, 0, 0)
+                                       : __builtin_amdgcn_mfma_f32_32x32x2f32(a[tm], b[tn], acc[tm][tn], 0, 0, 0);
+        }
+    }
+    if (TREE)
+        tree_epilogue<TrF32, BM, BN, BN, TM, TN, kProjThreads, true>(acc, lds16, wm * (BM / 2), wn * (BN / 2), tid, lane, row0,
+                                                               row_end, col0, d_out, lds_bias, relu, out, tt, lvl,
+                                                               tile_in_level, my_id);
+    else
+        project_epilogue<TrF32, TM, TN>(acc, row0 + wm * (BM / 2), col0 + wn * (BN / 2), lane, row_end, d_out,
+                                        lds_bias + wn * (BN / 2), relu, out);
+}
+
 // bf16 / fp16: v_mfma_f32_32x32x16_{bf16,f16}.  Lane l feeds 8 consecutive k of row (or
 // column) l%32, k-group l/32, so both operands sit in LDS with k contiguous and are read
 // as 128-bit words: A [BM][BK+8], B [BN][BK+8] (row stride 80 bytes: conflict free).
@@ -1071,7 +1288,7 @@ static int64_t tree_tiles(const TreeLayer& t, int BM, TreeTiles& tt) {
     return tiles;
 }
 
-template <int BM, int BN, int BK, int D>
+template <int BM, int BN, int BK, bool SPLIT>
 static hopgnn_status launch_project_f32(bool vec, hipStream_t s, const void* Hsrc, const int32_t* self_idx,
                                         const void* mean, const void* Ws, const void* Wn, const void* bias,
                                         int64_t n_dst, int32_t d_in, int32_t k_total, int32_t d_out, int relu,
@@ -1088,20 +1305,28 @@ static hopgnn_status launch_project_f32(bool vec, hipStream_t s, const void* Hsr
     auto b = static_cast<const float*>(bias);
     auto o = static_cast<float*>(out);
     auto z = static_cast<const float*>(zero);
-    constexpr size_t lds_loop = (size_t)2 * (BM * (BK + 4) + BK * (BN + 4)) * sizeof(float);
     constexpr size_t lds_tree = (size_t)BM * (BN + 4) * sizeof(float) + BM;     // staged tile + validity bytes
-    const size_t lds = tree != nullptr && lds_tree > lds_loop ? lds_tree : lds_loop;
-    auto kern = tree != nullptr ? sage_project_f32<BM, BN, BK, D, true, true>
-                : vec           ? sage_project_f32<BM, BN, BK, D, true, false>
-                                : sage_project_f32<BM, BN, BK, D, false, false>;
-    if (lds > 64 * 1024 &&
-        hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
-                            (int)lds) != hipSuccess)
-        return HOPGNN_EHIP;
-    hipLaunchKernelGGL(kern, grid, dim3(kProjThreads), lds, s, a, self_idx, m, ws, wn, b, n_dst, d_in, k_total, d_out,
-                       relu, ntn, z, o, n_rows_dev, tt);
-    HOPGNN_LAUNCH_CHECK();
-    return HOPGNN_OK;
+    size_t lds = SPLIT ? (size_t)2 * 3 * (BM + BN) * (BK + 8) * sizeof(uint16_t)
+                       : (size_t)2 * (BM * (BK + 4) + BK * (BN + 4)) * sizeof(float);
+    if (tree != nullptr && lds_tree > lds) lds = lds_tree;
+    auto launch = [&](auto kern) -> hopgnn_status {
+        if (lds > 64 * 1024 &&       // above the default limit the size has to be opted into
+            hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                (int)lds) != hipSuccess)
+            return HOPGNN_EHIP;
+        hipLaunchKernelGGL(kern, grid, dim3(kProjThreads), lds, s, a, self_idx, m, ws, wn, b, n_dst, d_in, k_total, d_out,
+                           relu, ntn, z, o, n_rows_dev, tt);
+        HOPGNN_LAUNCH_CHECK();
+        return HOPGNN_OK;
+    };
+    if constexpr (SPLIT)
+        return launch(tree != nullptr ? sage_project_split<BM, BN, BK, true, true>
+                      : vec           ? sage_project_split<BM, BN, BK, true, false>
+                                      : sage_project_split<BM, BN, BK, false, false>);
+    if constexpr (!SPLIT && BM == 64)
+        if (tree != nullptr) return launch(sage_project_f32<BM, BN, BK, 2, true, true>);
+    if constexpr (!SPLIT)
+        return launch(vec ? sage_project_f32<BM, BN, BK, 2, true, false> : sage_project_f32<BM, BN, BK, 2, false, false>);
 }
 
 template <typename Tr, int BM, int BN, int BK, int WM, int WN, int D = 2>
@@ -1185,13 +1410,13 @@ hopgnn_status project_dispatch(hopgnn_dtype dt, hipStream_t s, const void* Hsrc,
                                const void* mean, const void* W_self, const void* W_neigh, const uint16_t* Wt,
                                int32_t KP, const void* bias, int64_t n_dst, int32_t d_in, int32_t k_total,
                                int32_t d_out, int relu, const void* zero, void* out, int out_f32,
-                               const int64_t* n_rows_dev, const TreeLayer* tree) {
+                               const int64_t* n_rows_dev, const TreeLayer* tree, bool split) {
     const int per16 = dt == HOPGNN_F32 ? 4 : 8;
     const int64_t work = ceil_div(n_dst, 128) * ceil_div(d_out, 128);   // 128 x 128 output tiles
     bool vec = d_in % per16 == 0 && aligned(Hsrc, 16) && aligned(mean, 16);
     if (dt == HOPGNN_F32) vec = vec && d_out % per16 == 0 && aligned(W_self, 16) && aligned(W_neigh, 16);
     if (tree != nullptr) {      // the slot-tree kernels are built for the vector path only
-        if (!vec || out_f32 || n_rows_dev != nullptr || d_out % per16 != 0 || !aligned(out, 16) ||
+        if (!vec || (dt == HOPGNN_F32 && !split) || out_f32 || n_rows_dev != nullptr || d_out % per16 != 0 || !aligned(out, 16) ||
             (tree->mean_next != nullptr && !aligned(tree->mean_next, 16)) || tree->n_levels < 1 ||
             tree->n_levels > kMaxLayers + 1)
             return HOPGNN_EINVAL;
@@ -1199,10 +1424,16 @@ hopgnn_status project_dispatch(hopgnn_dtype dt, hipStream_t s, const void* Hsrc,
             if (tree->fan[h] < 1 || tree->fan[h] > kTreeMaxFan) return HOPGNN_EINVAL;
     }
     if (dt == HOPGNN_F32) {
-        // large tiles once there is enough work to fill 256 CUs twice over
+        // Large tiles once there is enough work to fill 256 CUs twice over.  On them inference (`split`: the
+        // single-call pass and hopgnn_sage_fwd) takes the split operands: 170 k rows of 2 x 100 -> 256 with
+        // means 218 -> 146 us; on small tiles, whose waits are for memory, only 58 -> 54.  The stored rows
+        // of a training forward decide the ReLU masks of its backward, so that a rounding of theirs moves
+        // gradients by far more than its own size (5.7e-5 of the three-layer gradients at that shape):
+        // hopgnn_sage_fwd_agg and _dev, which training calls, keep the fp32 instruction's bits.
         if (d_out > 64 && work >= 512)
-            return launch_project_f32<128, 128, 16, 2>(vec, s, Hsrc, self_idx, mean, W_self, W_neigh, bias, n_dst, d_in, k_total, d_out, relu, zero, out, n_rows_dev, tree);
-        return launch_project_f32<64, 64, 32, 2>(vec, s, Hsrc, self_idx, mean, W_self, W_neigh, bias, n_dst, d_in, k_total, d_out, relu, zero, out, n_rows_dev, tree);
+            return split ? launch_project_f32<128, 128, 16, true>(vec, s, Hsrc, self_idx, mean, W_self, W_neigh, bias, n_dst, d_in, k_total, d_out, relu, zero, out, n_rows_dev, tree)
+                         : launch_project_f32<128, 128, 16, false>(vec, s, Hsrc, self_idx, mean, W_self, W_neigh, bias, n_dst, d_in, k_total, d_out, relu, zero, out, n_rows_dev, tree);
+        return launch_project_f32<64, 64, 32, false>(vec, s, Hsrc, self_idx, mean, W_self, W_neigh, bias, n_dst, d_in, k_total, d_out, relu, zero, out, n_rows_dev, tree);
     }
     const bool huge = d_out > 128 && work >= 1024;   // 256 x 256 tiles once they still fill 256 CUs
     const bool big = d_out > 64 && work >= 512;
@@ -1254,8 +1485,9 @@ extern "C" hopgnn_status hopgnn_sage_fwd(const void* Hsrc, hopgnn_dtype dt, int6
                                          const void* W_neigh, const void* bias, int32_t d_out,
                                          int32_t relu, void* out, void* ws, size_t ws_bytes,
                                          void* stream) {
-    return hopgnn_sage_fwd_agg(Hsrc, dt, n_src, d_in, self_idx, indptr, idx, n_dst, W_self, W_neigh, bias, d_out,
-                               HOPGNN_AGG_MEAN, relu, out, ws, ws_bytes, stream);
+    // the layer as the single-call pass runs it: the same bits
+    return sage_fwd_marked(Hsrc, dt, n_src, d_in, self_idx, indptr, idx, n_dst, nullptr, W_self, W_neigh, bias, d_out,
+                           HOPGNN_AGG_MEAN, relu, out, ws, ws_bytes, stream, nullptr, true);
 }
 
 extern "C" hopgnn_status hopgnn_sage_fwd_agg(const void* Hsrc, hopgnn_dtype dt, int64_t n_src, int32_t d_in,
@@ -1286,7 +1518,7 @@ hopgnn_status sage_fwd_marked(const void* Hsrc, hopgnn_dtype dt, int64_t n_src, 
                               const int32_t* indptr, const int32_t* idx, int64_t n_dst, const int64_t* n_dst_dev,
                               const void* W_self, const void* W_neigh, const void* bias, int32_t d_out, int32_t agg,
                               int32_t relu, void* out, void* ws, size_t ws_bytes, void* stream,
-                              const LayerMarks* marks) {
+                              const LayerMarks* marks, bool split) {
     if (agg != HOPGNN_AGG_MEAN && agg != HOPGNN_AGG_SUM && agg != HOPGNN_AGG_MAX) return HOPGNN_EINVAL;
     if (dt != HOPGNN_F32 && dt != HOPGNN_BF16 && dt != HOPGNN_F16) return HOPGNN_EINVAL;
     if (n_src < 0 || n_dst < 0 || d_in < 1 || d_out < 1) return HOPGNN_EINVAL;
@@ -1323,7 +1555,7 @@ hopgnn_status sage_fwd_marked(const void* Hsrc, hopgnn_dtype dt, int64_t n_src, 
     if (marks != nullptr && (!mark(marks->agg_end, s) || !mark(marks->proj_begin, s))) return HOPGNN_EHIP;
 
     st = project_dispatch(dt, s, Hsrc, self_idx, mean, W_self, W_neigh, Wt, L.KP, bias, n_dst, d_in, 2 * d_in, d_out, relu,
-                          zero, out, 0, n_dst_dev);
+                          zero, out, 0, n_dst_dev, nullptr, split);
     if (st != HOPGNN_OK) return st;
     if (marks != nullptr && !mark(marks->proj_end, s)) return HOPGNN_EHIP;
     return HOPGNN_OK;

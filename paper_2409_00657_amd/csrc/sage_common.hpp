@@ -89,6 +89,85 @@ __device__ __forceinline__ floatx16 mfma16<TrF16>(const uint4& a, const uint4& b
                                                   *reinterpret_cast<const halfx8*>(&b), c, 0, 0, 0);
 }
 
+// fp32 on the bf16 matrix instruction.  A float is the sum of three bf16 values: its leading 8
+// significant bits cut off, the next 8 rounded to nearest, and what is left (exact in 8 bits).  Of the
+// nine products of two such sums the six down to 2^-16 of the leading one are formed; each is exact in
+// the fp32 accumulator, and the three left out are below 2^-22 and of either sign (the cut is followed
+// by a rounding), under the rounding that the sums themselves carry.
+__device__ __forceinline__ void split2_bf16(float x, float y, uint32_t& hi, uint32_t& mid, uint32_t& lo) {
+    const uint32_t ux = __float_as_uint(x), uy = __float_as_uint(y);
+    hi = __builtin_amdgcn_perm(uy, ux, 0x07060302u);
+    const float rx = x - __uint_as_float(ux & 0xFFFF0000u), ry = y - __uint_as_float(uy & 0xFFFF0000u);
+    mid = TrBF16::pack2(rx, ry);
+    lo = TrBF16::pack2(rx - __uint_as_float(mid << 16), ry - __uint_as_float(mid & 0xFFFF0000u));
+}
+
+// One thread's eight consecutive k, split and written to the three pieces of a staged operand row.
+template <int PIECE>      // elements between the pieces
+__device__ __forceinline__ void stage_split8(const float (&x)[8], uint16_t* dst) {
+    uint4 h, m, l;
+    split2_bf16(x[0], x[1], h.x, m.x, l.x);
+    split2_bf16(x[2], x[3], h.y, m.y, l.y);
+    split2_bf16(x[4], x[5], h.z, m.z, l.z);
+    split2_bf16(x[6], x[7], h.w, m.w, l.w);
+    *reinterpret_cast<uint4*>(dst) = h;
+    *reinterpret_cast<uint4*>(dst + PIECE) = m;
+    *reinterpret_cast<uint4*>(dst + 2 * PIECE) = l;
+}
+
+// One staged K tile (BK deep, both operands in three pieces, k contiguous, rows LD apart) added to a wave's
+// TM x TN block of 32x32 tiles; sa / sb: the lane's first word of its operand's first piece.  SWAP exchanges
+// the operands (a lane then holds runs of one row of the first).
+template <int TM, int TN, int BK, int LD, int A_PIECE, int B_PIECE, bool SWAP>
+__device__ __forceinline__ void mma_split(floatx16 (&acc)[TM][TN], const uint16_t* sa, const uint16_t* sb) {
+    constexpr int pa[6] = {2, 0, 1, 1, 0, 0}, pb[6] = {0, 2, 1, 0, 1, 0};     // smallest products first
+#pragma unroll
+    for (int kk = 0; kk < BK; kk += 16) {
+        uint4 fa[3][TM], fb[3][TN];
+#pragma unroll
+        for (int p = 2; p >= 0; --p) {
+#pragma unroll
+            for (int tm = 0; tm < TM; ++tm)
+                fa[p][tm] = *reinterpret_cast<const uint4*>(sa + p * A_PIECE + tm * 32 * LD + kk);
+#pragma unroll
+            for (int tn = 0; tn < TN; ++tn)
+                fb[2 - p][tn] = *reinterpret_cast<const uint4*>(sb + (2 - p) * B_PIECE + tn * 32 * LD + kk);
+        }
+#pragma unroll
+        for (int p = 0; p < 6; ++p)
+#pragma unroll
+            for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+                for (int tn = 0; tn < TN; ++tn)
+                    acc[tm][tn] = SWAP ? mfma16<TrBF16>(fb[pb[p]][tn], fa[pa[p]][tm], acc[tm][tn])
+                                       : mfma16<TrBF16>(fa[pa[p]][tm], fb[pb[p]][tn], acc[tm][tn]);
+    }
+}
+
+// Whether every sum of a wave is finite.  Where one is not, the caller zeroes them and forms them again with
+// the fp32 instruction.
+template <int TM, int TN>
+__device__ __forceinline__ bool wave_finite(const floatx16 (&acc)[TM][TN]) {
+    float f = 0.f;
+#pragma unroll
+    for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+        for (int tn = 0; tn < TN; ++tn)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) f = fmaf(acc[tm][tn][i], 0.f, f);
+    return !__any(!(f == 0.f));
+}
+
+template <int TM, int TN>
+__device__ __forceinline__ void zero_acc(floatx16 (&acc)[TM][TN]) {
+#pragma unroll
+    for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+        for (int tn = 0; tn < TN; ++tn)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[tm][tn][i] = 0.f;
+}
+
 // ------------------------------------------------------------ segmented mean --
 
 // Side job of the mean kernels for 2-byte types: the projection wants the weights with k
@@ -383,11 +462,12 @@ constexpr int kTreeMaxFan = 64;          // a group of siblings must fit the sma
 // groups of siblings, the deepest level's rows are not written when tree->mean_next is given, and
 // that array receives the next layer's neighbour means (same bits as the segmented-mean kernel
 // would give over the stored rows).  Needs rows of whole 16-byte words, every fan <= kTreeMaxFan, no n_rows_dev.
+// split: large fp32 products on the bf16 instruction (split2_bf16); slot-tree layers of fp32 need it.
 hopgnn_status project_dispatch(hopgnn_dtype dt, hipStream_t s, const void* Hsrc, const int32_t* self_idx,
                                const void* agg, const void* W_self, const void* W_neigh, const uint16_t* Wt,
                                int32_t KP, const void* bias, int64_t n_dst, int32_t d_in, int32_t k_total,
                                int32_t d_out, int relu, const void* zero, void* out, int out_f32,
-                               const int64_t* n_rows_dev, const TreeLayer* tree = nullptr);
+                               const int64_t* n_rows_dev, const TreeLayer* tree = nullptr, bool split = false);
 
 // Writes the transposed, zero-padded weights of one 2-byte layer (job.Wt, see TransposeJob) and
 // clears `zero_row` (zero_bytes, may be 0): what the segmented-mean kernel does as a side job, as
@@ -405,6 +485,6 @@ hopgnn_status sage_fwd_marked(const void* Hsrc, hopgnn_dtype dt, int64_t n_src, 
                               const int32_t* indptr, const int32_t* idx, int64_t n_dst, const int64_t* n_dst_dev,
                               const void* W_self, const void* W_neigh, const void* bias, int32_t d_out, int32_t agg,
                               int32_t relu, void* out, void* ws, size_t ws_bytes, void* stream,
-                              const LayerMarks* marks);
+                              const LayerMarks* marks, bool split = false);
 
 }  // namespace hopgnn

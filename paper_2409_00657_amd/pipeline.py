@@ -335,6 +335,11 @@ class HotPath:
         for per_batch in self._layer_args:
             for k in range(L):
                 per_batch[k] = per_batch[k][:-2] + (self._fwd_ws[k].data_ptr(), self._fwd_ws[k].numel())
+                if self.model == "sage" and self._layer_fn is self._lib.hopgnn_sage_fwd:
+                    # rows that a backward pass will mask by: the call that keeps the fp32 instruction's rounding
+                    per_batch[k] = per_batch[k][:-4] + (hb.AGG_MEAN,) + per_batch[k][-4:]
+        if self.model == "sage":
+            self._layer_fn = self._lib.hopgnn_sage_fwd_agg
         self._bwd_args = []
         hdt = hb.DTYPE_OF[dt]
         for b in range(self.group):
