@@ -11,9 +11,9 @@
 //
 // Hsrc, the weights and the stored forward output are in the activation type (fp32, bf16 or
 // fp16); gradients (dOut, gW, gbias, dHsrc) are always fp32 in memory.  For fp32 activations the
-// contractions run on the fp32 MFMA.  For 2-byte activations they run on the 2-byte MFMA with fp32
+// contractions run on the bf16 MFMA over operands split in three (split2_bf16).  For 2-byte activations they run on the 2-byte MFMA with fp32
 // accumulators, dZ rounded to the activation type on its way into LDS (shapes whose rows are not
-// whole 16-byte runs take the fp32 MFMA with the 2-byte operands widened instead); the bias gradient
+// whole 16-byte runs take the fp32 kernels with the 2-byte operands widened instead); the bias gradient
 // always sums fp32 values.  The weight gradient contracts over the destination
 // rows, which are split over workgroups; the partial tiles are summed in split order by a
 // second kernel, so gW/gbias are bit-stable from run to run.  dHsrc uses float atomic adds:
@@ -89,16 +89,18 @@ bwd_zero(float4* __restrict__ p, int64_t n4, const int64_t* __restrict__ n_rows_
 // ---------------------------------------------------------- weight gradient --
 //
 // G[k][n] = sum_r A[r][k] dZ[r][n] with A = [x_self | mean].  The contraction index r is the
-// MFMA's K dimension: for v_mfma_f32_32x32x2_f32 lane l feeds A[r + l/32][k0 + l%32] and
-// dZ[r + l/32][n0 + l%32], i.e. both operands are 32 consecutive floats of a row - no
-// transposition anywhere.  A workgroup (4 waves, 2 x 2) owns a 128 x 128 tile of G for the rows
-// [split*rows_per_split, ...), a wave a 64 x 64 piece (2 x 2 MFMA tiles: two A values and two
-// dZ values feed four MFMAs).  Rows are staged 16 at a time through LDS, so that every element
-// leaves global memory once per workgroup in a 128-bit load; the next chunk's loads (and the
-// self indices of the chunk after it) are in flight while the current chunk is multiplied.
+// MFMA's K dimension.  A workgroup (4 waves, 2 x 2) owns a 128 x 128 tile of G for the rows
+// [split*rows_per_split, ...), a wave a 64 x 64 piece (2 x 2 MFMA tiles).  Rows are staged 16 at a
+// time (one step of v_mfma_f32_32x32x16_bf16) through LDS, both operands split into three bf16 pieces
+// (split2_bf16), row-major; a lane's operand, 8 values down a column, comes from two transposing LDS
+// reads.  Every element leaves global memory once per workgroup in a 128-bit load; the next chunk's
+// loads (and the self indices of the chunk after it) are in flight while the current one is multiplied.
 // Every load is unconditional from a clamped, in-bounds address and masked when it is written
 // to LDS, which keeps the loop free of branches.  The tile goes to partial[split]; workgroups
 // of the first k-tile row also produce the column sums of dZ.
+// Bound by the matrix cores on v_mfma_f32_32x32x2_f32 (512 cycles per 32 x 32 x 16 block); the six
+// products of the split operands take 192.  A wave whose sums are not all finite forms them again with
+// the fp32 instruction straight from memory (the pieces of an infinity are not numbers).
 // The host sizes the row splits for the capacity; when only the device knows how many rows exist,
 // the rows that do are dealt out evenly over the same number of splits (multiples of 32 rows, never
 // more than the host's figure), so that no split idles while another works through the whole input.
@@ -113,7 +115,7 @@ __device__ __forceinline__ int32_t balanced_split(int32_t rows_per_split, int64_
 
 constexpr int kGradTile = 128;
 constexpr int kGradRows = 16;               // contraction rows per LDS chunk
-constexpr int kGradLd = kGradTile + 32;     // LDS row stride: the two rows of one MFMA step sit 32 banks apart
+constexpr int kGradLd = kGradTile + 32;     // 2-byte elements; the pitch of bwd_weight_grad16, for the same reads
 
 // One thread's share of a chunk: two rows (lr, lr + 8), four consecutive columns, of each operand.
 template <typename Tr>
@@ -122,6 +124,21 @@ struct GradFrag {
     float4 b[2];
     typename Raw4<Tr>::type o[2];      // MASK: the stored forward outputs that decide the ReLU mask
 };
+
+// 8 values down a column, rows row0 .. row0 + 7 of column col0 + lane % 32, as one MFMA operand: two
+// transposing LDS reads (ds_read_b64_tr_b16).  Within 16 lanes, lanes 4j .. 4j+3 name the four 8-byte
+// words of a 16-element piece of row j (j = 0..3), and lane i receives element i of each of the four
+// rows: four consecutive rows of ONE column, with no vector instruction spent on it.
+typedef short v4i16 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) v4i16 lds_v4i16;
+__device__ __forceinline__ uint4 tr_column8(const uint16_t* S, int ld, int row0, int col0, int lane) {
+    const int tr_row = (lane & 15) >> 2, tr_col = ((lane >> 4) & 1) * 16 + 4 * (lane & 3);
+    const uint16_t* p = S + (row0 + tr_row) * ld + col0 + tr_col;
+    union { uint4 v; v4i16 h[2]; } u;
+    u.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16*)p);
+    u.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16*)(p + 4 * ld));
+    return u.v;
+}
 
 // MASK: dZ is the incoming gradient itself and OutFwd the stored forward output; the ReLU mask is
 // applied on the way into LDS (a layer whose input gradient is not needed has no other reader of
@@ -133,8 +150,8 @@ bwd_weight_grad(const typename Tr::store_t* __restrict__ Hsrc, const int32_t* __
                 const typename Tr::store_t* __restrict__ OutFwd, int64_t n_dst, int32_t d_in,
                 int32_t d_out, int32_t rows_per_split, uint32_t tiles_n, float* __restrict__ partial,
                 float* __restrict__ bias_partial, const int64_t* __restrict__ n_rows_dev, int32_t k_self) {
-    __shared__ __attribute__((aligned(16))) float As[2][kGradRows][kGradLd];
-    __shared__ __attribute__((aligned(16))) float Bs[2][kGradRows][kGradLd];
+    __shared__ __attribute__((aligned(16))) uint16_t As[2][3][kGradRows][kGradLd];
+    __shared__ __attribute__((aligned(16))) uint16_t Bs[2][3][kGradRows][kGradLd];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int g = lane >> 5, l32 = lane & 31;
     const int wk = wave >> 1, wn = wave & 1;
@@ -187,6 +204,21 @@ bwd_weight_grad(const typename Tr::store_t* __restrict__ Hsrc, const int32_t* __
             }
         }
     };
+    // The bf16 instruction's own additions do not round to nearest, which adds up over thousands of rows.  So
+    // a chunk's products are summed from zero and added to the tile by ordinary additions, and every other row
+    // split sums the negated terms, so that the splits' shares of what is left cancel.  Error of 170 k rows x
+    // 100 x 256 (normal / all positive terms): 6.7e-7 / 6.9e-8 with the fp32 instruction; 9.5e-7 / 2.6e-7
+    // with neither measure, 5.7e-7 / 2.1e-7 with the negation alone, 8.8e-7 / 5.2e-8 with the sums alone.
+    const uint32_t flip = (blockIdx.y & 1) != 0 ? 0x80000000u : 0u;
+    float colsum[4] = {0.f, 0.f, 0.f, 0.f};      // of this thread's columns, over its rows
+    auto put = [&](const float (&v)[4], uint16_t (&S)[3][kGradRows][kGradLd], int row) {
+        uint2 h, m, l;
+        split2_bf16(v[0], v[1], h.x, m.x, l.x);
+        split2_bf16(v[2], v[3], h.y, m.y, l.y);
+        *reinterpret_cast<uint2*>(&S[0][row][lc]) = h;
+        *reinterpret_cast<uint2*>(&S[1][row][lc]) = m;
+        *reinterpret_cast<uint2*>(&S[2][row][lc]) = l;
+    };
     auto store = [&](int chunk, const int32_t (&sidx)[2], const GradFrag<Tr>& f, int buf) {
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
@@ -206,11 +238,12 @@ bwd_weight_grad(const typename Tr::store_t* __restrict__ Hsrc, const int32_t* __
             for (int e = 0; e < 4; ++e) {
                 const int k = ka + e, n = nb + e;
                 const bool a_ok = row_ok && k < K && (k >= k_self || sidx[i] >= 0);
-                av[e] = a_ok ? av[e] : 0.f;
+                av[e] = a_ok ? __uint_as_float(__float_as_uint(av[e]) ^ flip) : 0.f;
                 bv[e] = row_ok && n < d_out && ov[e] > 0.f ? bv[e] : 0.f;
+                colsum[e] += bv[e];
             }
-            *reinterpret_cast<float4*>(&As[buf][lr + 8 * i][lc]) = make_float4(av[0], av[1], av[2], av[3]);
-            *reinterpret_cast<float4*>(&Bs[buf][lr + 8 * i][lc]) = make_float4(bv[0], bv[1], bv[2], bv[3]);
+            put(av, As[buf], lr + 8 * i);
+            put(bv, Bs[buf], lr + 8 * i);
         }
     };
 
@@ -221,7 +254,6 @@ bwd_weight_grad(const typename Tr::store_t* __restrict__ Hsrc, const int32_t* __
         for (int j = 0; j < 2; ++j)
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
-    float colsum[2] = {0.f, 0.f};
 
     int32_t s_cur[2] = {self_of(0, 0), self_of(0, 1)};
     int32_t s_nxt[2] = {self_of(1, 0), self_of(1, 1)};
@@ -237,24 +269,61 @@ bwd_weight_grad(const typename Tr::store_t* __restrict__ Hsrc, const int32_t* __
         s_cur[1] = s_nxt[1];
         s_nxt[0] = self_of(c + 2, 0);
         s_nxt[1] = self_of(c + 2, 1);
+        uint4 fa[3][2], fb[3][2];
 #pragma unroll
-        for (int st = 0; st < kGradRows / 2; ++st) {
-            const int row = 2 * st + g;
-            const float a0 = As[buf][row][wk * 64 + l32], a1 = As[buf][row][wk * 64 + 32 + l32];
-            const float b0 = Bs[buf][row][wn * 64 + l32], b1 = Bs[buf][row][wn * 64 + 32 + l32];
-            acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0, b0, acc[0][0], 0, 0, 0);
-            acc[0][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0, b1, acc[0][1], 0, 0, 0);
-            acc[1][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1, b0, acc[1][0], 0, 0, 0);
-            acc[1][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1, b1, acc[1][1], 0, 0, 0);
-            colsum[0] += b0;
-            colsum[1] += b1;
+        for (int p = 2; p >= 0; --p)
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                fa[p][i] = tr_column8(&As[buf][p][0][0], kGradLd, 8 * g, (2 * wk + i) * 32, lane);
+                fb[2 - p][i] = tr_column8(&Bs[buf][2 - p][0][0], kGradLd, 8 * g, (2 * wn + i) * 32, lane);
+            }
+        constexpr int pa[6] = {2, 0, 1, 1, 0, 0}, pb[6] = {0, 2, 1, 0, 1, 0};     // smallest products first
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            floatx16 sum[1][2];
+            zero_acc<1, 2>(sum);
+#pragma unroll
+            for (int p = 0; p < 6; ++p)
+#pragma unroll
+                for (int j = 0; j < 2; ++j) sum[0][j] = mfma16<TrBF16>(fa[pa[p]][i], fb[pb[p]][j], sum[0][j]);
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) acc[i][j][e] += sum[0][j][e];
         }
         store(c + 1, s_cur, f, buf ^ 1);
         lds_barrier();
     }
 
-    // partial[split][k][n]; accumulator register e of lane l holds G row 8*(e/4)+4*(l/32)+e%4, col l%32
     const int k0 = (int)tk * kGradTile + wk * 64, n0 = (int)tn * kGradTile + wn * 64;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[i][j][e] = __uint_as_float(__float_as_uint(acc[i][j][e]) ^ flip);
+    if (!wave_finite<2, 2>(acc)) {     // v_mfma_f32_32x32x2_f32: lane l feeds A[r + l/32][k0 + l%32], dZ[r + l/32][n0 + l%32]
+        zero_acc<2, 2>(acc);
+        for (int64_t r = r0 + g; r - g < r1; r += 2) {
+            float a[2], b[2];
+            const bool row_ok = r < r1;
+            const int64_t srow = !row_ok ? -1 : self_idx != nullptr ? (int64_t)self_idx[r] : r;
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const int k = k0 + i * 32 + l32, n = n0 + i * 32 + l32;
+                a[i] = !row_ok || k >= K ? 0.f
+                       : k < k_self      ? (srow >= 0 ? Tr::to_f(Hsrc[srow * d_in + k]) : 0.f)
+                                         : Tr::to_f(Mean[r * d_in + k - k_self]);
+                b[i] = row_ok && n < d_out && (!MASK || Tr::to_f(OutFwd[r * d_out + n]) > 0.f) ? dZ[r * d_out + n] : 0.f;
+            }
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[j], acc[i][j], 0, 0, 0);
+        }
+    }
+
+    // partial[split][k][n]; accumulator register e of lane l holds G row 8*(e/4)+4*(l/32)+e%4, col l%32
     float* P = partial + (int64_t)blockIdx.y * K * d_out;
 #pragma unroll
     for (int i = 0; i < 2; ++i)
@@ -268,12 +337,19 @@ bwd_weight_grad(const typename Tr::store_t* __restrict__ Hsrc, const int32_t* __
                 if (kk < K) P[(int64_t)kk * d_out + n] = acc[i][j][e];
             }
         }
-    if (bias_partial != nullptr && tk == 0 && wk == 0) {   // one wave per 64-column block
+    if (bias_partial != nullptr && tk == 0) {
+        // the row groups' sums of every column, added in a fixed order (the staging tiles are free: the
+        // loop's last barrier is behind every read of them)
+        float* cs = reinterpret_cast<float*>(&As[0][0][0][0]);      // [8][kGradTile]
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const float cs = colsum[j] + __shfl_xor(colsum[j], 32, kWave);   // even rows + odd rows
-            const int n = n0 + j * 32 + l32;
-            if (g == 0 && n < d_out) bias_partial[(int64_t)blockIdx.y * d_out + n] = cs;
+        for (int e = 0; e < 4; ++e) cs[lr * kGradTile + lc + e] = colsum[e];
+        lds_barrier();
+        if (tid < kGradTile) {
+            float t = 0.f;
+#pragma unroll
+            for (int q = 0; q < 8; ++q) t += cs[q * kGradTile + tid];
+            const int n = (int)tn * kGradTile + tid;
+            if (n < d_out) bias_partial[(int64_t)blockIdx.y * d_out + n] = t;
         }
     }
 }
@@ -410,21 +486,6 @@ bwd_weight_grad16(const typename Tr::store_t* __restrict__ Hsrc, const int32_t* 
             *reinterpret_cast<uint2*>(&Bs[buf][br + B_ROWS * i][bc]) = make_uint2(Tr::pack2(bv[0], bv[1]), Tr::pack2(bv[2], bv[3]));
         }
     };
-    // 8 values down a column, rows row0 .. row0 + 7 of column col0 + lane % 32, as one MFMA operand: two
-    // transposing LDS reads (ds_read_b64_tr_b16).  Within 16 lanes, lanes 4j .. 4j+3 name the four 8-byte
-    // words of a 16-element piece of row j (j = 0..3), and lane i receives element i of each of the four
-    // rows: four consecutive rows of ONE column, with no vector instruction spent on it.
-    typedef short v4i16 __attribute__((ext_vector_type(4)));
-    typedef __attribute__((address_space(3))) v4i16 lds_v4i16;
-    const int tr_row = (lane & 15) >> 2, tr_col = ((lane >> 4) & 1) * 16 + 4 * (lane & 3);
-    auto column8 = [&](const uint16_t* S, int ld, int row0, int col0) -> uint4 {
-        const uint16_t* p = S + (row0 + tr_row) * ld + col0 + tr_col;
-        union { uint4 v; v4i16 h[2]; } u;
-        u.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16*)p);
-        u.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16*)(p + 4 * ld));
-        return u.v;
-    };
-
     floatx16 acc[TM][TN];
 #pragma unroll
     for (int i = 0; i < TM; ++i)
@@ -461,9 +522,9 @@ bwd_weight_grad16(const typename Tr::store_t* __restrict__ Hsrc, const int32_t* 
         for (int kk = 0; kk < kG16Rows; kk += 16) {
             uint4 a[TM], b[TN];
 #pragma unroll
-            for (int i = 0; i < TM; ++i) a[i] = column8(&As[buf][0][0], LDA, kk + 8 * g, (wk * TM + i) * 32);
+            for (int i = 0; i < TM; ++i) a[i] = tr_column8(&As[buf][0][0], LDA, kk + 8 * g, (wk * TM + i) * 32, lane);
 #pragma unroll
-            for (int j = 0; j < TN; ++j) b[j] = column8(&Bs[buf][0][0], LDB, kk + 8 * g, (wn * TN + j) * 32);
+            for (int j = 0; j < TN; ++j) b[j] = tr_column8(&Bs[buf][0][0], LDB, kk + 8 * g, (wn * TN + j) * 32, lane);
 #pragma unroll
             for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -546,19 +607,22 @@ bwd_weight_reduce(const float* __restrict__ partial, const float* __restrict__ b
 // ----------------------------------------------------------- input gradient --
 //
 // D[r][j] = sum_n dZ[r][n] Wcat[j][n], j over the 2*d_in rows of [W_self ; W_neigh].  Both
-// operands have the contraction index contiguous, so both sit in LDS row-major [64][BK+4] and
-// are read as 128-bit words: lane group g = l/32 takes the four n values 4g..4g+3 of an 8-wide
-// block and the block's four MFMAs pair the i-th values (a permutation of the summation order).
-template <typename Tr>
-__global__ void __launch_bounds__(kBwdThreads)
+// operands have the contraction index contiguous; both are split into three bf16 pieces on their way to
+// LDS (see split2_bf16: six products of 192 cycles in all against 512 of the fp32 instruction), two K
+// tiles in LDS and two in registers as in the fp32 projection.  4 waves (2 x 2), each a
+// (BM/2) x (BN/2) piece of D.  VEC: d_out % 4 == 0, whole words of four.
+template <typename Tr, int BM, int BN, int BK, bool VEC>
+__global__ void __launch_bounds__(kBwdThreads, 2)
 bwd_input_grad(const float* __restrict__ dZ, const typename Tr::store_t* __restrict__ Wself,
                const typename Tr::store_t* __restrict__ Wneigh, int64_t n_dst_cap, int32_t d_in, int32_t d_out,
                float* __restrict__ D, const int64_t* __restrict__ n_rows_dev, int32_t k_self) {
     using T = typename Tr::store_t;
     using R4 = typename Raw4<Tr>::type;
-    constexpr int BM = 64, BN = 64, BK = 16, LD = BK + 4;
-    __shared__ __attribute__((aligned(16))) float As[BM][LD];
-    __shared__ __attribute__((aligned(16))) float Bs[BN][LD];
+    constexpr int LD = BK + 8, TM = BM / 64, TN = BN / 64;
+    constexpr int A_ITEMS = BM * BK / 8 / kBwdThreads, B_ITEMS = BN * BK / 8 / kBwdThreads;
+    static_assert(A_ITEMS >= 1 && B_ITEMS >= 1 && BK % 16 == 0 && (LD / 8) % 2 == 1, "tile");
+    constexpr int A_PIECE = BM * LD, B_PIECE = BN * LD, STAGE = 3 * (A_PIECE + B_PIECE);
+    extern __shared__ __attribute__((aligned(16))) uint16_t lds16[];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int g = lane >> 5, l32 = lane & 31;
     const int wm = wave >> 1, wn = wave & 1;
@@ -567,78 +631,151 @@ bwd_input_grad(const float* __restrict__ dZ, const typename Tr::store_t* __restr
     if (row0 >= n_dst) return;                 // uniform over the workgroup
     const int col0 = blockIdx.y * BN;
     const int N = k_self + d_in;        // rows of [W_self ; W_neigh], or of the one matrix (k_self = 0)
-    const bool vec = (d_out & 3) == 0;
 
-    // one 16-byte item of each tile per thread: row tid/4, words (tid%4)*4 .. +3
-    const int lr = tid >> 2, lk = (tid & 3) * 4;
-    const int64_t ar = row0 + lr;
-    const int bj = col0 + lr;
-    const float* arow = ar < n_dst ? dZ + ar * d_out : nullptr;
-    const T* brow = bj < N ? (bj < k_self ? Wself + (int64_t)bj * d_out : Wneigh + (int64_t)(bj - k_self) * d_out)
-                           : nullptr;
-    auto load4w = [&](const T* row, int kq) {      // raw weight elements, widened when they go to LDS
-        union { R4 v; T e[4]; } u;
+    // items of eight k: row (item / (BK/8)) of the tile, k (item % (BK/8)) * 8; rows past the end repeat
+    // row 0 of the operand and are zeroed on their way to LDS
+    const float* arow[A_ITEMS];
+    const T* brow[B_ITEMS];
+    bool a_ok[A_ITEMS], b_ok[B_ITEMS];
+    const int lk = (tid % (BK / 8)) * 8;
+    static_assert(kBwdThreads % (BK / 8) == 0, "one k per thread for all items");
 #pragma unroll
-        for (int e = 0; e < 4; ++e) u.e[e] = Tr::from_f(0.f);
-        if (row != nullptr) {
-            if (vec && kq + 3 < d_out) {
-                u.v = *reinterpret_cast<const R4*>(row + kq);
+    for (int i = 0; i < A_ITEMS; ++i) {
+        const int64_t r = row0 + (i * kBwdThreads + tid) / (BK / 8);
+        a_ok[i] = r < n_dst;
+        arow[i] = dZ + (a_ok[i] ? r : 0) * d_out;
+    }
+#pragma unroll
+    for (int i = 0; i < B_ITEMS; ++i) {
+        const int j = col0 + (i * kBwdThreads + tid) / (BK / 8);
+        b_ok[i] = j < N;
+        const int jj = b_ok[i] ? j : 0;
+        brow[i] = jj < k_self ? Wself + (int64_t)jj * d_out : Wneigh + (int64_t)(jj - k_self) * d_out;
+    }
+    struct Regs {
+        float4 a[A_ITEMS][2];
+        R4 b[B_ITEMS][2];
+    };
+    auto load = [&](Regs& R, int t) {      // unconditional loads from clamped addresses
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int k = t * BK + lk + 4 * h;
+            if (VEC) {
+                const int kc = k < d_out ? k : 0;
+#pragma unroll
+                for (int i = 0; i < A_ITEMS; ++i) R.a[i][h] = *reinterpret_cast<const float4*>(arow[i] + kc);
+#pragma unroll
+                for (int i = 0; i < B_ITEMS; ++i) R.b[i][h] = *reinterpret_cast<const R4*>(brow[i] + kc);
             } else {
 #pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    if (kq + e < d_out) u.e[e] = row[kq + e];
+                for (int i = 0; i < A_ITEMS; ++i) {
+                    float v[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) v[e] = arow[i][k + e < d_out ? k + e : 0];
+                    R.a[i][h] = make_float4(v[0], v[1], v[2], v[3]);
+                }
+#pragma unroll
+                for (int i = 0; i < B_ITEMS; ++i) {
+                    union { R4 v; T e[4]; } u;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) u.e[e] = brow[i][k + e < d_out ? k + e : 0];
+                    R.b[i][h] = u.v;
+                }
             }
         }
-        return u.v;
     };
-    auto load4 = [&](const float* row, int kq) {
-        float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (row != nullptr) {
-            if (vec && kq + 3 < d_out) {
-                v = *reinterpret_cast<const float4*>(row + kq);
-            } else {
-                if (kq + 0 < d_out) v.x = row[kq + 0];
-                if (kq + 1 < d_out) v.y = row[kq + 1];
-                if (kq + 2 < d_out) v.z = row[kq + 2];
-                if (kq + 3 < d_out) v.w = row[kq + 3];
-            }
+    auto put = [&](const float4 (&v)[2], bool ok, int t, uint16_t* dst, auto piece) {
+        float x[8] = {v[0].x, v[0].y, v[0].z, v[0].w, v[1].x, v[1].y, v[1].z, v[1].w};
+#pragma unroll
+        for (int e = 0; e < 8; ++e) x[e] = ok && t * BK + lk + e < d_out ? x[e] : 0.f;
+        stage_split8<decltype(piece)::value>(x, dst);
+    };
+    auto store = [&](const Regs& R, int t, int st) {
+        uint16_t* s = lds16 + st * STAGE;
+#pragma unroll
+        for (int i = 0; i < A_ITEMS; ++i)
+            put(R.a[i], a_ok[i], t, s + ((i * kBwdThreads + tid) / (BK / 8)) * LD + lk, std::integral_constant<int, A_PIECE>{});
+#pragma unroll
+        for (int i = 0; i < B_ITEMS; ++i) {
+            const float4 w[2] = {Raw4<Tr>::widen(R.b[i][0]), Raw4<Tr>::widen(R.b[i][1])};
+            put(w, b_ok[i], t, s + 3 * A_PIECE + ((i * kBwdThreads + tid) / (BK / 8)) * LD + lk,
+                std::integral_constant<int, B_PIECE>{});
         }
-        return v;
     };
 
-    floatx16 acc;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) acc[i] = 0.f;
+    floatx16 acc[TM][TN];
+    zero_acc<TM, TN>(acc);
     const int n_tiles = (d_out + BK - 1) / BK;
-    float4 ra = load4(arow, lk);
-    R4 rb = load4w(brow, lk);
-    for (int t = 0; t < n_tiles; ++t) {
-        __syncthreads();
-        *reinterpret_cast<float4*>(&As[lr][lk]) = ra;
-        *reinterpret_cast<float4*>(&Bs[lr][lk]) = Raw4<Tr>::widen(rb);
-        __syncthreads();
-        if (t + 1 < n_tiles) {
-            ra = load4(arow, (t + 1) * BK + lk);
-            rb = load4w(brow, (t + 1) * BK + lk);
-        }
+    Regs r[2];
+    load(r[0], 0);
+    store(r[0], 0, 0);
+    load(r[1], 1);
+    lds_barrier();
+    auto iter = [&](int t, int i) {     // i = t % 2, a constant after unrolling; tiles past the end are zeros, never multiplied
+        load(r[i], t + 2);
+        mma_split<TM, TN, BK, LD, A_PIECE, B_PIECE, false>(
+            acc, lds16 + i * STAGE + (wm * (BM / 2) + l32) * LD + g * 8,
+            lds16 + i * STAGE + 3 * A_PIECE + (wn * (BN / 2) + l32) * LD + g * 8);
+        store(r[i ^ 1], t + 1, i ^ 1);
+        lds_barrier();
+    };
+    int t = 0;
+    for (; t + 2 <= n_tiles; t += 2) {
+        iter(t, 0);
+        iter(t + 1, 1);
+    }
+    if (t < n_tiles) iter(t, 0);
+
+    const int64_t wrow = row0 + wm * (BM / 2);
+    const int wcol = col0 + wn * (BN / 2);
+    if (!wave_finite<TM, TN>(acc)) {     // v_mfma_f32_32x32x2_f32: lane l feeds dZ[row l%32][k = l/32], W[row l%32][k = l/32]
+        zero_acc<TM, TN>(acc);
+        for (int k = g; k - g < d_out; k += 2) {
+            float a[TM], b[TN];
 #pragma unroll
-        for (int kk = 0; kk < BK; kk += 8) {
-            const float4 a = *reinterpret_cast<const float4*>(&As[wm * 32 + l32][kk + 4 * g]);
-            const float4 b = *reinterpret_cast<const float4*>(&Bs[wn * 32 + l32][kk + 4 * g]);
-            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x, b.x, acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.y, b.y, acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.z, b.z, acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.w, b.w, acc, 0, 0, 0);
+            for (int tm = 0; tm < TM; ++tm) {
+                const int64_t row = wrow + tm * 32 + l32;
+                a[tm] = row < n_dst && k < d_out ? dZ[row * d_out + k] : 0.f;
+            }
+#pragma unroll
+            for (int tn = 0; tn < TN; ++tn) {
+                const int j = wcol + tn * 32 + l32;
+                b[tn] = j < N && k < d_out ? Tr::to_f((j < k_self ? Wself + (int64_t)j * d_out : Wneigh + (int64_t)(j - k_self) * d_out)[k]) : 0.f;
+            }
+#pragma unroll
+            for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+                for (int tn = 0; tn < TN; ++tn) acc[tm][tn] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[tm], b[tn], acc[tm][tn], 0, 0, 0);
         }
     }
-    const int col = col0 + wn * 32 + l32;
-    if (col < N) {
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            const int64_t row = row0 + wm * 32 + 8 * (i / 4) + 4 * g + (i & 3);
-            if (row < n_dst) D[row * N + col] = acc[i];
-        }
+    for (int tn = 0; tn < TN; ++tn) {
+        const int col = wcol + tn * 32 + l32;
+        if (col >= N) continue;
+#pragma unroll
+        for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                const int64_t row = wrow + tm * 32 + 8 * (i / 4) + 4 * g + (i & 3);
+                if (row < n_dst) D[row * N + col] = acc[tm][tn][i];
+            }
     }
+}
+
+template <typename Tr, int BM, int BN, int BK>
+static hopgnn_status launch_input_grad_tile(hipStream_t s, const float* dZ, const typename Tr::store_t* W_self,
+                                            const typename Tr::store_t* W_neigh, int64_t n_dst, int32_t d_in, int32_t d_out,
+                                            float* D, const int64_t* n_rows_dev, int32_t k_self) {
+    const int64_t gy = ceil_div((int64_t)k_self + d_in, BN);
+    constexpr size_t lds = (size_t)2 * 3 * (BM + BN) * (BK + 8) * sizeof(uint16_t);
+    auto kern = d_out % 4 == 0 ? bwd_input_grad<Tr, BM, BN, BK, true> : bwd_input_grad<Tr, BM, BN, BK, false>;
+    if (lds > 64 * 1024 && hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
+        return HOPGNN_EHIP;
+    hipLaunchKernelGGL(kern, dim3((unsigned)ceil_div(n_dst, BM), (unsigned)gy), dim3(kBwdThreads), lds, s, dZ, W_self, W_neigh,
+                       n_dst, d_in, d_out, D, n_rows_dev, k_self);
+    HOPGNN_LAUNCH_CHECK();
+    return HOPGNN_OK;
 }
 
 // The same product for 2-byte activations on v_mfma_f32_32x32x16_{bf16,f16}: the weights as stored,
@@ -726,6 +863,25 @@ bwd_input_grad16(const float* __restrict__ dZ, const typename Tr::store_t* __res
             if (row < n_dst) D[row * N + col] = acc[i];
         }
     }
+}
+
+// The large tile once there are enough of them to give every CU two workgroups (the rule of the fp32
+// projection).  2-byte weights on 16-byte boundaries take the 2-byte kernel.
+template <typename Tr>
+static hopgnn_status launch_input_grad(hipStream_t s, const float* dZ, const typename Tr::store_t* W_self,
+                                       const typename Tr::store_t* W_neigh, int64_t n_dst, int32_t d_in, int32_t d_out,
+                                       float* D, const int64_t* n_rows_dev, int32_t k_self) {
+    if constexpr (sizeof(typename Tr::store_t) == 2) {
+        if (aligned(dZ, 16) && aligned(W_self, 16) && aligned(W_neigh, 16)) {
+            hipLaunchKernelGGL(bwd_input_grad16<Tr>, dim3((unsigned)ceil_div(n_dst, 64), (unsigned)ceil_div((int64_t)k_self + d_in, 64)),
+                               dim3(kBwdThreads), 0, s, dZ, W_self, W_neigh, n_dst, d_in, d_out, D, n_rows_dev, k_self);
+            HOPGNN_LAUNCH_CHECK();
+            return HOPGNN_OK;
+        }
+    }
+    if (ceil_div(n_dst, 128) * ceil_div((int64_t)k_self + d_in, 128) >= 512)
+        return launch_input_grad_tile<Tr, 128, 128, 16>(s, dZ, W_self, W_neigh, n_dst, d_in, d_out, D, n_rows_dev, k_self);
+    return launch_input_grad_tile<Tr, 64, 64, 32>(s, dZ, W_self, W_neigh, n_dst, d_in, d_out, D, n_rows_dev, k_self);
 }
 
 // dHsrc[self_idx[r]] += D[r][:d_in];  dHsrc[idx[e]] += D[r][d_in:] / c_r for the valid entries e.
@@ -1075,14 +1231,9 @@ static hopgnn_status sage_bwd_typed(const void* Hsrc, int64_t n_src, int32_t d_i
     if (dHsrc != nullptr && n_src > 0) {
         const int64_t gy = ceil_div((int64_t)k_self + d_in, 64);
         if (gy > 65535) return HOPGNN_ERANGE;
-        auto in_kernel = bwd_input_grad<Tr>;
-        if constexpr (sizeof(T) == 2) {
-            if (aligned(dZ, 16) && aligned(W_self, 16) && aligned(W_neigh, 16)) in_kernel = bwd_input_grad16<Tr>;
-        }
-        hipLaunchKernelGGL(in_kernel, dim3((unsigned)ceil_div(n_dst, 64), (unsigned)gy), dim3(kBwdThreads), 0, s, dZ,
-                           static_cast<const T*>(W_self), static_cast<const T*>(W_neigh), n_dst, d_in, d_out, D, n_dst_dev,
-                           k_self);
-        HOPGNN_LAUNCH_CHECK();
+        const hopgnn_status st = launch_input_grad<Tr>(s, dZ, static_cast<const T*>(W_self), static_cast<const T*>(W_neigh),
+                                                       n_dst, d_in, d_out, D, n_dst_dev, k_self);
+        if (st != HOPGNN_OK) return st;
         const int group = mean_group(d_in);
         if (kind.scatter != kScatterMean)
             hipLaunchKernelGGL(bwd_scatter_kind<Tr>, dim3((unsigned)ceil_div(n_dst * group, kBwdThreads)), dim3(kBwdThreads),
@@ -1546,13 +1697,9 @@ static hopgnn_status gat_bwd_typed(const void* Hsrc, int64_t n_src, const int64_
     if (dHsrc != nullptr) {      // dHsrc = dz W^T, every element written
         const int64_t gy = ceil_div(d_in, 64);
         if (gy > 65535) return HOPGNN_ERANGE;
-        auto in_kernel = bwd_input_grad<Tr>;
-        if constexpr (sizeof(T) == 2) {
-            if (aligned(W, 16)) in_kernel = bwd_input_grad16<Tr>;
-        }
-        hipLaunchKernelGGL(in_kernel, dim3((unsigned)ceil_div(n_src, 64), (unsigned)gy), dim3(kBwdThreads), 0, s, dZ,
-                           static_cast<const T*>(W), static_cast<const T*>(W), n_src, d_in, d_out, dHsrc, n_src_dev, 0);
-        HOPGNN_LAUNCH_CHECK();
+        const hopgnn_status st = launch_input_grad<Tr>(s, dZ, static_cast<const T*>(W), static_cast<const T*>(W), n_src, d_in,
+                                                       d_out, dHsrc, n_src_dev, 0);
+        if (st != HOPGNN_OK) return st;
     }
     return HOPGNN_OK;
 }

@@ -1,0 +1,104 @@
+"""The fp32 contractions (projection of the single-call pass, weight gradient, input gradient) as six bf16 products of split operands:
+tile edges, magnitudes at both ends of the type, and infinities, against 64-bit products."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+# A sum of K products in fp32: rounding errors of 2^-24 each, their square root over K of it; a factor of 4 for
+# the worst of a tensor's elements over the tensor's scale.  The three products left out stay below 2^-22.
+BOUND = lambda K: 4 * max(K, 16) ** 0.5 * 2.0 ** -24
+
+# (rows, d_in, d_out): one row and word, remainders of the 64-row tile, widths off the 16-byte grid, the first
+# sizes of the 128-row tile (512 tiles and more) with remainders in every direction
+SHAPES = [(1, 4, 4), (63, 20, 12), (65, 7, 5), (129, 100, 256), (64, 16, 64), (33000, 36, 132), (65537, 12, 68)]
+
+
+@pytest.fixture(scope="module")
+def hb():
+    from paper_2409_00657_amd import binding
+    binding.load_library()
+    return binding
+
+
+def _inputs(n, d_in, d_out, seed=0):
+    g = torch.Generator(device=DEV).manual_seed(seed)
+    r = lambda *s: torch.randn(s, generator=g, device=DEV)
+    H, Ws, Wn, G = r(n, d_in), r(d_in, d_out) / d_in ** 0.5, r(d_in, d_out) / d_in ** 0.5, r(n, d_out)
+    idx = torch.randperm(n, generator=g, device=DEV).to(torch.int32)      # one neighbour each: the mean is its row
+    return H, Ws, Wn, G, torch.arange(n + 1, device=DEV, dtype=torch.int32), idx
+
+
+def _forward(H, Ws, Wn, idx):
+    """Every vertex has one neighbour and is a root: the single-call pass is the plain layer over all rows."""
+    from paper_2409_00657_amd.pipeline import HotPath
+    n, out = H.shape[0], torch.empty((H.shape[0], Ws.shape[1]), device=DEV)
+    hp = HotPath(torch.arange(n + 1, device=DEV, dtype=torch.int64), idx, H, [(Ws, Wn, None)], n, [1])
+    hp.forward(torch.arange(n, device=DEV, dtype=torch.int32), [3], out)
+    return out
+
+
+def _backward(hb, H, Ws, Wn, G, indptr, idx):
+    n, (d_in, d_out) = H.shape[0], Ws.shape
+    gWs, gWn, gb = torch.zeros_like(Ws), torch.zeros_like(Wn), torch.zeros(d_out, device=DEV)
+    dH = torch.empty_like(H)
+    ws = torch.empty(hb.hopgnn_sage_bwd_ws_bytes(H.dtype, n, d_in, d_out, True), dtype=torch.uint8, device=DEV)
+    hb.hopgnn_sage_bwd(H, n, None, indptr, idx, n, Ws, Wn, None, False, G, gWs, gWn, gb, dH, ws)
+    return gWs, gWn, gb, dH
+
+
+def _err(a, ref):
+    return float(((a.double() - ref).abs().max() / ref.pow(2).mean().sqrt()).item())
+
+
+def _ref(H, Ws, Wn, G, idx):
+    H, Ws, Wn, G, i = H.double(), Ws.double(), Wn.double(), G.double(), idx.long()
+    dH = G @ Ws.t().contiguous()
+    dH.index_add_(0, i, G @ Wn.t().contiguous())
+    return H @ Ws + H[i] @ Wn, (H.t().contiguous() @ G, H[i].t().contiguous() @ G, G.sum(0), dH)
+
+
+@pytest.mark.parametrize("shape", SHAPES)
+@pytest.mark.parametrize("scale", [1.0, 1e-30])
+def test_products_of_split_operands(hb, shape, scale):
+    n, d_in, d_out = shape
+    H, Ws, Wn, G, indptr, idx = _inputs(*shape)
+    H, G = H * scale, G * scale
+    out_ref, bwd_ref = _ref(H, Ws, Wn, G, idx)
+    out = _forward(H, Ws, Wn, idx)
+    assert _err(out, out_ref) <= BOUND(2 * d_in)
+    if scale != 1.0:
+        G = G / scale          # their product with H stays a normal number
+        bwd_ref = _ref(H, Ws, Wn, G, idx)[1]
+    grads = _backward(hb, H, Ws, Wn, G, indptr, idx)
+    for a, ref, K in zip(grads, bwd_ref, (n, n, n, 2 * d_out)):
+        assert _err(a, ref) <= BOUND(K)
+
+
+@pytest.mark.parametrize("shape", [(65, 20, 12), (65, 7, 5), (33000, 36, 132)])
+def test_infinities_and_the_largest_floats(hb, shape):
+    """An infinite operand gives the infinities and NaNs of the plain products, and only in its own row (column)."""
+    n, d_in, d_out = shape
+    H, Ws, Wn, G, indptr, idx = _inputs(*shape, seed=1)
+    big = torch.finfo(torch.float32).max      # rounds to infinity as bf16
+    H[3, 1], H[5, 2], H[n - 1, d_in - 1], H[7, 0] = float("inf"), -float("inf"), float("nan"), big
+    Ws[0], Wn[0] = 0.25, -0.125
+    out_ref, _ = _ref(H, Ws, Wn, G, idx)
+    out = _forward(H, Ws, Wn, idx)
+    ref32 = out_ref.float()
+    assert torch.equal(torch.isnan(out), torch.isnan(ref32)) and torch.equal(torch.isposinf(out), torch.isposinf(ref32))
+    assert torch.equal(torch.isneginf(out), torch.isneginf(ref32))
+    rows = torch.isfinite(ref32).all(1) & (ref32.abs().amax(1) < 1e30)
+    assert _err(out[rows], out_ref[rows]) <= BOUND(2 * d_in)
+    huge = torch.isfinite(ref32).all(1) & ~rows
+    assert int(huge.sum()) == 2 and torch.allclose(out[huge].double(), out_ref[huge], rtol=BOUND(2 * d_in))
+
+    H, Ws, Wn, G, indptr, idx = _inputs(*shape, seed=2)
+    G[4, 2], G[n - 1, 0] = float("inf"), -float("inf")
+    _, ref = _ref(H, Ws, Wn, G, idx)
+    for a, r in zip(_backward(hb, H, Ws, Wn, G, indptr, idx), ref):
+        r32 = r.float()
+        for kind in (torch.isnan, torch.isposinf, torch.isneginf):
+            assert torch.equal(kind(a), kind(r32))
+        ok = torch.isfinite(r32)
+        assert float(((a[ok].double() - r[ok]).abs().max() / r[ok].pow(2).mean().sqrt()).item()) <= BOUND(max(n, 2 * d_out))
