@@ -521,7 +521,7 @@ hopgnn_status hopgnn_gcn_bwd(const void *Hsrc, hopgnn_dtype dt, int64_t n_src, i
  *          bytes (0 for invalid arguments), 256-byte aligned.
  * Arithmetic is fp32; with a 2-byte dt the gradient with respect to z is rounded to dt before the
  * two matrix products (gW, dHsrc) as in hopgnn_sage_bwd.  The sums over destination rows into a
- * source row (dz, score gradients) are float atomic adds: their rounding depends on arrival order.
+ * source row (dz, score gradients) are taken in no fixed order: their rounding may differ by call.
  * gbias, ga_src and ga_dst are summed in a fixed order.  Errors as hopgnn_gat_fwd, plus EINVAL for
  * a NULL fwd_ws or a ReLU without out_fwd, ENOMEM_WS for a short workspace.
  */

@@ -1393,7 +1393,7 @@ __device__ __forceinline__ float wave_sum(float v) {
 }
 __device__ __forceinline__ float leaky02(float x) { return x > 0.f ? x : 0.2f * x; }
 
-constexpr int kColRows = 128;    // rows per workgroup of the column-sum kernels
+constexpr int kColRows = 64;     // rows per workgroup of the column-sum kernel
 
 // partial[b][n] = sum over the rows of block b of dOut[r][n] where the activation passes
 template <typename Tr>
@@ -1404,33 +1404,358 @@ col_sum_rows(const float* __restrict__ dOut, const typename Tr::store_t* __restr
     const int64_t r1 = r0 + kColRows < n_rows ? r0 + kColRows : n_rows;
     for (int32_t n = threadIdx.x; n < d_out; n += kBwdThreads) {
         float acc = 0.f;
-        for (int64_t r = r0; r < r1; ++r) {
-            const float g = dOut[r * d_out + n];
-            acc += !relu || Tr::to_f(out_fwd[r * d_out + n]) > 0.f ? g : 0.f;
+        if (relu) {
+#pragma unroll 8
+            for (int64_t r = r0; r < r1; ++r) {
+                const float g = dOut[r * d_out + n];
+                acc += Tr::to_f(out_fwd[r * d_out + n]) > 0.f ? g : 0.f;
+            }
+        } else {
+#pragma unroll 8
+            for (int64_t r = r0; r < r1; ++r) acc += dOut[r * d_out + n];
         }
         partial[(int64_t)blockIdx.x * d_out + n] = acc;
     }
 }
 
 // out[i] += sum over p < n_parts of partial[p * part_stride + i], i < width, in a fixed order (wave q
-// takes the parts q, q + 4, ...; the four sums are combined as (s0 + s1) + (s2 + s3)): bit-stable.
-// With a device row count only the parts of the rows that exist are summed (rows_per_part rows each).
-__global__ void __launch_bounds__(kBwdThreads)
+// takes the parts q, q + 16, ...; the sixteen sums are added in wave order): bit-stable.  The parts are a
+// chain of dependent adds behind independent loads: sixteen waves with four loads each in flight (four
+// waves with one took 33 us a call on the attention layers' parts).
+constexpr int kReduceWaves = 16;
+__global__ void __launch_bounds__(kReduceWaves * kWave)
 reduce_parts_add(const float* __restrict__ partial, int64_t part_stride, int32_t n_parts, int32_t width,
-                 float* __restrict__ out, const int64_t* __restrict__ n_rows_dev, int32_t rows_per_part) {
-    __shared__ float part[4][kWave];
+                 float* __restrict__ out) {
+    __shared__ float part[kReduceWaves][kWave];
     const int lane = threadIdx.x & 63, q = threadIdx.x >> 6;
     const int32_t i = blockIdx.x * kWave + lane;
-    if (n_rows_dev != nullptr) {
-        const int64_t live = (*n_rows_dev + rows_per_part - 1) / rows_per_part;
-        n_parts = live < n_parts ? (int32_t)live : n_parts;
-    }
     float s = 0.f;
-    if (i < width)
-        for (int32_t p = q; p < n_parts; p += 4) s += partial[(int64_t)p * part_stride + i];
+    if (i < width) {
+        const float* src = partial + i;
+        int32_t p = q;
+        for (; p + 3 * kReduceWaves < n_parts; p += 4 * kReduceWaves) {
+            const float v0 = src[(int64_t)p * part_stride], v1 = src[(int64_t)(p + kReduceWaves) * part_stride];
+            const float v2 = src[(int64_t)(p + 2 * kReduceWaves) * part_stride];
+            const float v3 = src[(int64_t)(p + 3 * kReduceWaves) * part_stride];
+            s = (((s + v0) + v1) + v2) + v3;
+        }
+        for (; p < n_parts; p += kReduceWaves) s += src[(int64_t)p * part_stride];
+    }
     part[q][lane] = s;
     __syncthreads();
-    if (q == 0 && i < width) out[i] += (part[0][lane] + part[1][lane]) + (part[2][lane] + part[3][lane]);
+    if (q == 0 && i < width) {
+        float sum = 0.f;
+#pragma unroll
+        for (int w = 0; w < kReduceWaves; ++w) sum += part[w][lane];
+        out[i] += sum;
+    }
+}
+
+// ---- by source rows: what a source row receives is collected by the row itself.
+//
+// Adding every entry's alpha_i dY[r] to dz[u_i] in memory moves n_entries x d_out float atomics, which
+// run at 0.4 TB/s here (170 k rows x 6.5 entries x 256 columns: 2.27 ms).  Instead the entries are listed
+// by source row (counted, placed, filled: integer atomics, one per entry), a first pass over the
+// destination rows leaves per row and head what the softmax's backward needs (score of the row, maximum,
+// 1 / denominator, S = sum alpha_i dalpha_i, sum of de_i) and the masked gradient, and one wavefront per
+// source row walks its list: alpha and dalpha of an entry come again from those and the row's own z,
+// which stays in registers.  dz is written once, finished; no float atomics.
+// Lane layout of both passes: a head's d_head / 4 words on a power-of-two segment of `seg` lanes (NW words
+// a lane when it has more than 64), 64 / seg heads side by side, blockIdx.y the group of heads.
+// Needs d_head % 4 == 0 and at most 512, and a 16-byte aligned dOut.  Lists are sized for kGatListCap entries
+// per destination row on average; a longer input (only the device knows) is left to the kernels below.
+constexpr int kGatListCap = 32;
+
+struct GatGate {                 // run only if the entries exceed (over = 1) / do not exceed (0) what the lists hold
+    const int32_t* nnz;          // DEVICE; NULL: always run
+    int64_t cap;
+    int32_t over;
+};
+__device__ __forceinline__ bool gate_closed(const GatGate& g) {
+    return g.nnz != nullptr && ((int64_t)*g.nnz > g.cap) != (g.over != 0);
+}
+
+template <int NW>
+struct GatLane {
+    int32_t h, w0;
+    int32_t col[NW];
+    bool ok[NW];
+    __device__ __forceinline__ GatLane(int lane, int32_t seg, int32_t dh, int32_t n_heads) {
+        w0 = lane & (seg - 1);
+        const int32_t hh = (int32_t)blockIdx.y * (kWave / seg) + lane / seg;
+        h = hh < n_heads ? hh : 0;
+#pragma unroll
+        for (int i = 0; i < NW; ++i) {
+            const int32_t w = w0 + i * seg;
+            ok[i] = hh < n_heads && 4 * w < dh;
+            col[i] = ok[i] ? h * dh + 4 * w : 0;
+        }
+    }
+};
+__device__ __forceinline__ float seg_sum(float v, int32_t seg) {
+    for (int o = seg >> 1; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
+    return v;
+}
+__device__ __forceinline__ float dot4(const float4& a, const float4& b) { return a.x * b.x + a.y * b.y + a.z * b.z + a.w * b.w; }
+
+// Entry e of a row's list, e = beg - 1 standing for the row itself (negative: no term).
+__device__ __forceinline__ int32_t gat_entry(int32_t e, int32_t beg, int32_t end, int32_t s, const int32_t* idx) {
+    return e < beg ? s : e < end ? idx[e] : -1;
+}
+
+__global__ void __launch_bounds__(kBwdThreads)
+gat_list_zero(int32_t* __restrict__ cnt, int32_t* __restrict__ cursor, int64_t n_src, const int64_t* __restrict__ n_rows_dev) {
+    const int64_t i = (int64_t)blockIdx.x * kBwdThreads + threadIdx.x;
+    if (i == 0) *cursor = 0;
+    if (i < n_src && (n_rows_dev == nullptr || i < *n_rows_dev)) cnt[i] = 0;
+}
+
+// FILL = false: cnt[u] = entries naming u.  true: list[pos[u]++] = destination row (its complement for the
+// row's own term).  Eight lanes per destination row.
+template <bool FILL>
+__global__ void __launch_bounds__(kBwdThreads)
+gat_list_entries(const int32_t* __restrict__ self_idx, const int32_t* __restrict__ indptr, const int32_t* __restrict__ idx,
+                 int64_t n_dst, int32_t* __restrict__ at, int32_t* __restrict__ list, GatGate gate) {
+    if (gate_closed(gate)) return;
+    const int64_t gid = (int64_t)blockIdx.x * kBwdThreads + threadIdx.x;
+    const int64_t r = gid >> 3;
+    if (r >= n_dst) return;
+    const int32_t s = self_idx != nullptr ? self_idx[r] : (int32_t)r;
+    const int32_t beg = indptr[r], end = indptr[r + 1];
+    for (int32_t e = beg - 1 + (int32_t)(gid & 7); e < end; e += 8) {
+        const int32_t u = gat_entry(e, beg, end, s, idx);
+        if (u < 0) continue;
+        const int32_t p = atomicAdd(&at[u], 1);
+        if (FILL) list[p] = e < beg ? ~(int32_t)r : (int32_t)r;
+    }
+}
+
+// Every source row's piece of the list, in no particular order of the rows: one atomic per workgroup.
+__global__ void __launch_bounds__(kBwdThreads)
+gat_list_place(const int32_t* __restrict__ cnt, int32_t* __restrict__ pos, int32_t* __restrict__ cursor, int64_t n_src,
+               const int64_t* __restrict__ n_rows_dev, GatGate gate) {
+    if (gate_closed(gate)) return;
+    __shared__ int32_t wave_total[kBwdThreads / kWave], base;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t u = (int64_t)blockIdx.x * kBwdThreads + threadIdx.x;
+    const bool live = u < n_src && (n_rows_dev == nullptr || u < *n_rows_dev);
+    const int32_t c = live ? cnt[u] : 0;
+    int32_t incl = c;
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+        const int32_t v = __shfl_up(incl, o, kWave);
+        if (lane >= o) incl += v;
+    }
+    if (lane == kWave - 1) wave_total[wave] = incl;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        int32_t total = 0;
+        for (int w = 0; w < kBwdThreads / kWave; ++w) total += wave_total[w];
+        base = atomicAdd(cursor, total);
+    }
+    __syncthreads();
+    int32_t before = base;
+    for (int w = 0; w < wave; ++w) before += wave_total[w];
+    if (live) pos[u] = before + incl - c;
+}
+
+// One wavefront per destination row and group of heads.  The scores are read twice (maximum, then everything
+// else), the z rows once: den, sum p d and, over the entries on LeakyReLU's flat side, sum p and sum p d give
+// S = sum alpha_i d_i and, because sum alpha_i (d_i - S) = 0,
+//   sum_i de_i = sum alpha_i (d_i - S) slope_i = -0.8 sum_{flat} alpha_i (d_i - S).
+template <typename Tr, int NW>
+__global__ void __launch_bounds__(kBwdThreads)
+gat_bwd_stats(const float* __restrict__ Z, const float* __restrict__ scores, const int32_t* __restrict__ self_idx,
+              const int32_t* __restrict__ indptr, const int32_t* __restrict__ idx,
+              const typename Tr::store_t* __restrict__ out_fwd, int relu, const float* __restrict__ dOut, int64_t n_dst,
+              int32_t d_out, int32_t n_heads, int32_t seg, float4* __restrict__ stat, float* __restrict__ sum_de,
+              float* __restrict__ masked, GatGate gate) {
+    if (gate_closed(gate)) return;
+    const int lane = threadIdx.x & 63;
+    const int64_t r = (int64_t)blockIdx.x * (kBwdThreads / kWave) + (threadIdx.x >> 6);
+    if (r >= n_dst) return;                       // the whole wavefront
+    const int32_t stride = 2 * n_heads;
+    const GatLane<NW> L(lane, seg, d_out / n_heads, n_heads);
+    float4 g[NW];
+#pragma unroll
+    for (int i = 0; i < NW; ++i) {
+        g[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (!L.ok[i]) continue;
+        g[i] = *reinterpret_cast<const float4*>(dOut + r * d_out + L.col[i]);
+        if (relu) {
+            const typename Tr::store_t* o = out_fwd + r * d_out + L.col[i];
+            g[i].x = Tr::to_f(o[0]) > 0.f ? g[i].x : 0.f;
+            g[i].y = Tr::to_f(o[1]) > 0.f ? g[i].y : 0.f;
+            g[i].z = Tr::to_f(o[2]) > 0.f ? g[i].z : 0.f;
+            g[i].w = Tr::to_f(o[3]) > 0.f ? g[i].w : 0.f;
+            *reinterpret_cast<float4*>(masked + r * d_out + L.col[i]) = g[i];
+        }
+    }
+    const int32_t s = self_idx != nullptr ? self_idx[r] : (int32_t)r;
+    const int32_t beg = indptr[r], end = indptr[r + 1];
+    const float sd = s >= 0 ? scores[(int64_t)s * stride + n_heads + L.h] : 0.f;
+    constexpr int U = 4;      // entries in flight
+    float mx = -INFINITY;
+    for (int32_t e = beg - 1; e < end; e += U) {
+        int32_t u[U];
+        float sc[U];
+#pragma unroll
+        for (int k = 0; k < U; ++k) u[k] = gat_entry(e + k, beg, end, s, idx);
+#pragma unroll
+        for (int k = 0; k < U; ++k) sc[k] = u[k] >= 0 ? scores[(int64_t)u[k] * stride + L.h] : 0.f;
+#pragma unroll
+        for (int k = 0; k < U; ++k)
+            if (u[k] >= 0) mx = fmaxf(mx, leaky02(sd + sc[k]));
+    }
+    float den = 0.f, pd = 0.f, pn = 0.f, pdn = 0.f;
+    for (int32_t e = beg - 1; e < end; e += U) {
+        int32_t u[U];
+        float sc[U];
+        float4 z[U][NW];
+#pragma unroll
+        for (int k = 0; k < U; ++k) u[k] = gat_entry(e + k, beg, end, s, idx);
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            const int64_t row = u[k] >= 0 ? u[k] : 0;
+            sc[k] = scores[row * stride + L.h];
+#pragma unroll
+            for (int i = 0; i < NW; ++i) z[k][i] = *reinterpret_cast<const float4*>(Z + row * d_out + L.col[i]);
+        }
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            if (u[k] < 0) continue;               // uniform over the wavefront
+            float d = 0.f;
+#pragma unroll
+            for (int i = 0; i < NW; ++i) d += L.ok[i] ? dot4(g[i], z[k][i]) : 0.f;
+            d = seg_sum(d, seg);
+            const float ev = sd + sc[k], p = expf(leaky02(ev) - mx);
+            den += p;
+            pd += p * d;
+            if (!(ev > 0.f)) {
+                pn += p;
+                pdn += p * d;
+            }
+        }
+    }
+    if (L.w0 == 0 && L.ok[0]) {      // (without entries nothing refers to the row)
+        const float inv = 1.f / den, S = pd * inv;
+        stat[r * n_heads + L.h] = make_float4(sd, mx, inv, S);
+        sum_de[r * n_heads + L.h] = -0.8f * (pdn - S * pn) * inv;
+    }
+}
+
+// One wavefront per source row (rows dealt out over the grid) and group of heads: dz[u] finished, and the
+// workgroup's part of ga_src / ga_dst, partial[b][0][n] and partial[b][1][n].
+template <typename Tr, int NW>
+__global__ void __launch_bounds__(kBwdThreads)
+gat_bwd_pull(const float* __restrict__ Z, const float* __restrict__ scores, const float* __restrict__ dY,
+             const float4* __restrict__ stat, const float* __restrict__ sum_de, const int32_t* __restrict__ cnt,
+             const int32_t* __restrict__ pos, const int32_t* __restrict__ list, const typename Tr::store_t* __restrict__ a_src,
+             const typename Tr::store_t* __restrict__ a_dst, int64_t n_src, const int64_t* __restrict__ n_rows_dev,
+             int32_t d_out, int32_t n_heads, int32_t seg, float* __restrict__ dZ, float* __restrict__ partial, GatGate gate) {
+    if (gate_closed(gate)) return;
+    constexpr int WAVES = kBwdThreads / kWave;
+    __shared__ float4 red[WAVES][2][NW][kWave];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if (n_rows_dev != nullptr && *n_rows_dev < n_src) n_src = *n_rows_dev;
+    const int32_t stride = 2 * n_heads;
+    const GatLane<NW> L(lane, seg, d_out / n_heads, n_heads);
+    float4 as[NW], ad[NW], gas[NW], gad[NW];
+#pragma unroll
+    for (int i = 0; i < NW; ++i) {
+        as[i] = ad[i] = gas[i] = gad[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (!L.ok[i]) continue;
+        const typename Tr::store_t* ps = a_src + L.col[i];
+        const typename Tr::store_t* pd = a_dst + L.col[i];
+        as[i] = make_float4(Tr::to_f(ps[0]), Tr::to_f(ps[1]), Tr::to_f(ps[2]), Tr::to_f(ps[3]));
+        ad[i] = make_float4(Tr::to_f(pd[0]), Tr::to_f(pd[1]), Tr::to_f(pd[2]), Tr::to_f(pd[3]));
+    }
+    auto fma4 = [](float a, const float4& x, float4& y) {
+        y.x += a * x.x;
+        y.y += a * x.y;
+        y.z += a * x.z;
+        y.w += a * x.w;
+    };
+    for (int64_t u = (int64_t)blockIdx.x * WAVES + wave; u < n_src; u += (int64_t)gridDim.x * WAVES) {
+        float4 z[NW], acc[NW];
+#pragma unroll
+        for (int i = 0; i < NW; ++i) {
+            z[i] = *reinterpret_cast<const float4*>(Z + u * d_out + L.col[i]);
+            if (!L.ok[i]) z[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+            acc[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+        const float ssrc = scores[u * stride + L.h];
+        float dss = 0.f, dsd = 0.f;
+        const int32_t end = pos[u], beg = end - cnt[u];
+        constexpr int U = 4;      // entries in flight
+        for (int32_t e = beg; e < end; e += U) {
+            int32_t x[U];
+            float4 st[U], g[U][NW];
+#pragma unroll
+            for (int k = 0; k < U; ++k) x[k] = list[e + k < end ? e + k : e];
+#pragma unroll
+            for (int k = 0; k < U; ++k) {
+                const int64_t r = x[k] < 0 ? ~x[k] : x[k];
+                st[k] = stat[r * n_heads + L.h];
+#pragma unroll
+                for (int i = 0; i < NW; ++i) g[k][i] = *reinterpret_cast<const float4*>(dY + r * d_out + L.col[i]);
+            }
+#pragma unroll
+            for (int k = 0; k < U; ++k) {
+                if (e + k >= end) break;          // uniform over the wavefront
+                float d = 0.f;
+#pragma unroll
+                for (int i = 0; i < NW; ++i) d += L.ok[i] ? dot4(g[k][i], z[i]) : 0.f;
+                d = seg_sum(d, seg);
+                const float ev = st[k].x + ssrc, al = expf(leaky02(ev) - st[k].y) * st[k].z;
+                dss += al * (d - st[k].w) * (ev > 0.f ? 1.f : 0.2f);
+#pragma unroll
+                for (int i = 0; i < NW; ++i) fma4(al, g[k][i], acc[i]);
+                if (x[k] < 0) dsd += sum_de[(int64_t)~x[k] * n_heads + L.h];
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < NW; ++i) {
+            fma4(dss, z[i], gas[i]);
+            fma4(dsd, z[i], gad[i]);
+            acc[i].x += dss * as[i].x + dsd * ad[i].x;
+            acc[i].y += dss * as[i].y + dsd * ad[i].y;
+            acc[i].z += dss * as[i].z + dsd * ad[i].z;
+            acc[i].w += dss * as[i].w + dsd * ad[i].w;
+            if (L.ok[i]) *reinterpret_cast<float4*>(dZ + u * d_out + L.col[i]) = acc[i];
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < NW; ++i) {
+        red[wave][0][i][lane] = gas[i];
+        red[wave][1][i][lane] = gad[i];
+    }
+    __syncthreads();
+    if (wave < 2) {          // wave 0 sums ga_src, wave 1 ga_dst
+#pragma unroll
+        for (int i = 0; i < NW; ++i) {
+            float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+            for (int w = 0; w < WAVES; ++w) fma4(1.f, red[w][wave][i][lane], v);
+            if (L.ok[i]) *reinterpret_cast<float4*>(partial + ((int64_t)blockIdx.x * 2 + wave) * d_out + L.col[i]) = v;
+        }
+    }
+}
+
+// ---- by destination rows, with float atomics: small inputs, head widths the lane layout above does not take,
+// and inputs with more entries than the lists hold.
+
+__global__ void __launch_bounds__(kBwdThreads)
+gat_zero(float* __restrict__ dZ, float* __restrict__ ds, int64_t n_src, const int64_t* __restrict__ n_rows_dev, int32_t d_out,
+         int32_t n_scores, GatGate gate) {
+    if (gate_closed(gate)) return;
+    if (n_rows_dev != nullptr && *n_rows_dev < n_src) n_src = *n_rows_dev;
+    const int64_t step = (int64_t)gridDim.x * kBwdThreads, t0 = (int64_t)blockIdx.x * kBwdThreads + threadIdx.x;
+    if (d_out % 4 == 0)
+        for (int64_t i = t0; i < n_src * (d_out / 4); i += step) reinterpret_cast<float4*>(dZ)[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+    else
+        for (int64_t i = t0; i < n_src * d_out; i += step) dZ[i] = 0.f;
+    for (int64_t i = t0; i < n_src * n_scores; i += step) ds[i] = 0.f;
 }
 
 // One wavefront per destination row; heads are taken kHeadBatch at a time, side by side: per entry
@@ -1446,11 +1771,12 @@ __global__ void __launch_bounds__(kBwdThreads)
 gat_bwd_rows(const float* __restrict__ Z, const float* __restrict__ scores, const int32_t* __restrict__ self_idx,
              const int32_t* __restrict__ indptr, const int32_t* __restrict__ idx,
              const typename Tr::store_t* __restrict__ out_fwd, int relu, const float* __restrict__ dOut,
-             int64_t n_dst, int32_t d_out, int32_t n_heads, float* __restrict__ dZ, float* __restrict__ ds) {
+             int64_t n_dst, int32_t d_out, int32_t n_heads, float* __restrict__ dZ, float* __restrict__ ds, GatGate gate) {
+    if (gate_closed(gate)) return;
     const int lane = threadIdx.x & 63;
-    const int64_t r = (int64_t)blockIdx.x * (kBwdThreads / kWave) + (threadIdx.x >> 6);
-    if (r >= n_dst) return;                       // the whole wavefront
     const int32_t dh = d_out / n_heads, stride = 2 * n_heads;
+    for (int64_t r = (int64_t)blockIdx.x * (kBwdThreads / kWave) + (threadIdx.x >> 6); r < n_dst;
+         r += (int64_t)gridDim.x * (kBwdThreads / kWave)) {      // the whole wavefront
     const int64_t s = self_idx != nullptr ? (int64_t)self_idx[r] : r;
     const int32_t beg = indptr[r], end = indptr[r + 1];
     const float* gy_row = dOut + r * d_out;
@@ -1567,26 +1893,24 @@ gat_bwd_rows(const float* __restrict__ Z, const float* __restrict__ scores, cons
                 if (lane == b && b < nh) atomicAdd(&ds[s * stride + n_heads + h0 + b], sum_de[b]);
         }
     }
+    }
 }
 
-constexpr int kSrcRows = 256;    // source rows per workgroup of gat_bwd_src
-
 // dz[u] += ds_src[u,h] a_src[h] + ds_dst[u,h] a_dst[h] in place (one thread owns a column of the
-// block's rows), and the block's part of ga_src / ga_dst: partial[b][0][n], partial[b][1][n].
+// workgroup's rows, dealt out over the grid), and the workgroup's part of ga_src / ga_dst as in gat_bwd_pull.
 template <typename Tr>
 __global__ void __launch_bounds__(kBwdThreads)
 gat_bwd_src(const float* __restrict__ Z, const float* __restrict__ ds, const typename Tr::store_t* __restrict__ a_src,
-            const typename Tr::store_t* __restrict__ a_dst, int64_t n_src_cap, const int64_t* __restrict__ n_rows_dev,
-            int32_t d_out, int32_t n_heads, float* __restrict__ dZ, float* __restrict__ partial) {
+            const typename Tr::store_t* __restrict__ a_dst, int64_t n_src, const int64_t* __restrict__ n_rows_dev,
+            int32_t d_out, int32_t n_heads, float* __restrict__ dZ, float* __restrict__ partial, GatGate gate) {
+    if (gate_closed(gate)) return;
     const int32_t dh = d_out / n_heads, stride = 2 * n_heads;
-    const int64_t n_src = n_rows_dev != nullptr && *n_rows_dev < n_src_cap ? *n_rows_dev : n_src_cap;
-    const int64_t u0 = (int64_t)blockIdx.x * kSrcRows;       // a block past the last row writes zero parts
-    const int64_t u1 = u0 + kSrcRows < n_src ? u0 + kSrcRows : n_src;
+    if (n_rows_dev != nullptr && *n_rows_dev < n_src) n_src = *n_rows_dev;
     for (int32_t n = threadIdx.x; n < d_out; n += kBwdThreads) {
         const int32_t h = n / dh;
         const float as = Tr::to_f(a_src[n]), ad = Tr::to_f(a_dst[n]);
         float acc_s = 0.f, acc_d = 0.f;
-        for (int64_t u = u0; u < u1; ++u) {
+        for (int64_t u = blockIdx.x; u < n_src; u += gridDim.x) {
             const float dss = ds[u * stride + h], dsd = ds[u * stride + n_heads + h];
             const float z = Z[u * d_out + n];
             acc_s += dss * z;
@@ -1598,20 +1922,42 @@ gat_bwd_src(const float* __restrict__ Z, const float* __restrict__ ds, const typ
     }
 }
 
+// Workgroups (= parts of ga_src / ga_dst) of the source-row kernels: at least 16 rows each, and no more than
+// fill the chip eight times over, so that the parts stay few.
+static inline int64_t gat_src_parts(int64_t n_src) {
+    const int64_t want = ceil_div(n_src, 16);
+    return want < 2048 ? want : 2048;
+}
+
 struct GatBwdWs {
-    size_t dz_bytes, ds_bytes, col_bytes, zero_bytes;
+    size_t dz_bytes, ds_bytes, col_bytes;
+    size_t cnt_bytes, list_bytes, stat_bytes, sum_bytes, masked_bytes;      // the source-row path; 0 where it is not taken
     BwdWs G;          // the weight gradient's partial tiles (rows = source rows)
     size_t total;
 };
+// Whether the source rows collect their gradient themselves: the lane layout fits, positions fit 32 bits, and
+// there are enough rows (the lists and the gated launches cost about eight launches).
+static inline bool gat_by_source(int64_t n_dst, int32_t d_out, int32_t n_heads) {
+    const int32_t dh = d_out / n_heads;
+    return n_dst >= 512 && dh % 4 == 0 && dh <= 512 && n_dst * (1 + kGatListCap) < ((int64_t)1 << 31);
+}
 static GatBwdWs gat_bwd_ws_layout(int64_t n_src, int64_t n_dst, int32_t d_in, int32_t d_out, int32_t n_heads) {
     GatBwdWs L{};
     const int64_t ns = n_src > 0 ? n_src : 1, nd = n_dst > 0 ? n_dst : 1;
     L.dz_bytes = align_up((size_t)ns * d_out * 4, 256);
     L.ds_bytes = align_up((size_t)ns * 2 * n_heads * 4, 256);
-    const int64_t parts = ceil_div(nd, kColRows) > 2 * ceil_div(ns, kSrcRows) ? ceil_div(nd, kColRows) : 2 * ceil_div(ns, kSrcRows);
+    const int64_t parts = ceil_div(nd, kColRows) > 2 * gat_src_parts(ns) ? ceil_div(nd, kColRows) : 2 * gat_src_parts(ns);
+    if (gat_by_source(nd, d_out, n_heads)) {
+        L.cnt_bytes = align_up((size_t)ns * 4, 256);        // counts, positions (and the cursor in a word of its own)
+        L.list_bytes = align_up((size_t)nd * (1 + kGatListCap) * 4, 256);
+        L.stat_bytes = align_up((size_t)nd * n_heads * 16, 256);
+        L.sum_bytes = align_up((size_t)nd * n_heads * 4, 256);
+        L.masked_bytes = align_up((size_t)nd * d_out * 4, 256);
+    }
     L.col_bytes = align_up((size_t)parts * d_out * 4, 256);
     L.G = bwd_ws_layout(ns, d_in, d_out, 0);      // (row splits as for fp32 operands: any count is valid)
     L.total = L.dz_bytes + L.ds_bytes + L.col_bytes + L.G.partial_bytes + L.G.bias_bytes;
+    if (L.cnt_bytes > 0) L.total += 2 * L.cnt_bytes + 256 + L.list_bytes + L.stat_bytes + L.sum_bytes + L.masked_bytes;
     return L;
 }
 
@@ -1639,36 +1985,69 @@ static hopgnn_status gat_bwd_typed(const void* Hsrc, int64_t n_src, const int64_
         hipLaunchKernelGGL(col_sum_rows<Tr>, dim3((unsigned)parts), dim3(kBwdThreads), 0, s, dOut,
                            static_cast<const T*>(out_fwd), relu, n_dst, d_out, col);
         HOPGNN_LAUNCH_CHECK();
-        hipLaunchKernelGGL(reduce_parts_add, dim3((unsigned)ceil_div(d_out, kWave)), dim3(kBwdThreads), 0, s, col,
-                           (int64_t)d_out, parts, d_out, gbias, nullptr, 0);
+        hipLaunchKernelGGL(reduce_parts_add, dim3((unsigned)ceil_div(d_out, kWave)), dim3(kReduceWaves * kWave), 0, s, col,
+                           (int64_t)d_out, parts, d_out, gbias);
         HOPGNN_LAUNCH_CHECK();
     }
     if (n_src == 0) return HOPGNN_OK;              // no entries anywhere: only the bias has a gradient
 
-    // dz and ds start at zero (fill kernels, never a memset node): the source rows that exist
-    if (d_out % 4 == 0)
-        hipLaunchKernelGGL(bwd_zero, dim3((unsigned)ceil_div(n_src * (d_out / 4), kBwdThreads)), dim3(kBwdThreads), 0, s,
-                           reinterpret_cast<float4*>(dZ), n_src * (d_out / 4), n_src_dev, d_out / 4);
-    else
-        hipLaunchKernelGGL(bwd_zero_elem, dim3((unsigned)ceil_div(n_src * d_out, kBwdThreads)), dim3(kBwdThreads), 0, s, dZ,
-                           n_src * d_out, n_src_dev, d_out);
+    const int32_t src_blocks = (int32_t)gat_src_parts(n_src);
+    GatGate gate{nullptr, 0, 0};
+    if (L.cnt_bytes > 0 && aligned(dOut, 16)) {
+        gate = GatGate{indptr + n_dst, (int64_t)kGatListCap * n_dst, 0};
+        char* q = reinterpret_cast<char*>(bias_partial) + L.G.bias_bytes;
+        int32_t* cursor = reinterpret_cast<int32_t*>(q);
+        int32_t* cnt = reinterpret_cast<int32_t*>(q += 256);
+        int32_t* pos = reinterpret_cast<int32_t*>(q += L.cnt_bytes);
+        int32_t* list = reinterpret_cast<int32_t*>(q += L.cnt_bytes);
+        float4* stat = reinterpret_cast<float4*>(q += L.list_bytes);
+        float* sum_de = reinterpret_cast<float*>(q += L.stat_bytes);
+        float* masked = reinterpret_cast<float*>(q += L.sum_bytes);
+        const int32_t words = d_out / n_heads / 4;
+        int32_t seg = 1;
+        while (seg < words && seg < kWave) seg *= 2;
+        const unsigned groups = (unsigned)ceil_div(n_heads, kWave / seg);
+        const dim3 by_row((unsigned)ceil_div(n_dst * 8, kBwdThreads));
+        hipLaunchKernelGGL(gat_list_zero, dim3((unsigned)ceil_div(n_src, kBwdThreads)), dim3(kBwdThreads), 0, s, cnt, cursor,
+                           n_src, n_src_dev);
+        HOPGNN_LAUNCH_CHECK();
+        hipLaunchKernelGGL(gat_list_entries<false>, by_row, dim3(kBwdThreads), 0, s, self_idx, indptr, idx, n_dst, cnt, list, gate);
+        HOPGNN_LAUNCH_CHECK();
+        hipLaunchKernelGGL(gat_list_place, dim3((unsigned)ceil_div(n_src, kBwdThreads)), dim3(kBwdThreads), 0, s, cnt, pos,
+                           cursor, n_src, n_src_dev, gate);
+        HOPGNN_LAUNCH_CHECK();
+        hipLaunchKernelGGL(gat_list_entries<true>, by_row, dim3(kBwdThreads), 0, s, self_idx, indptr, idx, n_dst, pos, list, gate);
+        HOPGNN_LAUNCH_CHECK();
+        auto stats = words > kWave ? gat_bwd_stats<Tr, 2> : gat_bwd_stats<Tr, 1>;
+        hipLaunchKernelGGL(stats, dim3((unsigned)ceil_div(n_dst, kBwdThreads / kWave), groups), dim3(kBwdThreads), 0, s, Z, scores,
+                           self_idx, indptr, idx, static_cast<const T*>(out_fwd), relu, dOut, n_dst, d_out, n_heads, seg, stat,
+                           sum_de, masked, gate);
+        HOPGNN_LAUNCH_CHECK();
+        auto pull = words > kWave ? gat_bwd_pull<Tr, 2> : gat_bwd_pull<Tr, 1>;
+        hipLaunchKernelGGL(pull, dim3((unsigned)src_blocks, groups), dim3(kBwdThreads), 0, s, Z, scores, relu ? masked : dOut, stat,
+                           sum_de, cnt, pos, list, static_cast<const T*>(a_src), static_cast<const T*>(a_dst), n_src, n_src_dev,
+                           d_out, n_heads, seg, dZ, col, gate);
+        HOPGNN_LAUNCH_CHECK();
+        gate.over = 1;           // the kernels below then run only for more entries than the lists hold
+    }
+    // dz and ds start at zero (a fill kernel, never a memset node): the source rows that exist
+    const int64_t row_blocks = ceil_div(n_dst, kBwdThreads / kWave);
+    const unsigned few = 1024;   // workgroups of a launch that as a rule finds its gate closed
+    const int64_t zero_blocks = ceil_div(n_src * ceil_div(d_out, 4), kBwdThreads);
+    auto grid_of = [&](int64_t blocks) { return dim3(gate.nnz != nullptr && blocks > few ? few : (unsigned)blocks); };
+    hipLaunchKernelGGL(gat_zero, grid_of(zero_blocks), dim3(kBwdThreads), 0, s, dZ, ds, n_src, n_src_dev, d_out, 2 * n_heads, gate);
     HOPGNN_LAUNCH_CHECK();
-    hipLaunchKernelGGL(bwd_zero_elem, dim3((unsigned)ceil_div(n_src * 2 * n_heads, kBwdThreads)), dim3(kBwdThreads), 0, s, ds,
-                       n_src * 2 * n_heads, n_src_dev, 2 * n_heads);
+    hipLaunchKernelGGL(gat_bwd_rows<Tr>, grid_of(row_blocks), dim3(kBwdThreads), 0, s, Z, scores, self_idx, indptr, idx,
+                       static_cast<const T*>(out_fwd), relu, dOut, n_dst, d_out, n_heads, dZ, ds, gate);
     HOPGNN_LAUNCH_CHECK();
-    hipLaunchKernelGGL(gat_bwd_rows<Tr>, dim3((unsigned)ceil_div(n_dst, kBwdThreads / kWave)), dim3(kBwdThreads), 0, s, Z,
-                       scores, self_idx, indptr, idx, static_cast<const T*>(out_fwd), relu, dOut, n_dst, d_out, n_heads, dZ,
-                       ds);
-    HOPGNN_LAUNCH_CHECK();
-    const int32_t src_blocks = (int32_t)ceil_div(n_src, kSrcRows);
     hipLaunchKernelGGL(gat_bwd_src<Tr>, dim3((unsigned)src_blocks), dim3(kBwdThreads), 0, s, Z, ds,
-                       static_cast<const T*>(a_src), static_cast<const T*>(a_dst), n_src, n_src_dev, d_out, n_heads, dZ, col);
+                       static_cast<const T*>(a_src), static_cast<const T*>(a_dst), n_src, n_src_dev, d_out, n_heads, dZ, col, gate);
     HOPGNN_LAUNCH_CHECK();
-    hipLaunchKernelGGL(reduce_parts_add, dim3((unsigned)ceil_div(d_out, kWave)), dim3(kBwdThreads), 0, s, col,
-                       (int64_t)2 * d_out, src_blocks, d_out, ga_src, n_src_dev, kSrcRows);
+    hipLaunchKernelGGL(reduce_parts_add, dim3((unsigned)ceil_div(d_out, kWave)), dim3(kReduceWaves * kWave), 0, s, col,
+                       (int64_t)2 * d_out, src_blocks, d_out, ga_src);
     HOPGNN_LAUNCH_CHECK();
-    hipLaunchKernelGGL(reduce_parts_add, dim3((unsigned)ceil_div(d_out, kWave)), dim3(kBwdThreads), 0, s, col + d_out,
-                       (int64_t)2 * d_out, src_blocks, d_out, ga_dst, n_src_dev, kSrcRows);
+    hipLaunchKernelGGL(reduce_parts_add, dim3((unsigned)ceil_div(d_out, kWave)), dim3(kReduceWaves * kWave), 0, s, col + d_out,
+                       (int64_t)2 * d_out, src_blocks, d_out, ga_dst);
     HOPGNN_LAUNCH_CHECK();
 
     // gW += Hsrc^T dz: one matrix (k_self = 0), the "aggregate" operand is Hsrc itself, rows = source rows
