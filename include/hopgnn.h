@@ -513,7 +513,9 @@ hopgnn_status hopgnn_gcn_bwd(const void *Hsrc, hopgnn_dtype dt, int64_t n_src, i
  *          hopgnn_gat_fwd_ws_bytes(...) bytes); 256-byte aligned.
  * n_src_dev DEVICE, or NULL = n_src: the number of source rows that exist when only the device
  *          knows it (layer 1 reads the pre-gathered rows; n_src is then their capacity), as in
- *          hopgnn_gat_fwd; rows past it are neither read nor written.
+ *          hopgnn_gat_fwd; dHsrc is not written past it.  self_idx and idx are to name rows below
+ *          it: an entry between it and n_src reads whatever z and scores fwd_ws holds there and
+ *          gives its own row no gradient.
  * out_fwd  the stored forward output (ReLU mask; may be NULL when relu == 0); dOut fp32.
  * gW [d_in x d_out], ga_src [d_out], ga_dst [d_out], gbias [d_out] (or NULL): DEVICE fp32
  *          accumulators, ADDED to.  dHsrc DEVICE out [n_src x d_in] fp32, overwritten, or NULL.

@@ -1511,12 +1511,15 @@ gat_list_zero(int32_t* __restrict__ cnt, int32_t* __restrict__ cursor, int64_t n
 }
 
 // FILL = false: cnt[u] = entries naming u.  true: list[pos[u]++] = destination row (its complement for the
-// row's own term).  Eight lanes per destination row.
+// row's own term).  Eight lanes per destination row.  An entry that names a row past the source rows that
+// exist is listed nowhere: such a row has no piece of the list (and no gradient that anything reads).
 template <bool FILL>
 __global__ void __launch_bounds__(kBwdThreads)
 gat_list_entries(const int32_t* __restrict__ self_idx, const int32_t* __restrict__ indptr, const int32_t* __restrict__ idx,
-                 int64_t n_dst, int32_t* __restrict__ at, int32_t* __restrict__ list, GatGate gate) {
+                 int64_t n_dst, int64_t n_src, const int64_t* __restrict__ n_rows_dev, int32_t* __restrict__ at,
+                 int32_t* __restrict__ list, GatGate gate) {
     if (gate_closed(gate)) return;
+    if (n_rows_dev != nullptr && *n_rows_dev < n_src) n_src = *n_rows_dev;
     const int64_t gid = (int64_t)blockIdx.x * kBwdThreads + threadIdx.x;
     const int64_t r = gid >> 3;
     if (r >= n_dst) return;
@@ -1524,7 +1527,7 @@ gat_list_entries(const int32_t* __restrict__ self_idx, const int32_t* __restrict
     const int32_t beg = indptr[r], end = indptr[r + 1];
     for (int32_t e = beg - 1 + (int32_t)(gid & 7); e < end; e += 8) {
         const int32_t u = gat_entry(e, beg, end, s, idx);
-        if (u < 0) continue;
+        if (u < 0 || u >= n_src) continue;
         const int32_t p = atomicAdd(&at[u], 1);
         if (FILL) list[p] = e < beg ? ~(int32_t)r : (int32_t)r;
     }
@@ -2011,12 +2014,14 @@ static hopgnn_status gat_bwd_typed(const void* Hsrc, int64_t n_src, const int64_
         hipLaunchKernelGGL(gat_list_zero, dim3((unsigned)ceil_div(n_src, kBwdThreads)), dim3(kBwdThreads), 0, s, cnt, cursor,
                            n_src, n_src_dev);
         HOPGNN_LAUNCH_CHECK();
-        hipLaunchKernelGGL(gat_list_entries<false>, by_row, dim3(kBwdThreads), 0, s, self_idx, indptr, idx, n_dst, cnt, list, gate);
+        hipLaunchKernelGGL(gat_list_entries<false>, by_row, dim3(kBwdThreads), 0, s, self_idx, indptr, idx, n_dst,
+                           n_src, n_src_dev, cnt, list, gate);
         HOPGNN_LAUNCH_CHECK();
         hipLaunchKernelGGL(gat_list_place, dim3((unsigned)ceil_div(n_src, kBwdThreads)), dim3(kBwdThreads), 0, s, cnt, pos,
                            cursor, n_src, n_src_dev, gate);
         HOPGNN_LAUNCH_CHECK();
-        hipLaunchKernelGGL(gat_list_entries<true>, by_row, dim3(kBwdThreads), 0, s, self_idx, indptr, idx, n_dst, pos, list, gate);
+        hipLaunchKernelGGL(gat_list_entries<true>, by_row, dim3(kBwdThreads), 0, s, self_idx, indptr, idx, n_dst,
+                           n_src, n_src_dev, pos, list, gate);
         HOPGNN_LAUNCH_CHECK();
         auto stats = words > kWave ? gat_bwd_stats<Tr, 2> : gat_bwd_stats<Tr, 1>;
         hipLaunchKernelGGL(stats, dim3((unsigned)ceil_div(n_dst, kBwdThreads / kWave), groups), dim3(kBwdThreads), 0, s, Z, scores,

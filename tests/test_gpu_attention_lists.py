@@ -47,3 +47,35 @@ def test_the_lists_are_rebuilt_on_every_call(hb):  # noqa: F811
         first = first or [x.clone() for x in got]
         for x, y in zip(got, first):       # fp32 sums in another order (the bound of the general test)
             assert float((x - y).abs().max() / y.pow(2).mean().sqrt()) <= 1e-4
+
+
+@pytest.mark.parametrize("heads,d_out", [(4, 64), (3, 30)])      # by source rows; the kernels with float atomics
+def test_entries_past_the_device_count_stay_inside_the_lists(hb, heads, d_out):  # noqa: F811
+    """Entries (and the rows' own terms, without self_idx) that name rows between the device's count and the
+    capacity, with z and scores of zero there: the result is that of the whole capacity with zero rows, and
+    nothing past the count or outside the workspace is written."""
+    import numpy as np
+    rng = np.random.default_rng(7)
+    n_src, n_dst, live, d_in = 1200, 900, 600, 24
+    H, W, _, dOut, indptr, idx, _ = general._inputs(rng, torch.float32, (n_src, n_dst, d_in, d_out, 8))
+    assert int((idx >= live).sum()) > 1000
+    H[live:] = 0
+    t, dev = general._t, general.DEV
+    a_s, a_d = torch.randn(d_out, device=dev), torch.randn(d_out, device=dev)
+    ws_bytes = hb.hopgnn_gat_bwd_ws_bytes(torch.float32, n_src, n_dst, d_in, d_out, heads)
+    res = []
+    for count in (None, torch.tensor([live], dtype=torch.int64, device=dev)):
+        fwd_ws = torch.zeros(hb.hopgnn_gat_fwd_ws_bytes(torch.float32, n_src, d_in, d_out, heads), dtype=torch.uint8, device=dev)
+        out = torch.empty((n_dst, d_out), device=dev)
+        hb.hopgnn_gat_fwd(H, n_src, None, t(indptr), t(idx), n_dst, W, a_s, a_d, None, heads, True, out, fwd_ws, count)
+        room = torch.full((ws_bytes + (1 << 20),), 0x5A, dtype=torch.uint8, device=dev)      # positions of 0x5A5A5A5A if left alone
+        g = [torch.zeros((d_in, d_out), device=dev), torch.zeros(d_out, device=dev), torch.zeros(d_out, device=dev)]
+        dH = torch.full((n_src, d_in), 7.0, device=dev)
+        hb.hopgnn_gat_bwd(H, n_src, None, t(indptr), t(idx), n_dst, W, a_s, a_d, out, fwd_ws, True, t(dOut), heads,
+                          g[0], g[1], g[2], None, dH, room[:ws_bytes], n_src_dev=count)
+        torch.cuda.synchronize()
+        assert bool((room[ws_bytes:] == 0x5A).all())
+        res.append([out] + g + [dH])
+    assert bool((res[1][4][live:] == 7.0).all())
+    for x, y in zip(res[1][:4] + [res[1][4][:live]], res[0][:4] + [res[0][4][:live]]):     # the bound of the test above
+        assert float((x - y).abs().max() / y.pow(2).mean().sqrt()) <= 1e-4
