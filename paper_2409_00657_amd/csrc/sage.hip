@@ -591,8 +591,6 @@ sage_project_f32(const float* __restrict__ Hsrc, const int32_t* __restrict__ sel
 // block, six v_mfma_f32_32x32x16_bf16 of the split operands 192.  Both operands are split on their way
 // to LDS (three pieces each, k contiguous, row stride conflict free for 128-bit reads), the weights in
 // this kernel too, so nothing derived from them outlives the call.
-// A block whose sums are not all finite (an infinity, or a sum past the largest float: the pieces of an
-// infinity are not numbers) is done again with the fp32 instruction straight from memory.
 template <int BM, int BN, int BK, bool VEC, bool TREE>
 __global__ void __launch_bounds__(kProjThreads, 2)
 sage_project_split(const float* __restrict__ Hsrc, const int32_t* __restrict__ self_idx,
@@ -767,34 +765,19 @@ sage_project_split(const float* __restrict__ Hsrc, const int32_t* __restrict__ s
     }
     if (t < n_tiles) iter(t, 0);
 
-    if (!wave_finite<TM, TN>(acc)) {      // v_mfma_f32_32x32x2_f32: lane l feeds A[row l%32][k = l/32], B[k = l/32][col l%32]
-        zero_acc<TM, TN>(acc);
-        int64_t so[TM], mo[TM];
-#pragma unroll
-        for (int tm = 0; tm < TM; ++tm) {
+    redo_nonfinite<TM, TN, TREE>(
+        acc, 0, K, lane,
+        [&](int tm, int64_t k) -> float {
             const int64_t row = row0 + wm * (BM / 2) + tm * 32 + fl32;
-            const int64_t s = row >= row_end ? -1 : self_idx != nullptr ? (int64_t)self_idx[row] : row;
-            so[tm] = s >= 0 ? s * d_in : -1;
-            mo[tm] = row < row_end ? row * d_in : -1;
-        }
-        for (int k = fg; k - fg < K; k += 2) {
-            float a[TM], b[TN];
-#pragma unroll
-            for (int tm = 0; tm < TM; ++tm)
-                a[tm] = k < d_in ? (so[tm] >= 0 ? Hsrc[so[tm] + k] : 0.f) : (k < K && mo[tm] >= 0 ? Mean[mo[tm] + k - d_in] : 0.f);
-#pragma unroll
-            for (int tn = 0; tn < TN; ++tn) {
-                const int32_t n = col0 + wn * (BN / 2) + tn * 32 + fl32;
-                b[tn] = k < K && n < d_out ? (k < d_in ? Wself + (int64_t)k * d_out : Wneigh + (int64_t)(k - d_in) * d_out)[n] : 0.f;
-            }
-#pragma unroll
-            for (int tm = 0; tm < TM; ++tm)
-#pragma unroll
-                for (int tn = 0; tn < TN; ++tn)
-                    acc[tm][tn] = TREE ? __builtin_amdgcn_mfma_f32_32x32x2f32(b[tn], a[tm], acc[tm][tn], 0, 0, 0)
-                                       : __builtin_amdgcn_mfma_f32_32x32x2f32(a[tm], b[tn], acc[tm][tn], 0, 0, 0);
-        }
-    }
+            if (row >= row_end || k >= K) return 0.f;
+            if (k >= d_in) return Mean[row * d_in + k - d_in];
+            const int64_t s = self_idx != nullptr ? (int64_t)self_idx[row] : row;
+            return s >= 0 ? Hsrc[s * d_in + k] : 0.f;
+        },
+        [&](int tn, int64_t k) -> float {
+            const int32_t n = col0 + wn * (BN / 2) + tn * 32 + fl32;
+            return k < K && n < d_out ? (k < d_in ? Wself + k * d_out : Wneigh + (k - d_in) * d_out)[n] : 0.f;
+        });
     if (TREE)
         tree_epilogue<TrF32, BM, BN, BN, TM, TN, kProjThreads, true>(acc, lds16, wm * (BM / 2), wn * (BN / 2), tid, lane, row0,
                                                                row_end, col0, d_out, lds_bias, relu, out, tt, lvl,

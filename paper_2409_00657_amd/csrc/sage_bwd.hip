@@ -99,8 +99,7 @@ bwd_zero(float4* __restrict__ p, int64_t n4, const int64_t* __restrict__ n_rows_
 // to LDS, which keeps the loop free of branches.  The tile goes to partial[split]; workgroups
 // of the first k-tile row also produce the column sums of dZ.
 // Bound by the matrix cores on v_mfma_f32_32x32x2_f32 (512 cycles per 32 x 32 x 16 block); the six
-// products of the split operands take 192.  A wave whose sums are not all finite forms them again with
-// the fp32 instruction straight from memory (the pieces of an infinity are not numbers).
+// products of the split operands take 192.
 // The host sizes the row splits for the capacity; when only the device knows how many rows exist,
 // the rows that do are dealt out evenly over the same number of splits (multiples of 32 rows, never
 // more than the host's figure), so that no split idles while another works through the whole input.
@@ -302,26 +301,19 @@ bwd_weight_grad(const typename Tr::store_t* __restrict__ Hsrc, const int32_t* __
         for (int j = 0; j < 2; ++j)
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[i][j][e] = __uint_as_float(__float_as_uint(acc[i][j][e]) ^ flip);
-    if (!wave_finite<2, 2>(acc)) {     // v_mfma_f32_32x32x2_f32: lane l feeds A[r + l/32][k0 + l%32], dZ[r + l/32][n0 + l%32]
-        zero_acc<2, 2>(acc);
-        for (int64_t r = r0 + g; r - g < r1; r += 2) {
-            float a[2], b[2];
-            const bool row_ok = r < r1;
-            const int64_t srow = !row_ok ? -1 : self_idx != nullptr ? (int64_t)self_idx[r] : r;
-#pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                const int k = k0 + i * 32 + l32, n = n0 + i * 32 + l32;
-                a[i] = !row_ok || k >= K ? 0.f
-                       : k < k_self      ? (srow >= 0 ? Tr::to_f(Hsrc[srow * d_in + k]) : 0.f)
-                                         : Tr::to_f(Mean[r * d_in + k - k_self]);
-                b[i] = row_ok && n < d_out && (!MASK || Tr::to_f(OutFwd[r * d_out + n]) > 0.f) ? dZ[r * d_out + n] : 0.f;
-            }
-#pragma unroll
-            for (int i = 0; i < 2; ++i)
-#pragma unroll
-                for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[j], acc[i][j], 0, 0, 0);
-        }
-    }
+    redo_nonfinite<2, 2, false>(
+        acc, r0, r1, lane,
+        [&](int i, int64_t r) -> float {
+            const int k = k0 + i * 32 + l32;
+            if (r >= r1 || k >= K) return 0.f;
+            if (k >= k_self) return Tr::to_f(Mean[r * d_in + k - k_self]);
+            const int64_t srow = self_idx != nullptr ? (int64_t)self_idx[r] : r;
+            return srow >= 0 ? Tr::to_f(Hsrc[srow * d_in + k]) : 0.f;
+        },
+        [&](int j, int64_t r) -> float {
+            const int n = n0 + j * 32 + l32;
+            return r < r1 && n < d_out && (!MASK || Tr::to_f(OutFwd[r * d_out + n]) > 0.f) ? dZ[r * d_out + n] : 0.f;
+        });
 
     // partial[split][k][n]; accumulator register e of lane l holds G row 8*(e/4)+4*(l/32)+e%4, col l%32
     float* P = partial + (int64_t)blockIdx.y * K * d_out;
@@ -728,26 +720,17 @@ bwd_input_grad(const float* __restrict__ dZ, const typename Tr::store_t* __restr
 
     const int64_t wrow = row0 + wm * (BM / 2);
     const int wcol = col0 + wn * (BN / 2);
-    if (!wave_finite<TM, TN>(acc)) {     // v_mfma_f32_32x32x2_f32: lane l feeds dZ[row l%32][k = l/32], W[row l%32][k = l/32]
-        zero_acc<TM, TN>(acc);
-        for (int k = g; k - g < d_out; k += 2) {
-            float a[TM], b[TN];
-#pragma unroll
-            for (int tm = 0; tm < TM; ++tm) {
-                const int64_t row = wrow + tm * 32 + l32;
-                a[tm] = row < n_dst && k < d_out ? dZ[row * d_out + k] : 0.f;
-            }
-#pragma unroll
-            for (int tn = 0; tn < TN; ++tn) {
-                const int j = wcol + tn * 32 + l32;
-                b[tn] = j < N && k < d_out ? Tr::to_f((j < k_self ? Wself + (int64_t)j * d_out : Wneigh + (int64_t)(j - k_self) * d_out)[k]) : 0.f;
-            }
-#pragma unroll
-            for (int tm = 0; tm < TM; ++tm)
-#pragma unroll
-                for (int tn = 0; tn < TN; ++tn) acc[tm][tn] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[tm], b[tn], acc[tm][tn], 0, 0, 0);
-        }
-    }
+    redo_nonfinite<TM, TN, false>(
+        acc, 0, d_out, lane,
+        [&](int tm, int64_t k) -> float {
+            const int64_t row = wrow + tm * 32 + l32;
+            return row < n_dst && k < d_out ? dZ[row * d_out + k] : 0.f;
+        },
+        [&](int tn, int64_t k) -> float {
+            const int j = wcol + tn * 32 + l32;
+            if (j >= N || k >= d_out) return 0.f;
+            return Tr::to_f((j < k_self ? Wself + (int64_t)j * d_out : Wneigh + (int64_t)(j - k_self) * d_out)[k]);
+        });
 #pragma unroll
     for (int tn = 0; tn < TN; ++tn) {
         const int col = wcol + tn * 32 + l32;

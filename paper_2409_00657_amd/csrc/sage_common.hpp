@@ -144,20 +144,6 @@ __device__ __forceinline__ void mma_split(floatx16 (&acc)[TM][TN], const uint16_
     }
 }
 
-// Whether every sum of a wave is finite.  Where one is not, the caller zeroes them and forms them again with
-// the fp32 instruction.
-template <int TM, int TN>
-__device__ __forceinline__ bool wave_finite(const floatx16 (&acc)[TM][TN]) {
-    float f = 0.f;
-#pragma unroll
-    for (int tm = 0; tm < TM; ++tm)
-#pragma unroll
-        for (int tn = 0; tn < TN; ++tn)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) f = fmaf(acc[tm][tn][i], 0.f, f);
-    return !__any(!(f == 0.f));
-}
-
 template <int TM, int TN>
 __device__ __forceinline__ void zero_acc(floatx16 (&acc)[TM][TN]) {
 #pragma unroll
@@ -166,6 +152,33 @@ __device__ __forceinline__ void zero_acc(floatx16 (&acc)[TM][TN]) {
         for (int tn = 0; tn < TN; ++tn)
 #pragma unroll
             for (int i = 0; i < 16; ++i) acc[tm][tn][i] = 0.f;
+}
+
+// What the split cannot form - products with an infinity or a NaN - has come out as an infinity or a NaN.  Exactly those elements of a wave's block are formed again with
+// v_mfma_f32_32x32x2_f32 (lane l feeds A[row l%32][k = l/32] and B[k = l/32][col l%32]) straight from memory;
+// every other element keeps its bits, whatever its neighbours in the block hold.
+// a_of(tm, k), b_of(tn, k): this lane's operands, zero outside the matrices.
+template <int TM, int TN, bool SWAP, typename FA, typename FB>
+__device__ __forceinline__ void redo_nonfinite(floatx16 (&acc)[TM][TN], int64_t k_begin, int64_t k_end, int lane, FA a_of, FB b_of) {
+#pragma unroll
+    for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+        for (int tn = 0; tn < TN; ++tn) {
+            float f = 0.f;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) f = fmaf(acc[tm][tn][i], 0.f, f);
+            if (!__any(!(f == 0.f))) continue;
+            floatx16 r;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) r[i] = 0.f;
+            for (int64_t k0 = k_begin; k0 < k_end; k0 += 2) {
+                const int64_t k = k0 + (lane >> 5);
+                const float a = a_of(tm, k), b = b_of(tn, k);
+                r = SWAP ? __builtin_amdgcn_mfma_f32_32x32x2f32(b, a, r, 0, 0, 0) : __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, r, 0, 0, 0);
+            }
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[tm][tn][i] = acc[tm][tn][i] * 0.f == 0.f ? acc[tm][tn][i] : r[i];
+        }
 }
 
 // ------------------------------------------------------------ segmented mean --

@@ -102,3 +102,54 @@ def test_infinities_and_the_largest_floats(hb, shape):
             assert torch.equal(kind(a), kind(r32))
         ok = torch.isfinite(r32)
         assert float(((a[ok].double() - r[ok]).abs().max() / r[ok].pow(2).mean().sqrt()).item()) <= BOUND(max(n, 2 * d_out))
+
+
+def _two_layers(fuse, big):
+    """Forward pass of two layers over 33 000 first-layer rows of 256 columns (520 large tiles), the outputs of
+    every stored row; `big`: an infinity, a NaN and the largest float among the features."""
+    from paper_2409_00657_amd import synth
+    from paper_2409_00657_amd.pipeline import HotPath
+    g = synth.rmat_graph(13, 9.0, seed=11, device=DEV)
+    X = synth.features(g.n_vertices, 100, torch.float32, device=DEV)
+    W = synth.sage_weights(100, 256, 2, torch.float32, device=DEV, bias=True)
+    seeds = synth.seeds(g.n_vertices, 3000, 300, device=DEV)
+    if big:
+        v = seeds[:4].long().unique()[:3]
+        X[v[0], 5], X[v[1], 7], X[v[2], 0] = float("inf"), float("nan"), torch.finfo(torch.float32).max
+    hp = HotPath(g.offsets, g.indices, X, W, 3000, [10, 3], fuse_tree=fuse)
+    out = torch.empty((3000, 256), device=DEV)
+    hp.forward(seeds, [17], out)
+    torch.cuda.synchronize()
+    return out, hp.H[0][:3000].clone()
+
+
+def _same_bits(a, b):
+    return torch.equal(torch.isnan(a), torch.isnan(b)) and torch.equal(torch.nan_to_num(a, nan=0.0), torch.nan_to_num(b, nan=0.0))
+
+
+def test_fused_and_plain_tiles_give_the_same_bits_beside_infinities():
+    """The two cut the rows into tiles at different places."""
+    fused, plain = _two_layers(True, True), _two_layers(False, True)
+    assert not bool(torch.isfinite(plain[1]).all()) and bool(torch.isfinite(plain[0]).all(1).any())
+    for a, b in zip(fused, plain):
+        assert _same_bits(a, b)
+    clean = _two_layers(True, False)
+    top = plain[1].abs().amax(1)            # a row reached by one of the three holds infinities, huge values or, where the
+    rows = torch.isfinite(plain[1]).all(1) & (top < 1e30) & (top > 0)      # ReLU has met its NaNs, nothing but zeros
+    assert int(rows.sum()) > 2500 and torch.equal(fused[1][rows], clean[1][rows])
+
+
+@pytest.mark.parametrize("shape", [(129, 100, 256), (33000, 36, 132)])
+def test_an_infinity_leaves_the_other_rows_and_columns_their_bits(hb, shape):
+    n, d_in, d_out = shape
+    H, Ws, Wn, G, indptr, idx = _inputs(*shape, seed=3)
+    idx = torch.arange(n, device=DEV, dtype=torch.int32)
+    H2, G2 = H.clone(), G.clone()
+    H2[5, 2], G2[9, 3] = float("inf"), float("-inf")
+    a, b = _forward(H, Ws, Wn, idx), _forward(H2, Ws, Wn, idx)
+    keep = torch.arange(n, device=DEV) != 5
+    assert torch.equal(a[keep], b[keep]) and not bool(torch.isfinite(b[5]).any())
+    g1, g2 = _backward(hb, H, Ws, Wn, G, indptr, idx), _backward(hb, H, Ws, Wn, G2, indptr, idx)
+    cols, rows = torch.arange(d_out, device=DEV) != 3, torch.arange(n, device=DEV) != 9
+    assert torch.equal(g1[0][:, cols], g2[0][:, cols]) and torch.equal(g1[1][:, cols], g2[1][:, cols])
+    assert torch.equal(g1[3][rows], g2[3][rows]) and not bool(torch.isfinite(g2[3][9]).any())
