@@ -765,6 +765,7 @@ sage_project_split(const float* __restrict__ Hsrc, const int32_t* __restrict__ s
     }
     if (t < n_tiles) iter(t, 0);
 
+    unscale_split<TM, TN>(acc);
     redo_nonfinite<TM, TN, TREE>(
         acc, 0, K, lane,
         [&](int tm, int64_t k) -> float {

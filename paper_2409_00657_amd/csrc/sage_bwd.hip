@@ -295,12 +295,7 @@ bwd_weight_grad(const typename Tr::store_t* __restrict__ Hsrc, const int32_t* __
     }
 
     const int k0 = (int)tk * kGradTile + wk * 64, n0 = (int)tn * kGradTile + wn * 64;
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) acc[i][j][e] = __uint_as_float(__float_as_uint(acc[i][j][e]) ^ flip);
+    unscale_split<2, 2>(acc, flip != 0 ? -kSplitUnscale : kSplitUnscale);
     redo_nonfinite<2, 2, false>(
         acc, r0, r1, lane,
         [&](int i, int64_t r) -> float {
@@ -720,6 +715,7 @@ bwd_input_grad(const float* __restrict__ dZ, const typename Tr::store_t* __restr
 
     const int64_t wrow = row0 + wm * (BM / 2);
     const int wcol = col0 + wn * (BN / 2);
+    unscale_split<TM, TN>(acc);
     redo_nonfinite<TM, TN, false>(
         acc, 0, d_out, lane,
         [&](int tm, int64_t k) -> float {

@@ -89,12 +89,18 @@ __device__ __forceinline__ floatx16 mfma16<TrF16>(const uint4& a, const uint4& b
                                                   *reinterpret_cast<const halfx8*>(&b), c, 0, 0, 0);
 }
 
-// fp32 on the bf16 matrix instruction.  A float is the sum of three bf16 values: its leading 8
-// significant bits cut off, the next 8 rounded to nearest, and what is left (exact in 8 bits).  Of the
+// fp32 on the bf16 matrix instruction.  A float times 2^24 is the sum of three bf16 values: its leading 8
+// significant bits cut off, the next 8 rounded to nearest, and what is left (exact in 8 bits).  The scaling
+// (exact) puts the last bit of every float, subnormals included, inside bf16's range; unscaled, a float below
+// 2^-110 would lose it.  Operands past 2^103 and sums past 2^79 leave the range on the large side: see
+// redo_nonfinite.  Of the
 // nine products of two such sums the six down to 2^-16 of the leading one are formed; each is exact in
 // the fp32 accumulator, and the three left out are below 2^-22 and of either sign (the cut is followed
 // by a rounding), under the rounding that the sums themselves carry.
+constexpr float kSplitScale = 0x1p24f, kSplitUnscale = 0x1p-48f;
 __device__ __forceinline__ void split2_bf16(float x, float y, uint32_t& hi, uint32_t& mid, uint32_t& lo) {
+    x *= kSplitScale;
+    y *= kSplitScale;
     const uint32_t ux = __float_as_uint(x), uy = __float_as_uint(y);
     hi = __builtin_amdgcn_perm(uy, ux, 0x07060302u);
     const float rx = x - __uint_as_float(ux & 0xFFFF0000u), ry = y - __uint_as_float(uy & 0xFFFF0000u);
@@ -154,7 +160,19 @@ __device__ __forceinline__ void zero_acc(floatx16 (&acc)[TM][TN]) {
             for (int i = 0; i < 16; ++i) acc[tm][tn][i] = 0.f;
 }
 
-// What the split cannot form - products with an infinity or a NaN - has come out as an infinity or a NaN.  Exactly those elements of a wave's block are formed again with
+// The sums of products of two scaled operands, unscaled.
+template <int TM, int TN>
+__device__ __forceinline__ void unscale_split(floatx16 (&acc)[TM][TN], float by = kSplitUnscale) {
+#pragma unroll
+    for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+        for (int tn = 0; tn < TN; ++tn)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[tm][tn][i] *= by;
+}
+
+// What the split cannot form - products with an infinity or a NaN, operands past 2^103, sums past 2^79 - has
+// come out as an infinity or a NaN.  Exactly those elements of a wave's block are formed again with
 // v_mfma_f32_32x32x2_f32 (lane l feeds A[row l%32][k = l/32] and B[k = l/32][col l%32]) straight from memory;
 // every other element keeps its bits, whatever its neighbours in the block hold.
 // a_of(tm, k), b_of(tn, k): this lane's operands, zero outside the matrices.

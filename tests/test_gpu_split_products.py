@@ -153,3 +153,57 @@ def test_an_infinity_leaves_the_other_rows_and_columns_their_bits(hb, shape):
     cols, rows = torch.arange(d_out, device=DEV) != 3, torch.arange(n, device=DEV) != 9
     assert torch.equal(g1[0][:, cols], g2[0][:, cols]) and torch.equal(g1[1][:, cols], g2[1][:, cols])
     assert torch.equal(g1[3][rows], g2[3][rows]) and not bool(torch.isfinite(g2[3][9]).any())
+
+
+def _slots_backward(hb, H, Ws, Wn, G):
+    """n destination rows with one child row each: the input gradients of a row and of its child, no atomics."""
+    n, (d_in, d_out) = G.shape[0], Ws.shape
+    gWs, gWn, gb = torch.zeros_like(Ws), torch.zeros_like(Wn), torch.zeros(d_out, device=DEV)
+    dH = torch.empty((2 * n, d_in), device=DEV)
+    indptr = torch.arange(n + 1, device=DEV, dtype=torch.int32)
+    idx = torch.arange(n, 2 * n, device=DEV, dtype=torch.int32)
+    ws = torch.empty(hb.hopgnn_sage_bwd_ws_bytes(torch.float32, n, d_in, d_out, True), dtype=torch.uint8, device=DEV)
+    hb.hopgnn_sage_bwd_slots(H, 2 * n, indptr, idx, n, n, Ws, Wn, None, False, G, gWs, gWn, gb, dH, ws)
+    return gWs, gWn, dH[:n], dH[n:]
+
+
+@pytest.mark.parametrize("shape", [(65, 20, 12), (777, 7, 5), (129, 100, 256), (33000, 36, 132)])
+@pytest.mark.parametrize("scale", [1e-34, 1e-36, 2e-38])
+def test_the_smallest_magnitudes(hb, shape, scale):
+    """Down to and among the subnormal floats: the bound of ordinary magnitudes, for each operand in turn."""
+    n, d_in, d_out = shape
+    H, Ws, Wn, G, _, idx = _inputs(*shape, seed=4)
+    small = H * scale
+    assert _err(_forward(small, Ws, Wn, idx), _ref(small, Ws, Wn, G, idx)[0]) <= BOUND(2 * d_in)
+    Wss, Wns = Ws * scale, Wn * scale
+    assert _err(_forward(H, Wss, Wns, idx), _ref(H, Wss, Wns, G, idx)[0]) <= BOUND(2 * d_in)
+    H = torch.cat([H, H[idx.long()]])
+    for h, g in ((H, G * scale), (H * scale, G)):
+        gWs, gWn, dSelf, dNeigh = _slots_backward(hb, h, Ws, Wn, g)
+        hd, gd = h.double(), g.double()
+        for got, ref, K in ((gWs, hd[:n].t().contiguous() @ gd, n), (gWn, hd[n:].t().contiguous() @ gd, n),
+                            (dSelf, gd @ Ws.double().t().contiguous(), d_out), (dNeigh, gd @ Wn.double().t().contiguous(), d_out)):
+            assert _err(got, ref) <= BOUND(K)
+
+
+@pytest.mark.parametrize("shape", [(65, 20, 12), (33000, 36, 132)])
+def test_operands_beyond_the_scaled_range(hb, shape):
+    """Finite values past 2^103, and sums past 2^79 of smaller ones, come out as the fp32 instruction forms them."""
+    n, d_in, d_out = shape
+    H, Ws, Wn, G, indptr, idx = _inputs(*shape, seed=6)
+    H[3] *= 1e33
+    H[5] *= 1e25
+    G[7] *= 1e33
+    G[9] *= 1e25
+    out_ref, ref = _ref(H, Ws, Wn, G, idx)
+    out = _forward(H, Ws, Wn, idx)
+    assert bool(torch.isfinite(out).all())
+    row_err = (out.double() - out_ref).abs().amax(1) / out_ref.pow(2).mean(1).sqrt()
+    mixed = torch.isin(torch.arange(n, device=DEV), torch.tensor([3, 5], device=DEV)) | torch.isin(idx, torch.tensor([3, 5], device=DEV, dtype=torch.int32))
+    assert float(row_err[~mixed].max()) <= BOUND(2 * d_in) and float(row_err.max()) <= BOUND(2 * d_in)
+    G2 = torch.cat([H, H[idx.long()]]).clamp(-9, 9)
+    gWs, gWn, dSelf, dNeigh = _slots_backward(hb, G2, Ws, Wn, G)
+    for got, r in ((dSelf, G.double() @ Ws.double().t().contiguous()), (dNeigh, G.double() @ Wn.double().t().contiguous())):
+        assert float(((got.double() - r).abs().amax(1) / r.pow(2).mean(1).sqrt()).max()) <= BOUND(d_out)
+    for got, h in ((gWs, G2[:n]), (gWn, G2[n:])):
+        assert _err(got, h.double().t().contiguous() @ G.double()) <= BOUND(n)
