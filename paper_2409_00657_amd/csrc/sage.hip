@@ -587,8 +587,8 @@ sage_project_f32(const float* __restrict__ Hsrc, const int32_t* __restrict__ sel
                                         lds_bias + wn * (BN / 2), relu, out);
 }
 
-// The large tile of the fp32 forward pass.  Bound by the matrix cores: v_mfma_f32_32x32x2_f32 needs 512 cycles per 32 x 32 x 16
-// block, six v_mfma_f32_32x32x16_bf16 of the split operands 192.  Both operands are split on their way
+// The large tile of the fp32 forward pass.  v_mfma_f32_32x32x2_f32 needs 512 cycles per 32 x 32 x 16 block,
+// eight v_mfma_f32_32x32x16_bf16 of the split operands 256.  Both operands are split on their way
 // to LDS (three pieces each, k contiguous, row stride conflict free for 128-bit reads), the weights in
 // this kernel too, so nothing derived from them outlives the call.
 template <int BM, int BN, int BK, bool VEC, bool TREE>
@@ -649,8 +649,9 @@ sage_project_split(const float* __restrict__ Hsrc, const int32_t* __restrict__ s
         }
     }
 
-    floatx16 acc[TM][TN];
+    floatx16 acc[TM][TN], low[TM][TN];
     zero_acc<TM, TN>(acc);
+    zero_acc<TM, TN>(low);
 
     struct Regs {
         float a[A_ITEMS][8], b[B_ITEMS][8];
@@ -739,7 +740,7 @@ sage_project_split(const float* __restrict__ Hsrc, const int32_t* __restrict__ s
     auto compute = [&](int st) {      // slot-tree layers: operands exchanged, a lane then holds runs of one row
         const uint16_t* sa = lds16 + st * STAGE + (wm * (BM / 2) + fl32) * LD + fg * 8;
         const uint16_t* sb = lds16 + st * STAGE + 3 * A_PIECE + (wn * (BN / 2) + fl32) * LD + fg * 8;
-        mma_split<TM, TN, BK, LD, A_PIECE, B_PIECE, TREE>(acc, sa, sb);
+        mma_split<TM, TN, BK, LD, A_PIECE, B_PIECE, TREE>(acc, low, sa, sb);
     };
 
     // Two register sets and two LDS stages.  Iteration t: the loads of tile t+2 are issued first (into
@@ -765,7 +766,7 @@ sage_project_split(const float* __restrict__ Hsrc, const int32_t* __restrict__ s
     }
     if (t < n_tiles) iter(t, 0);
 
-    unscale_split<TM, TN>(acc);
+    join_split<TM, TN>(acc, low);
     redo_nonfinite<TM, TN, TREE>(
         acc, 0, K, lane,
         [&](int tm, int64_t k) -> float {

@@ -98,8 +98,9 @@ bwd_zero(float4* __restrict__ p, int64_t n4, const int64_t* __restrict__ n_rows_
 // Every load is unconditional from a clamped, in-bounds address and masked when it is written
 // to LDS, which keeps the loop free of branches.  The tile goes to partial[split]; workgroups
 // of the first k-tile row also produce the column sums of dZ.
-// Bound by the matrix cores on v_mfma_f32_32x32x2_f32 (512 cycles per 32 x 32 x 16 block); the six
-// products of the split operands take 192.
+// v_mfma_f32_32x32x2_f32 needs 512 cycles of the matrix cores per 32 x 32 x 16 block, the eight products of the
+// split operands 256.  At 170 k rows x 2 x 100 -> 256 those are 56 of the kernel's 176 us: what it waits for is
+// the splitting and the adds (vector instructions) and the LDS, two workgroups to a CU, each step behind a barrier.
 // The host sizes the row splits for the capacity; when only the device knows how many rows exist,
 // the rows that do are dealt out evenly over the same number of splits (multiples of 32 rows, never
 // more than the host's figure), so that no split idles while another works through the whole input.
@@ -143,7 +144,7 @@ __device__ __forceinline__ uint4 tr_column8(const uint16_t* S, int ld, int row0,
 // applied on the way into LDS (a layer whose input gradient is not needed has no other reader of
 // the masked gradient, so the separate masking pass and its array are saved).
 template <typename Tr, bool VEC, bool MASK>
-__global__ void __launch_bounds__(kBwdThreads)
+__global__ void __launch_bounds__(kBwdThreads, 2)
 bwd_weight_grad(const typename Tr::store_t* __restrict__ Hsrc, const int32_t* __restrict__ self_idx,
                 const typename Tr::store_t* __restrict__ Mean, const float* __restrict__ dZ,
                 const typename Tr::store_t* __restrict__ OutFwd, int64_t n_dst, int32_t d_in,
@@ -203,12 +204,6 @@ bwd_weight_grad(const typename Tr::store_t* __restrict__ Hsrc, const int32_t* __
             }
         }
     };
-    // The bf16 instruction's own additions do not round to nearest, which adds up over thousands of rows.  So
-    // a chunk's products are summed from zero and added to the tile by ordinary additions, and every other row
-    // split sums the negated terms, so that the splits' shares of what is left cancel.  Error of 170 k rows x
-    // 100 x 256 (normal / all positive terms): 6.7e-7 / 6.9e-8 with the fp32 instruction; 9.5e-7 / 2.6e-7
-    // with neither measure, 5.7e-7 / 2.1e-7 with the negation alone, 8.8e-7 / 5.2e-8 with the sums alone.
-    const uint32_t flip = (blockIdx.y & 1) != 0 ? 0x80000000u : 0u;
     float colsum[4] = {0.f, 0.f, 0.f, 0.f};      // of this thread's columns, over its rows
     auto put = [&](const float (&v)[4], uint16_t (&S)[3][kGradRows][kGradLd], int row) {
         uint2 h, m, l;
@@ -237,7 +232,7 @@ bwd_weight_grad(const typename Tr::store_t* __restrict__ Hsrc, const int32_t* __
             for (int e = 0; e < 4; ++e) {
                 const int k = ka + e, n = nb + e;
                 const bool a_ok = row_ok && k < K && (k >= k_self || sidx[i] >= 0);
-                av[e] = a_ok ? __uint_as_float(__float_as_uint(av[e]) ^ flip) : 0.f;
+                av[e] = a_ok ? av[e] : 0.f;
                 bv[e] = row_ok && n < d_out && ov[e] > 0.f ? bv[e] : 0.f;
                 colsum[e] += bv[e];
             }
@@ -246,13 +241,9 @@ bwd_weight_grad(const typename Tr::store_t* __restrict__ Hsrc, const int32_t* __
         }
     };
 
-    floatx16 acc[2][2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+    floatx16 acc[2][2], low[2][2];
+    zero_acc<2, 2>(acc);
+    zero_acc<2, 2>(low);
 
     int32_t s_cur[2] = {self_of(0, 0), self_of(0, 1)};
     int32_t s_nxt[2] = {self_of(1, 0), self_of(1, 1)};
@@ -276,26 +267,29 @@ bwd_weight_grad(const typename Tr::store_t* __restrict__ Hsrc, const int32_t* __
                 fa[p][i] = tr_column8(&As[buf][p][0][0], kGradLd, 8 * g, (2 * wk + i) * 32, lane);
                 fb[2 - p][i] = tr_column8(&Bs[buf][2 - p][0][0], kGradLd, 8 * g, (2 * wn + i) * 32, lane);
             }
-        constexpr int pa[6] = {2, 0, 1, 1, 0, 0}, pb[6] = {0, 2, 1, 0, 1, 0};     // smallest products first
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
-            floatx16 sum[1][2];
+            // Thousands of rows: the leading products of a step are summed from zero and added to the tile by
+            // ordinary additions, which round to nearest.  Error of 170 k rows x 100 x 256 (normal / all positive
+            // terms): 6.7e-7 / 6.9e-8 with the fp32 instruction, 2.4e-7 / 5.3e-8 with the tile as the
+            // instruction's own accumulator (9 us a training iteration of that shape less), 2.0e-7 / 5.1e-8 so.
+            floatx16 sum[1][2], lo1[1][2] = {{low[i][0], low[i][1]}};
             zero_acc<1, 2>(sum);
+            const uint4 fi[3][1] = {{fa[0][i]}, {fa[1][i]}, {fa[2][i]}};
+            mma_pieces<1, 2, false>(sum, lo1, fi, fb);
 #pragma unroll
-            for (int p = 0; p < 6; ++p)
-#pragma unroll
-                for (int j = 0; j < 2; ++j) sum[0][j] = mfma16<TrBF16>(fa[pa[p]][i], fb[pb[p]][j], sum[0][j]);
-#pragma unroll
-            for (int j = 0; j < 2; ++j)
+            for (int j = 0; j < 2; ++j) {
+                low[i][j] = lo1[0][j];
 #pragma unroll
                 for (int e = 0; e < 16; ++e) acc[i][j][e] += sum[0][j][e];
+            }
         }
         store(c + 1, s_cur, f, buf ^ 1);
         lds_barrier();
     }
 
     const int k0 = (int)tk * kGradTile + wk * 64, n0 = (int)tn * kGradTile + wn * 64;
-    unscale_split<2, 2>(acc, flip != 0 ? -kSplitUnscale : kSplitUnscale);
+    join_split<2, 2>(acc, low);
     redo_nonfinite<2, 2, false>(
         acc, r0, r1, lane,
         [&](int i, int64_t r) -> float {
@@ -595,7 +589,7 @@ bwd_weight_reduce(const float* __restrict__ partial, const float* __restrict__ b
 //
 // D[r][j] = sum_n dZ[r][n] Wcat[j][n], j over the 2*d_in rows of [W_self ; W_neigh].  Both
 // operands have the contraction index contiguous; both are split into three bf16 pieces on their way to
-// LDS (see split2_bf16: six products of 192 cycles in all against 512 of the fp32 instruction), two K
+// LDS (see split2_bf16: eight products of 256 cycles in all against 512 of the fp32 instruction), two K
 // tiles in LDS and two in registers as in the fp32 projection.  4 waves (2 x 2), each a
 // (BM/2) x (BN/2) piece of D.  VEC: d_out % 4 == 0, whole words of four.
 template <typename Tr, int BM, int BN, int BK, bool VEC>
@@ -690,8 +684,9 @@ bwd_input_grad(const float* __restrict__ dZ, const typename Tr::store_t* __restr
         }
     };
 
-    floatx16 acc[TM][TN];
+    floatx16 acc[TM][TN], low[TM][TN];
     zero_acc<TM, TN>(acc);
+    zero_acc<TM, TN>(low);
     const int n_tiles = (d_out + BK - 1) / BK;
     Regs r[2];
     load(r[0], 0);
@@ -701,7 +696,7 @@ bwd_input_grad(const float* __restrict__ dZ, const typename Tr::store_t* __restr
     auto iter = [&](int t, int i) {     // i = t % 2, a constant after unrolling; tiles past the end are zeros, never multiplied
         load(r[i], t + 2);
         mma_split<TM, TN, BK, LD, A_PIECE, B_PIECE, false>(
-            acc, lds16 + i * STAGE + (wm * (BM / 2) + l32) * LD + g * 8,
+            acc, low, lds16 + i * STAGE + (wm * (BM / 2) + l32) * LD + g * 8,
             lds16 + i * STAGE + 3 * A_PIECE + (wn * (BN / 2) + l32) * LD + g * 8);
         store(r[i ^ 1], t + 1, i ^ 1);
         lds_barrier();
@@ -715,7 +710,7 @@ bwd_input_grad(const float* __restrict__ dZ, const typename Tr::store_t* __restr
 
     const int64_t wrow = row0 + wm * (BM / 2);
     const int wcol = col0 + wn * (BN / 2);
-    unscale_split<TM, TN>(acc);
+    join_split<TM, TN>(acc, low);
     redo_nonfinite<TM, TN, false>(
         acc, 0, d_out, lane,
         [&](int tm, int64_t k) -> float {

@@ -89,21 +89,23 @@ __device__ __forceinline__ floatx16 mfma16<TrF16>(const uint4& a, const uint4& b
                                                   *reinterpret_cast<const halfx8*>(&b), c, 0, 0, 0);
 }
 
-// fp32 on the bf16 matrix instruction.  A float times 2^24 is the sum of three bf16 values: its leading 8
-// significant bits cut off, the next 8 rounded to nearest, and what is left (exact in 8 bits).  The scaling
-// (exact) puts the last bit of every float, subnormals included, inside bf16's range; unscaled, a float below
-// 2^-110 would lose it.  Operands past 2^103 and sums past 2^79 leave the range on the large side: see
-// redo_nonfinite.  Of the
-// nine products of two such sums the six down to 2^-16 of the leading one are formed; each is exact in
-// the fp32 accumulator, and the three left out are below 2^-22 and of either sign (the cut is followed
-// by a rounding), under the rounding that the sums themselves carry.
+// fp32 on the bf16 matrix instruction.  A float times 2^24 is the sum of three bf16 values: rounded to
+// nearest, what that left rounded to nearest, and the rest.  The scaling (exact) puts the last bit of every
+// float, subnormals included, inside bf16's range; unscaled, a float below 2^-110 would lose it.  Of the nine
+// products of two such sums eight are formed, each exact in the fp32 accumulator; the one left out is below
+// 2^-33 of the leading one.  The instruction rounds a sum to nearest but cuts off what its addends have below
+// the largest one's last place, so the leading products have an accumulator of their own and the small ones
+// another, added once at the end: a single product then rounds as in fp32, and sums come out closer than with
+// v_mfma_f32_32x32x2_f32.  Error over the result's rms, 1e-8, fp32 instruction / this / all in one accumulator:
+// one term 2.5 / 2.5 / 3.4, 16 of 224 terms 7.4 / 3.4 / 13.6, 224 normal terms 27 / 8.3 / 22, 1216 62 / 20 / 54,
+// 224 positive terms 23 / 8.9 / 18, 1216 54 / 19 / 36.
+// Operands past 2^103 and sums past 2^79 leave the range on the large side: see redo_nonfinite.
 constexpr float kSplitScale = 0x1p24f, kSplitUnscale = 0x1p-48f;
 __device__ __forceinline__ void split2_bf16(float x, float y, uint32_t& hi, uint32_t& mid, uint32_t& lo) {
     x *= kSplitScale;
     y *= kSplitScale;
-    const uint32_t ux = __float_as_uint(x), uy = __float_as_uint(y);
-    hi = __builtin_amdgcn_perm(uy, ux, 0x07060302u);
-    const float rx = x - __uint_as_float(ux & 0xFFFF0000u), ry = y - __uint_as_float(uy & 0xFFFF0000u);
+    hi = TrBF16::pack2(x, y);
+    const float rx = x - __uint_as_float(hi << 16), ry = y - __uint_as_float(hi & 0xFFFF0000u);
     mid = TrBF16::pack2(rx, ry);
     lo = TrBF16::pack2(rx - __uint_as_float(mid << 16), ry - __uint_as_float(mid & 0xFFFF0000u));
 }
@@ -121,12 +123,28 @@ __device__ __forceinline__ void stage_split8(const float (&x)[8], uint16_t* dst)
     *reinterpret_cast<uint4*>(dst + 2 * PIECE) = l;
 }
 
+// The products of one 16-deep step, operands fa / fb by piece: the leading one to `hi`, the rest to `lo`.
+// SWAP exchanges the operands (a lane then holds runs of one row of the first).
+template <int TM, int TN, bool SWAP>
+__device__ __forceinline__ void mma_pieces(floatx16 (&hi)[TM][TN], floatx16 (&lo)[TM][TN], const uint4 (&fa)[3][TM],
+                                           const uint4 (&fb)[3][TN]) {
+    constexpr int pa[8] = {1, 2, 2, 0, 1, 1, 0, 0}, pb[8] = {2, 1, 0, 2, 1, 0, 1, 0};     // smallest first
+#pragma unroll
+    for (int p = 0; p < 8; ++p)
+#pragma unroll
+        for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+            for (int tn = 0; tn < TN; ++tn) {
+                floatx16& c = p < 7 ? lo[tm][tn] : hi[tm][tn];
+                c = SWAP ? mfma16<TrBF16>(fb[pb[p]][tn], fa[pa[p]][tm], c) : mfma16<TrBF16>(fa[pa[p]][tm], fb[pb[p]][tn], c);
+            }
+}
+
 // One staged K tile (BK deep, both operands in three pieces, k contiguous, rows LD apart) added to a wave's
-// TM x TN block of 32x32 tiles; sa / sb: the lane's first word of its operand's first piece.  SWAP exchanges
-// the operands (a lane then holds runs of one row of the first).
+// TM x TN block of 32x32 tiles; sa / sb: the lane's first word of its operand's first piece.
 template <int TM, int TN, int BK, int LD, int A_PIECE, int B_PIECE, bool SWAP>
-__device__ __forceinline__ void mma_split(floatx16 (&acc)[TM][TN], const uint16_t* sa, const uint16_t* sb) {
-    constexpr int pa[6] = {2, 0, 1, 1, 0, 0}, pb[6] = {0, 2, 1, 0, 1, 0};     // smallest products first
+__device__ __forceinline__ void mma_split(floatx16 (&hi)[TM][TN], floatx16 (&lo)[TM][TN], const uint16_t* sa,
+                                          const uint16_t* sb) {
 #pragma unroll
     for (int kk = 0; kk < BK; kk += 16) {
         uint4 fa[3][TM], fb[3][TN];
@@ -139,14 +157,7 @@ __device__ __forceinline__ void mma_split(floatx16 (&acc)[TM][TN], const uint16_
             for (int tn = 0; tn < TN; ++tn)
                 fb[2 - p][tn] = *reinterpret_cast<const uint4*>(sb + (2 - p) * B_PIECE + tn * 32 * LD + kk);
         }
-#pragma unroll
-        for (int p = 0; p < 6; ++p)
-#pragma unroll
-            for (int tm = 0; tm < TM; ++tm)
-#pragma unroll
-                for (int tn = 0; tn < TN; ++tn)
-                    acc[tm][tn] = SWAP ? mfma16<TrBF16>(fb[pb[p]][tn], fa[pa[p]][tm], acc[tm][tn])
-                                       : mfma16<TrBF16>(fa[pa[p]][tm], fb[pb[p]][tn], acc[tm][tn]);
+        mma_pieces<TM, TN, SWAP>(hi, lo, fa, fb);
     }
 }
 
@@ -160,15 +171,15 @@ __device__ __forceinline__ void zero_acc(floatx16 (&acc)[TM][TN]) {
             for (int i = 0; i < 16; ++i) acc[tm][tn][i] = 0.f;
 }
 
-// The sums of products of two scaled operands, unscaled.
+// hi becomes the sum of the two accumulators, unscaled.
 template <int TM, int TN>
-__device__ __forceinline__ void unscale_split(floatx16 (&acc)[TM][TN], float by = kSplitUnscale) {
+__device__ __forceinline__ void join_split(floatx16 (&hi)[TM][TN], const floatx16 (&lo)[TM][TN]) {
 #pragma unroll
     for (int tm = 0; tm < TM; ++tm)
 #pragma unroll
         for (int tn = 0; tn < TN; ++tn)
 #pragma unroll
-            for (int i = 0; i < 16; ++i) acc[tm][tn][i] *= by;
+            for (int i = 0; i < 16; ++i) hi[tm][tn][i] = (hi[tm][tn][i] + lo[tm][tn][i]) * kSplitUnscale;
 }
 
 // What the split cannot form - products with an infinity or a NaN, operands past 2^103, sums past 2^79 - has

@@ -207,3 +207,39 @@ def test_operands_beyond_the_scaled_range(hb, shape):
         assert float(((got.double() - r).abs().amax(1) / r.pow(2).mean(1).sqrt()).max()) <= BOUND(d_out)
     for got, h in ((gWs, G2[:n]), (gWn, G2[n:])):
         assert _err(got, h.double().t().contiguous() @ G.double()) <= BOUND(n)
+
+
+@pytest.mark.parametrize("shape", [(65, 20, 12), (777, 76, 48), (33000, 36, 132)])
+def test_a_single_product_rounds_once(hb, shape):
+    """Rows with one non-zero element: every result is one product of two floats, so it carries
+    one rounding (and what the split adds to it)."""
+    n, d_in, d_out = shape
+    H, Ws, Wn, G, indptr, idx = _inputs(*shape, seed=8)
+    r = torch.arange(n, device=DEV)
+    one_h = torch.zeros_like(H)
+    one_h[r, r % d_in] = H[r, r % d_in]
+    # one rounding of the product, half a last place; the seven small partial products, together below 2^-7 of it, are
+    # summed with a rounding of 2^-24 of their sum each: 7 x 2^-31, less than 1/16 of 2^-24
+    once = lambda got, ref: bool(((got.double() - ref).abs() <= ref.abs() * 2.0 ** -24 * (1 + 1 / 16)).all())
+    assert once(_forward(one_h, Ws, torch.zeros_like(Wn), idx), one_h.double() @ Ws.double())
+    one_h[d_in:] = 0          # one row per column: one product per weight gradient element
+    one_g = torch.zeros_like(G)
+    one_g[r, r % d_out] = G[r, r % d_out]
+    gWs, _, _, _ = _slots_backward(hb, torch.cat([one_h, one_h]), Ws, Wn, G)
+    assert once(gWs, one_h.double().t().contiguous() @ G.double())
+    _, _, dSelf, dNeigh = _slots_backward(hb, torch.cat([one_h, one_h]), Ws, Wn, one_g)
+    assert once(dSelf, one_g.double() @ Ws.double().t().contiguous()) and once(dNeigh, one_g.double() @ Wn.double().t().contiguous())
+
+
+@pytest.mark.parametrize("shape", [(513, 600, 520), (33000, 600, 136), (20000, 16, 16)])
+def test_sums_of_one_sign(hb, shape):
+    """Terms that cannot cancel: roundings that lean one way would add up over K."""
+    n, d_in, d_out = shape
+    H, Ws, Wn, G, indptr, idx = (t.abs() for t in _inputs(*shape, seed=9))
+    out_ref, ref = _ref(H, Ws, Wn, G, idx)
+    got = _backward(hb, H, Ws, Wn, G, indptr, idx)
+    # relative 2-norm error of a sum whose K roundings lean no way: sqrt(K) 2^-24 of the sum's middle, at most half that
+    rel = lambda a, r: float((a.double() - r).norm() / r.norm())
+    assert rel(_forward(H, Ws, Wn, idx), out_ref) <= 0.5 * (2 * d_in) ** 0.5 * 2.0 ** -24
+    for a, r, K in zip(got, ref, (n, n, n, 2 * d_out)):
+        assert rel(a, r) <= 0.5 * max(K, 16) ** 0.5 * 2.0 ** -24
