@@ -335,7 +335,12 @@ hopgnn_status hopgnn_gather(const void *X, hopgnn_dtype dt, int64_t n_rows, int3
  * out      DEVICE [n_dst x d_out], dtype dt (sums are fp32, rounded once on store;
  *          for 2-byte types the mean is rounded to dt before the projection).
  * ws       DEVICE scratch of at least hopgnn_sage_fwd_ws_bytes(...) bytes, 256-byte aligned.
- * The sum over a segment runs in entry order, so results are run-to-run stable.
+ * The sum over a segment runs in entry order, so results are run-to-run stable, and a row's bits
+ * do not depend on the rows that share its call.
+ * fp32 products run on the bf16 matrix instruction over operands split in three, here and in
+ * hopgnn_sage_fwd_agg and hopgnn_batch_fwd; hopgnn_sage_fwd_dev and the GCN and attention layers
+ * run on the fp32 instruction.  Both are fp32-accurate (a sum's error against 64 bits is a third of
+ * the fp32 instruction's on the first), the last bits differ.
  * Errors: EINVAL, ENOMEM_WS, ERANGE (n_dst or n_src >= 2^31).
  */
 size_t hopgnn_sage_fwd_ws_bytes(hopgnn_dtype dt, int64_t n_dst, int32_t d_in, int32_t d_out);
@@ -350,9 +355,7 @@ hopgnn_status hopgnn_sage_fwd(const void *Hsrc, hopgnn_dtype dt, int64_t n_src, 
  * hopgnn_sage_fwd with another neighbour aggregator (the paper's discussion of generality names
  * sum and max beside the mean):  m_r = mean, sum or element-wise maximum of Hsrc[idx[e]] over the
  * valid entries of row r (0 for an empty segment), out[r] = act(x_r W_self + m_r W_neigh + bias).
- * agg is a hopgnn_agg; HOPGNN_AGG_MEAN is the layer of hopgnn_sage_fwd (whose large fp32 products
- * are formed from split operands, like hopgnn_batch_fwd's: the rounding differs; this call and _dev
- * keep one rounding for all sizes, the forward of a training step).  Same arguments, workspace
+ * agg is a hopgnn_agg; HOPGNN_AGG_MEAN is hopgnn_sage_fwd itself.  Same arguments, workspace
  * (hopgnn_sage_fwd_ws_bytes) and errors; for 2-byte types m_r is rounded to dt before the product.
  */
 hopgnn_status hopgnn_sage_fwd_agg(const void *Hsrc, hopgnn_dtype dt, int64_t n_src, int32_t d_in,
@@ -366,6 +369,9 @@ hopgnn_status hopgnn_sage_fwd_agg(const void *Hsrc, hopgnn_dtype dt, int64_t n_s
  * is sized for and *n_dst_dev (DEVICE, NULL = n_dst) the number of destination rows that exist;
  * rows past it are neither read nor written.  Used with hopgnn_sample_dedup, whose level sizes
  * depend on the data.  The identity-self check (n_src >= n_dst) applies to the capacity.
+ * For fp32 this is also the forward call of a training step (n_dst_dev NULL where the host knows the
+ * count): it stays on the fp32 matrix instruction, whose rounding decides the ReLU masks of rows
+ * near zero, where hopgnn_sage_fwd_agg splits its operands (see hopgnn_sage_fwd).
  */
 hopgnn_status hopgnn_sage_fwd_dev(const void *Hsrc, hopgnn_dtype dt, int64_t n_src, int32_t d_in,
                                   const int32_t *self_idx, const int32_t *indptr, const int32_t *idx,

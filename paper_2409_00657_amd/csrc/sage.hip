@@ -363,14 +363,13 @@ __device__ __forceinline__ void tree_epilogue(floatx16 (&acc)[TM][TN], void* lds
 // k values 4g..4g+3 of an 8-wide K block and the four MFMAs of the block pair A's i-th
 // value with B row 4g+i, which only permutes the order in which k is summed.
 // B is [BK][BN+4], read as 32 consecutive floats per half wave.
-template <int BM, int BN, int BK, int D, bool VEC, bool TREE>
+template <int BM, int BN, int BK, int D, bool VEC>
 __global__ void __launch_bounds__(kProjThreads)
 sage_project_f32(const float* __restrict__ Hsrc, const int32_t* __restrict__ self_idx,
                  const float* __restrict__ Mean, const float* __restrict__ Wself,
                  const float* __restrict__ Wneigh, const float* __restrict__ bias, int64_t n_dst,
                  int32_t d_in, int32_t k_total, int32_t d_out, int relu, uint32_t n_tiles_n,
-                 const float* __restrict__ Zero, float* __restrict__ out, const int64_t* __restrict__ n_rows_dev,
-                 TreeTiles tt) {
+                 const float* __restrict__ Zero, float* __restrict__ out, const int64_t* __restrict__ n_rows_dev) {
     constexpr int LDA = BK + 4, LDB = BN + 4;   // LDA/4 odd: conflict-free 128-bit reads
     static_assert(BK % 8 == 0 && (LDA / 4) % 2 == 1, "K tile");
     static_assert(D >= 2 && D % 2 == 0, "ring depth");
@@ -385,27 +384,16 @@ sage_project_f32(const float* __restrict__ Hsrc, const int32_t* __restrict__ sel
 
     uint32_t mt, nt;
     tile_of_block(blockIdx.x, n_tiles_n, mt, nt);
-    int64_t row0 = (int64_t)mt * BM, row_end;
-    int lvl = 0;
-    uint32_t tile_in_level = 0;
-    if (TREE) {
-        if (!tree_tile_rows<BM>(tt, mt, lvl, tile_in_level, row0, row_end)) return;
-    } else {
-        if (n_rows_dev != nullptr) {      // the row count lives on the device: rows past it do not exist
-            const int64_t live = *n_rows_dev;
-            n_dst = live < n_dst ? live : n_dst;
-        }
-        if (row0 >= n_dst) return;
-        row_end = n_dst;
+    const int64_t row0 = (int64_t)mt * BM;
+    if (n_rows_dev != nullptr) {      // the row count lives on the device: rows past it do not exist
+        const int64_t live = *n_rows_dev;
+        n_dst = live < n_dst ? live : n_dst;
     }
+    if (row0 >= n_dst) return;
     const int32_t col0 = nt * BN;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1;
     const int K = k_total;
-    // the slot id behind this thread's row of the tile (which siblings count in a mean): read here,
-    // used after the K loop
-    int32_t my_id = -1;
-    if (TREE && lvl >= 1 && tt.mean_next != nullptr && row0 + tid < row_end) my_id = tt.ids[row0 + tid];
 
     // rows this thread stages, fixed for the whole K loop
     int64_t a_self[A_ITEMS], a_mean[A_ITEMS];
@@ -415,7 +403,7 @@ sage_project_f32(const float* __restrict__ Hsrc, const int32_t* __restrict__ sel
         const int64_t r = row0 + i / (BK / 4);
         a_self[it] = -1;
         a_mean[it] = -1;
-        if (r < row_end) {
+        if (r < n_dst) {
             const int64_t s = self_idx != nullptr ? (int64_t)self_idx[r] : r;
             a_self[it] = s >= 0 ? s * d_in : -1;
             a_mean[it] = r * d_in;
@@ -531,9 +519,8 @@ sage_project_f32(const float* __restrict__ Hsrc, const int32_t* __restrict__ sel
             for (int tm = 0; tm < TM; ++tm) {
                 const float av = i == 0 ? f.a[tm].x : i == 1 ? f.a[tm].y : i == 2 ? f.a[tm].z : f.a[tm].w;
 #pragma unroll
-                for (int tn = 0; tn < TN; ++tn)   // slot-tree layers: operands exchanged, a lane then holds runs of one row
-                    acc[tm][tn] = TREE ? __builtin_amdgcn_mfma_f32_32x32x2f32(f.b[i][tn], av, acc[tm][tn], 0, 0, 0)
-                                       : __builtin_amdgcn_mfma_f32_32x32x2f32(av, f.b[i][tn], acc[tm][tn], 0, 0, 0);
+                for (int tn = 0; tn < TN; ++tn)
+                    acc[tm][tn] = __builtin_amdgcn_mfma_f32_32x32x2f32(av, f.b[i][tn], acc[tm][tn], 0, 0, 0);
             }
     };
     auto compute = [&](int st) {
@@ -578,19 +565,18 @@ sage_project_f32(const float* __restrict__ Hsrc, const int32_t* __restrict__ sel
 #pragma unroll
     for (int i = 0; i < D - 1; ++i)
         if (t + i < n_tiles) iter(t + i, i);
-    if (TREE)
-        tree_epilogue<TrF32, BM, BN, BN, TM, TN, kProjThreads, true>(acc, lds_f32, wm * (BM / 2), wn * (BN / 2), tid, lane, row0,
-                                                               row_end, col0, d_out, lds_bias, relu, out, tt, lvl,
-                                                               tile_in_level, my_id);
-    else
-        project_epilogue<TrF32, TM, TN>(acc, row0 + wm * (BM / 2), col0 + wn * (BN / 2), lane, row_end, d_out,
-                                        lds_bias + wn * (BN / 2), relu, out);
+    project_epilogue<TrF32, TM, TN>(acc, row0 + wm * (BM / 2), col0 + wn * (BN / 2), lane, n_dst, d_out,
+                                    lds_bias + wn * (BN / 2), relu, out);
 }
 
-// The large tile of the fp32 forward pass.  v_mfma_f32_32x32x2_f32 needs 512 cycles per 32 x 32 x 16 block,
+// The fp32 layer on the bf16 instruction.  v_mfma_f32_32x32x2_f32 needs 512 cycles per 32 x 32 x 16 block,
 // eight v_mfma_f32_32x32x16_bf16 of the split operands 256.  Both operands are split on their way
 // to LDS (three pieces each, k contiguous, row stride conflict free for 128-bit reads), the weights in
 // this kernel too, so nothing derived from them outlives the call.
+// 170 k rows of 2 x 100 -> 256 with means: 172 us against 218 on the fp32 instruction (146 with six products in
+// one accumulator, whose bits fell short of fp32's).  Small tiles wait for memory and gain nothing (16 k rows of
+// 2 x 256 -> 256 with means: 65 us against 59; 11 k of 2 x 128 -> 128: 17 against 17): they are split so that a
+// row's bits do not depend on the number of rows in its call.
 template <int BM, int BN, int BK, bool VEC, bool TREE>
 __global__ void __launch_bounds__(kProjThreads, 2)
 sage_project_split(const float* __restrict__ Hsrc, const int32_t* __restrict__ self_idx,
@@ -1299,8 +1285,12 @@ static hopgnn_status launch_project_f32(bool vec, hipStream_t s, const void* Hsr
             hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
                                 (int)lds) != hipSuccess)
             return HOPGNN_EHIP;
-        hipLaunchKernelGGL(kern, grid, dim3(kProjThreads), lds, s, a, self_idx, m, ws, wn, b, n_dst, d_in, k_total, d_out,
-                           relu, ntn, z, o, n_rows_dev, tt);
+        if constexpr (SPLIT)
+            hipLaunchKernelGGL(kern, grid, dim3(kProjThreads), lds, s, a, self_idx, m, ws, wn, b, n_dst, d_in, k_total, d_out,
+                               relu, ntn, z, o, n_rows_dev, tt);
+        else
+            hipLaunchKernelGGL(kern, grid, dim3(kProjThreads), lds, s, a, self_idx, m, ws, wn, b, n_dst, d_in, k_total, d_out,
+                               relu, ntn, z, o, n_rows_dev);
         HOPGNN_LAUNCH_CHECK();
         return HOPGNN_OK;
     };
@@ -1308,10 +1298,7 @@ static hopgnn_status launch_project_f32(bool vec, hipStream_t s, const void* Hsr
         return launch(tree != nullptr ? sage_project_split<BM, BN, BK, true, true>
                       : vec           ? sage_project_split<BM, BN, BK, true, false>
                                       : sage_project_split<BM, BN, BK, false, false>);
-    if constexpr (!SPLIT && BM == 64)
-        if (tree != nullptr) return launch(sage_project_f32<BM, BN, BK, 2, true, true>);
-    if constexpr (!SPLIT)
-        return launch(vec ? sage_project_f32<BM, BN, BK, 2, true, false> : sage_project_f32<BM, BN, BK, 2, false, false>);
+    if constexpr (!SPLIT) return launch(vec ? sage_project_f32<BM, BN, BK, 2, true> : sage_project_f32<BM, BN, BK, 2, false>);
 }
 
 template <typename Tr, int BM, int BN, int BK, int WM, int WN, int D = 2>
@@ -1409,16 +1396,14 @@ hopgnn_status project_dispatch(hopgnn_dtype dt, hipStream_t s, const void* Hsrc,
             if (tree->fan[h] < 1 || tree->fan[h] > kTreeMaxFan) return HOPGNN_EINVAL;
     }
     if (dt == HOPGNN_F32) {
-        // Large tiles once there is enough work to fill 256 CUs twice over.  On them inference (`split`: the
-        // single-call pass and hopgnn_sage_fwd) takes the split operands: 170 k rows of 2 x 100 -> 256 with
-        // means 218 -> 146 us; on small tiles, whose waits are for memory, only 58 -> 54.  The stored rows
-        // of a training forward decide the ReLU masks of its backward, so that a rounding of theirs moves
-        // gradients by far more than its own size (5.7e-5 of the three-layer gradients at that shape):
-        // hopgnn_sage_fwd_agg and _dev, which training calls, keep the fp32 instruction's bits.
-        if (d_out > 64 && work >= 512)
-            return split ? launch_project_f32<128, 128, 16, true>(vec, s, Hsrc, self_idx, mean, W_self, W_neigh, bias, n_dst, d_in, k_total, d_out, relu, zero, out, n_rows_dev, tree)
-                         : launch_project_f32<128, 128, 16, false>(vec, s, Hsrc, self_idx, mean, W_self, W_neigh, bias, n_dst, d_in, k_total, d_out, relu, zero, out, n_rows_dev, tree);
-        return launch_project_f32<64, 64, 32, false>(vec, s, Hsrc, self_idx, mean, W_self, W_neigh, bias, n_dst, d_in, k_total, d_out, relu, zero, out, n_rows_dev, tree);
+        // Large tiles once there is enough work to fill 256 CUs twice over.  `split` does not depend on the
+        // number of rows and both tiles sum in the same order, so that a row's bits do not depend on which rows
+        // share its call (merged groups, fused layers).
+        const bool big = d_out > 64 && work >= 512;
+        auto launch = split ? (big ? launch_project_f32<128, 128, 16, true> : launch_project_f32<64, 64, 32, true>)
+                            : (big ? launch_project_f32<128, 128, 16, false> : launch_project_f32<64, 64, 32, false>);
+        return launch(vec, s, Hsrc, self_idx, mean, W_self, W_neigh, bias, n_dst, d_in, k_total, d_out, relu, zero, out,
+                      n_rows_dev, tree);
     }
     const bool huge = d_out > 128 && work >= 1024;   // 256 x 256 tiles once they still fill 256 CUs
     const bool big = d_out > 64 && work >= 512;
@@ -1470,9 +1455,8 @@ extern "C" hopgnn_status hopgnn_sage_fwd(const void* Hsrc, hopgnn_dtype dt, int6
                                          const void* W_neigh, const void* bias, int32_t d_out,
                                          int32_t relu, void* out, void* ws, size_t ws_bytes,
                                          void* stream) {
-    // the layer as the single-call pass runs it: the same bits
-    return sage_fwd_marked(Hsrc, dt, n_src, d_in, self_idx, indptr, idx, n_dst, nullptr, W_self, W_neigh, bias, d_out,
-                           HOPGNN_AGG_MEAN, relu, out, ws, ws_bytes, stream, nullptr, true);
+    return hopgnn_sage_fwd_agg(Hsrc, dt, n_src, d_in, self_idx, indptr, idx, n_dst, W_self, W_neigh, bias, d_out,
+                               HOPGNN_AGG_MEAN, relu, out, ws, ws_bytes, stream);
 }
 
 extern "C" hopgnn_status hopgnn_sage_fwd_agg(const void* Hsrc, hopgnn_dtype dt, int64_t n_src, int32_t d_in,
@@ -1481,8 +1465,8 @@ extern "C" hopgnn_status hopgnn_sage_fwd_agg(const void* Hsrc, hopgnn_dtype dt, 
                                              const void* W_neigh, const void* bias, int32_t d_out, int32_t agg,
                                              int32_t relu, void* out, void* ws, size_t ws_bytes,
                                              void* stream) {
-    return hopgnn_sage_fwd_dev(Hsrc, dt, n_src, d_in, self_idx, indptr, idx, n_dst, nullptr, W_self, W_neigh, bias, d_out,
-                               agg, relu, out, ws, ws_bytes, stream);
+    return sage_fwd_marked(Hsrc, dt, n_src, d_in, self_idx, indptr, idx, n_dst, nullptr, W_self, W_neigh, bias, d_out, agg,
+                           relu, out, ws, ws_bytes, stream, nullptr, true);
 }
 
 extern "C" hopgnn_status hopgnn_sage_fwd_dev(const void* Hsrc, hopgnn_dtype dt, int64_t n_src, int32_t d_in,
@@ -1491,8 +1475,10 @@ extern "C" hopgnn_status hopgnn_sage_fwd_dev(const void* Hsrc, hopgnn_dtype dt, 
                                              const void* W_self, const void* W_neigh, const void* bias,
                                              int32_t d_out, int32_t agg, int32_t relu, void* out, void* ws,
                                              size_t ws_bytes, void* stream) {
+    // The forward call of a training step: its stored rows decide the ReLU masks of the backward, which flip with
+    // the rounding of a row near zero, so this call stays on the fp32 instruction.
     return sage_fwd_marked(Hsrc, dt, n_src, d_in, self_idx, indptr, idx, n_dst, n_dst_dev, W_self, W_neigh, bias, d_out,
-                           agg, relu, out, ws, ws_bytes, stream, nullptr);
+                           agg, relu, out, ws, ws_bytes, stream, nullptr, false);
 }
 
 namespace hopgnn {

@@ -504,7 +504,7 @@ constexpr int kTreeMaxFan = 64;          // a group of siblings must fit the sma
 // groups of siblings, the deepest level's rows are not written when tree->mean_next is given, and
 // that array receives the next layer's neighbour means (same bits as the segmented-mean kernel
 // would give over the stored rows).  Needs rows of whole 16-byte words, every fan <= kTreeMaxFan, no n_rows_dev.
-// split: large fp32 products on the bf16 instruction (split2_bf16); slot-tree layers of fp32 need it.
+// split: fp32 products on the bf16 instruction (split2_bf16); slot-tree layers of fp32 need it.
 hopgnn_status project_dispatch(hopgnn_dtype dt, hipStream_t s, const void* Hsrc, const int32_t* self_idx,
                                const void* agg, const void* W_self, const void* W_neigh, const uint16_t* Wt,
                                int32_t KP, const void* bias, int64_t n_dst, int32_t d_in, int32_t k_total,
@@ -527,6 +527,6 @@ hopgnn_status sage_fwd_marked(const void* Hsrc, hopgnn_dtype dt, int64_t n_src, 
                               const int32_t* indptr, const int32_t* idx, int64_t n_dst, const int64_t* n_dst_dev,
                               const void* W_self, const void* W_neigh, const void* bias, int32_t d_out, int32_t agg,
                               int32_t relu, void* out, void* ws, size_t ws_bytes, void* stream,
-                              const LayerMarks* marks, bool split = false);
+                              const LayerMarks* marks, bool split);
 
 }  // namespace hopgnn

@@ -295,6 +295,9 @@ class HotPath:
         backward pass.  Gradients are fp32 whatever the activation type.  The loss used by the
         harness is L = 1/2 |H_L|^2 for fp32 activations (dL/dH_L = H_L, read in place) and
         L = <G, H_L> with a fixed G for 2-byte activations (dL/dH_L = G, fp32).
+        From here on the step-by-step calls (`layer`, `layers`, `run_batch`, `run_group`) form fp32 layers of
+        "sage" with the fp32 matrix instruction (hopgnn_sage_fwd_dev), `forward` as before: the two agree to
+        rounding, no longer bit for bit.
         self.gW[k]: (gW_self, gW_neigh, gbias) for "sage"; (gW, None, gbias) for "gcn";
         (gW, None, gbias) plus self.g_attn[k] = (ga_src, ga_dst) for "gat"."""
         sh, dev, dt = self.shape, self.X.device, self.X.dtype
@@ -336,10 +339,11 @@ class HotPath:
             for k in range(L):
                 per_batch[k] = per_batch[k][:-2] + (self._fwd_ws[k].data_ptr(), self._fwd_ws[k].numel())
                 if self.model == "sage" and self._layer_fn is self._lib.hopgnn_sage_fwd:
-                    # rows that a backward pass will mask by: the call that keeps the fp32 instruction's rounding
-                    per_batch[k] = per_batch[k][:-4] + (hb.AGG_MEAN,) + per_batch[k][-4:]
+                    # rows that a backward pass will mask by: the call that stays on the fp32 instruction
+                    a = per_batch[k]
+                    per_batch[k] = a[:8] + (None,) + a[8:-4] + (hb.AGG_MEAN,) + a[-4:]
         if self.model == "sage":
-            self._layer_fn = self._lib.hopgnn_sage_fwd_agg
+            self._layer_fn = self._lib.hopgnn_sage_fwd_dev
         self._bwd_args = []
         hdt = hb.DTYPE_OF[dt]
         for b in range(self.group):

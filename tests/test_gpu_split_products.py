@@ -243,3 +243,57 @@ def test_sums_of_one_sign(hb, shape):
     assert rel(_forward(H, Ws, Wn, idx), out_ref) <= 0.5 * (2 * d_in) ** 0.5 * 2.0 ** -24
     for a, r, K in zip(got, ref, (n, n, n, 2 * d_out)):
         assert rel(a, r) <= 0.5 * max(K, 16) ** 0.5 * 2.0 ** -24
+
+
+@pytest.mark.parametrize("shape", [(33000, 36, 132), (33000, 37, 133), (5000, 12, 68)])
+def test_a_rows_bits_do_not_depend_on_the_rows_beside_it(hb, shape):
+    """The whole input, a tenth of it and a few rows (large tiles, small tiles) give a row the same bits, through
+    hopgnn_sage_fwd, hopgnn_sage_fwd_agg's mean and the single-call pass."""
+    n, d_in, d_out = shape
+    H, Ws, Wn, _, indptr, idx = _inputs(*shape, seed=10)
+    b = torch.randn(d_out, device=DEV)
+    ws = torch.empty(hb.hopgnn_sage_fwd_ws_bytes(torch.float32, n, d_in, d_out), dtype=torch.uint8, device=DEV)
+    outs = []
+    for rows in (n, n // 10, 33):
+        out, out_agg = torch.empty((rows, d_out), device=DEV), torch.empty((rows, d_out), device=DEV)
+        hb.hopgnn_sage_fwd(H, n, None, indptr, idx, rows, Ws, Wn, b, True, out, ws)
+        hb.hopgnn_sage_fwd_agg(H, n, None, indptr, idx, rows, Ws, Wn, b, hb.AGG_MEAN, True, out_agg, ws)
+        assert torch.equal(out, out_agg)
+        outs.append(out)
+    assert torch.equal(outs[1], outs[0][:n // 10]) and torch.equal(outs[2], outs[0][:33])
+    plain = torch.empty((n, d_out), device=DEV)
+    hb.hopgnn_sage_fwd(H, n, None, indptr, idx, n, Ws, Wn, None, False, plain, ws)
+    assert torch.equal(plain, _forward(H, Ws, Wn, idx))
+
+
+def test_merged_batches_keep_their_bits():
+    """Two batches in one call (520 large tiles) and one after the other (260 tiles' worth of small ones)."""
+    from paper_2409_00657_amd import synth
+    from paper_2409_00657_amd.pipeline import HotPath
+    g = synth.rmat_graph(13, 9.0, seed=11, device=DEV)
+    X = synth.features(g.n_vertices, 100, torch.float32, device=DEV)
+    W = synth.sage_weights(100, 256, 2, torch.float32, device=DEV, bias=True)
+    seeds = synth.seeds(g.n_vertices, 3000, 300, device=DEV)
+    outs = []
+    for merge in (True, False):
+        hp = HotPath(g.offsets, g.indices, X, W, 1500, [10, 3], group=2, merge=merge)
+        outs.append(torch.empty((3000, 256), device=DEV))
+        hp.forward(seeds, [17, 18], outs[-1])
+    torch.cuda.synchronize()
+    assert torch.equal(outs[0], outs[1])
+
+
+def test_the_training_forward_and_the_single_call_agree_to_rounding():
+    from paper_2409_00657_amd import synth
+    from paper_2409_00657_amd.pipeline import HotPath
+    g = synth.rmat_graph(13, 9.0, seed=11, device=DEV)
+    X = synth.features(g.n_vertices, 100, torch.float32, device=DEV)
+    W = synth.sage_weights(100, 256, 2, torch.float32, device=DEV, bias=True)
+    seeds = synth.seeds(g.n_vertices, 3000, 300, device=DEV)
+    hp = HotPath(g.offsets, g.indices, X, W, 3000, [10, 3])
+    out = torch.empty((3000, 256), device=DEV)
+    hp.forward(seeds, [17], out)
+    assert torch.equal(hp.run_batch(seeds, 17), out)
+    hp.enable_backward()
+    train = hp.run_batch(seeds, 17)
+    assert _err(train, out.double()) <= 2 * (BOUND(200) + BOUND(512))      # two layers, a rounding error on either side
