@@ -529,8 +529,11 @@ hopgnn_status hopgnn_gcn_bwd(const void *Hsrc, hopgnn_dtype dt, int64_t n_src, i
  *          bytes (0 for invalid arguments), 256-byte aligned.
  * Arithmetic is fp32; with a 2-byte dt the gradient with respect to z is rounded to dt before the
  * two matrix products (gW, dHsrc) as in hopgnn_sage_bwd.  The sums over destination rows into a
- * source row (dz, score gradients) are taken in no fixed order: their rounding may differ by call.
- * gbias, ga_src and ga_dst are summed in a fixed order.  Errors as hopgnn_gat_fwd, plus EINVAL for
+ * source row (dz, score gradients, and ga_src and ga_dst, which sum those) are taken in no fixed
+ * order: their rounding may differ by call.  gbias is summed in a fixed order.  From 512 destination
+ * rows on the workspace holds lists of the entries by source row and the masked gradient, about
+ * 4 d_out + 20 n_heads + 132 bytes a destination row, whether or not the call can use them.
+ * Errors as hopgnn_gat_fwd, plus EINVAL for
  * a NULL fwd_ws or a ReLU without out_fwd, ENOMEM_WS for a short workspace.
  */
 size_t hopgnn_gat_bwd_ws_bytes(hopgnn_dtype dt, int64_t n_src, int64_t n_dst, int32_t d_in, int32_t d_out,

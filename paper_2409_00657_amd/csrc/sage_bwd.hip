@@ -1434,11 +1434,21 @@ reduce_parts_add(const float* __restrict__ partial, int64_t part_stride, int32_t
 // 1 / denominator, S = sum alpha_i dalpha_i, sum of de_i) and the masked gradient, and one wavefront per
 // source row walks its list: alpha and dalpha of an entry come again from those and the row's own z,
 // which stays in registers.  dz is written once, finished; no float atomics.
+// A list longer than kGatPiece entries (a vertex that thousands of micrographs share) is cut into pieces of
+// that many, a wavefront each, which add what they have to the row's zeroed dz: everything a row collects is
+// linear in its entries.  One wavefront takes 0.45 us an entry at the end of a list that the others have left: 170 k
+// rows x 6 entries x 256 columns, a tenth of the entries naming one vertex, whole call: 6.4 ms with float atomics,
+// 47 with whole lists, 3.4 with pieces (of 1024 entries 3.7); drawn by a power law of 0.9: 5.2, 21.8, 2.6 (2.8).
+// Below 512 entries a piece's atomics and its second look at the row cost the ordinary skewed input more than the
+// shorter tail gives (training iteration of 1024 roots, 15,10,5, 100-256: 2866 us at 512, 2910 at 256).
 // Lane layout of both passes: a head's d_head / 4 words on a power-of-two segment of `seg` lanes (NW words
 // a lane when it has more than 64), 64 / seg heads side by side, blockIdx.y the group of heads.
 // Needs d_head % 4 == 0 and at most 512, and a 16-byte aligned dOut.  Lists are sized for kGatListCap entries
-// per destination row on average; a longer input (only the device knows) is left to the kernels below.
+// per destination row on average; a longer input (only the device knows) is left to the kernels below, which pay
+// nothing for it that could be measured (40 k rows x 64 entries: 5045 us before there were lists, 5076 now; at 32
+// entries, 16 k rows, the lists take 442 us and the atomics 1250).
 constexpr int kGatListCap = 32;
+constexpr int kGatPiece = 512;
 
 struct GatGate {                 // run only if the entries exceed (over = 1) / do not exceed (0) what the lists hold
     const int32_t* nnz;          // DEVICE; NULL: always run
@@ -1480,7 +1490,7 @@ __device__ __forceinline__ int32_t gat_entry(int32_t e, int32_t beg, int32_t end
 __global__ void __launch_bounds__(kBwdThreads)
 gat_list_zero(int32_t* __restrict__ cnt, int32_t* __restrict__ cursor, int64_t n_src, const int64_t* __restrict__ n_rows_dev) {
     const int64_t i = (int64_t)blockIdx.x * kBwdThreads + threadIdx.x;
-    if (i == 0) *cursor = 0;
+    if (i < 2) cursor[i] = 0;      // entries placed, pieces
     if (i < n_src && (n_rows_dev == nullptr || i < *n_rows_dev)) cnt[i] = 0;
 }
 
@@ -1507,10 +1517,12 @@ gat_list_entries(const int32_t* __restrict__ self_idx, const int32_t* __restrict
     }
 }
 
-// Every source row's piece of the list, in no particular order of the rows: one atomic per workgroup.
+// Every source row's part of the list, in no particular order of the rows: one atomic per workgroup.  A row
+// whose list is cut enters its pieces (row, first entry), at most 2 / kGatPiece per entry, and has its dz zeroed.
 __global__ void __launch_bounds__(kBwdThreads)
 gat_list_place(const int32_t* __restrict__ cnt, int32_t* __restrict__ pos, int32_t* __restrict__ cursor, int64_t n_src,
-               const int64_t* __restrict__ n_rows_dev, GatGate gate) {
+               const int64_t* __restrict__ n_rows_dev, int2* __restrict__ pieces, float* __restrict__ dZ, int32_t d_out,
+               GatGate gate) {
     if (gate_closed(gate)) return;
     __shared__ int32_t wave_total[kBwdThreads / kWave], base;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -1533,7 +1545,19 @@ gat_list_place(const int32_t* __restrict__ cnt, int32_t* __restrict__ pos, int32
     __syncthreads();
     int32_t before = base;
     for (int w = 0; w < wave; ++w) before += wave_total[w];
-    if (live) pos[u] = before + incl - c;
+    const int32_t first = before + incl - c;
+    if (live) pos[u] = first;
+    for (uint64_t m = __ballot(c > kGatPiece); m != 0; m &= m - 1) {      // the wavefront takes its long rows in turn
+        const int src = __ffsll((unsigned long long)m) - 1;
+        const int64_t row = u - lane + src;
+        const int32_t row_c = __shfl(c, src, kWave), row_first = __shfl(first, src, kWave);
+        const int32_t n = (row_c + kGatPiece - 1) / kGatPiece;
+        int32_t p0 = 0;
+        if (lane == 0) p0 = atomicAdd(cursor + 1, n);
+        p0 = __shfl(p0, 0, kWave);
+        for (int32_t i = lane; i < n; i += kWave) pieces[p0 + i] = make_int2((int32_t)row, row_first + i * kGatPiece);
+        for (int32_t i = lane; i < d_out; i += kWave) dZ[row * d_out + i] = 0.f;
+    }
 }
 
 // One wavefront per destination row and group of heads.  The scores are read twice (maximum, then everything
@@ -1621,14 +1645,14 @@ gat_bwd_stats(const float* __restrict__ Z, const float* __restrict__ scores, con
     }
 }
 
-// One wavefront per source row (rows dealt out over the grid) and group of heads: dz[u] finished, and the
-// workgroup's part of ga_src / ga_dst, partial[b][0][n] and partial[b][1][n].
+// One wavefront per piece of a long list, then per source row (both dealt out over the grid), and group of heads:
+// dz[u] finished, and the workgroup's part of ga_src / ga_dst, partial[b][0][n] and partial[b][1][n].
 template <typename Tr, int NW>
 __global__ void __launch_bounds__(kBwdThreads)
 gat_bwd_pull(const float* __restrict__ Z, const float* __restrict__ scores, const float* __restrict__ dY,
              const float4* __restrict__ stat, const float* __restrict__ sum_de, const int32_t* __restrict__ cnt,
-             const int32_t* __restrict__ pos, const int32_t* __restrict__ list, const typename Tr::store_t* __restrict__ a_src,
-             const typename Tr::store_t* __restrict__ a_dst, int64_t n_src, const int64_t* __restrict__ n_rows_dev,
+             const int32_t* __restrict__ pos, const int32_t* __restrict__ list, const int2* __restrict__ pieces,
+             const int32_t* __restrict__ n_pieces_dev, const typename Tr::store_t* __restrict__ a_src, const typename Tr::store_t* __restrict__ a_dst, int64_t n_src, const int64_t* __restrict__ n_rows_dev,
              int32_t d_out, int32_t n_heads, int32_t seg, float* __restrict__ dZ, float* __restrict__ partial, GatGate gate) {
     if (gate_closed(gate)) return;
     constexpr int WAVES = kBwdThreads / kWave;
@@ -1653,7 +1677,21 @@ gat_bwd_pull(const float* __restrict__ Z, const float* __restrict__ scores, cons
         y.z += a * x.z;
         y.w += a * x.w;
     };
-    for (int64_t u = (int64_t)blockIdx.x * WAVES + wave; u < n_src; u += (int64_t)gridDim.x * WAVES) {
+    const int32_t n_pieces = *n_pieces_dev;
+    for (int64_t t = (int64_t)blockIdx.x * WAVES + wave; t < n_pieces + n_src; t += (int64_t)gridDim.x * WAVES) {
+        const bool piece = t < n_pieces;          // uniform over the wavefront
+        int64_t u = t - n_pieces;
+        int32_t beg, end;
+        if (piece) {
+            const int2 p = pieces[t];
+            u = p.x;
+            beg = p.y;
+            end = pos[u] < beg + kGatPiece ? pos[u] : beg + kGatPiece;
+        } else {
+            if (cnt[u] > kGatPiece) continue;     // its pieces have it
+            end = pos[u];
+            beg = end - cnt[u];
+        }
         float4 z[NW], acc[NW];
 #pragma unroll
         for (int i = 0; i < NW; ++i) {
@@ -1663,7 +1701,6 @@ gat_bwd_pull(const float* __restrict__ Z, const float* __restrict__ scores, cons
         }
         const float ssrc = scores[u * stride + L.h];
         float dss = 0.f, dsd = 0.f;
-        const int32_t end = pos[u], beg = end - cnt[u];
         constexpr int U = 4;      // entries in flight
         for (int32_t e = beg; e < end; e += U) {
             int32_t x[U];
@@ -1699,7 +1736,16 @@ gat_bwd_pull(const float* __restrict__ Z, const float* __restrict__ scores, cons
             acc[i].y += dss * as[i].y + dsd * ad[i].y;
             acc[i].z += dss * as[i].z + dsd * ad[i].z;
             acc[i].w += dss * as[i].w + dsd * ad[i].w;
-            if (L.ok[i]) *reinterpret_cast<float4*>(dZ + u * d_out + L.col[i]) = acc[i];
+            if (!L.ok[i]) continue;
+            float* dz = dZ + u * d_out + L.col[i];
+            if (piece) {
+                atomicAdd(dz, acc[i].x);
+                atomicAdd(dz + 1, acc[i].y);
+                atomicAdd(dz + 2, acc[i].z);
+                atomicAdd(dz + 3, acc[i].w);
+            } else {
+                *reinterpret_cast<float4*>(dz) = acc[i];
+            }
         }
     }
 #pragma unroll
@@ -1900,20 +1946,22 @@ gat_bwd_src(const float* __restrict__ Z, const float* __restrict__ ds, const typ
 }
 
 // Workgroups (= parts of ga_src / ga_dst) of the source-row kernels: at least 16 rows each, and no more than
-// fill the chip eight times over, so that the parts stay few.
-static inline int64_t gat_src_parts(int64_t n_src) {
-    const int64_t want = ceil_div(n_src, 16);
+// fill the chip eight times over, so that the parts stay few.  (Few source rows may have long lists: the
+// destination rows count as well.)
+static inline int64_t gat_src_parts(int64_t n_src, int64_t n_dst) {
+    const int64_t want = ceil_div(n_src > n_dst ? n_src : n_dst, 16);
     return want < 2048 ? want : 2048;
 }
 
 struct GatBwdWs {
     size_t dz_bytes, ds_bytes, col_bytes;
-    size_t cnt_bytes, list_bytes, stat_bytes, sum_bytes, masked_bytes;      // the source-row path; 0 where it is not taken
+    size_t cnt_bytes, list_bytes, piece_bytes, stat_bytes, sum_bytes, masked_bytes;      // the source-row path; 0 where it is not taken
     BwdWs G;          // the weight gradient's partial tiles (rows = source rows)
     size_t total;
 };
 // Whether the source rows collect their gradient themselves: the lane layout fits, positions fit 32 bits, and
-// there are enough rows (the lists and the gated launches cost about eight launches).
+// there are enough rows (the lists and the gated launches cost about eight launches; 512 rows x 10 entries x 128
+// columns: 80 us by source rows, 107 with atomics; fewer rows were not measured by source rows).
 static inline bool gat_by_source(int64_t n_dst, int32_t d_out, int32_t n_heads) {
     const int32_t dh = d_out / n_heads;
     return n_dst >= 512 && dh % 4 == 0 && dh <= 512 && n_dst * (1 + kGatListCap) < ((int64_t)1 << 31);
@@ -1923,10 +1971,12 @@ static GatBwdWs gat_bwd_ws_layout(int64_t n_src, int64_t n_dst, int32_t d_in, in
     const int64_t ns = n_src > 0 ? n_src : 1, nd = n_dst > 0 ? n_dst : 1;
     L.dz_bytes = align_up((size_t)ns * d_out * 4, 256);
     L.ds_bytes = align_up((size_t)ns * 2 * n_heads * 4, 256);
-    const int64_t parts = ceil_div(nd, kColRows) > 2 * gat_src_parts(ns) ? ceil_div(nd, kColRows) : 2 * gat_src_parts(ns);
+    const int64_t src_parts = 2 * gat_src_parts(ns, nd);
+    const int64_t parts = ceil_div(nd, kColRows) > src_parts ? ceil_div(nd, kColRows) : src_parts;
     if (gat_by_source(nd, d_out, n_heads)) {
         L.cnt_bytes = align_up((size_t)ns * 4, 256);        // counts, positions (and the cursor in a word of its own)
         L.list_bytes = align_up((size_t)nd * (1 + kGatListCap) * 4, 256);
+        L.piece_bytes = align_up(((size_t)nd * (1 + kGatListCap) * 2 / kGatPiece + 1) * 8, 256);
         L.stat_bytes = align_up((size_t)nd * n_heads * 16, 256);
         L.sum_bytes = align_up((size_t)nd * n_heads * 4, 256);
         L.masked_bytes = align_up((size_t)nd * d_out * 4, 256);
@@ -1934,7 +1984,7 @@ static GatBwdWs gat_bwd_ws_layout(int64_t n_src, int64_t n_dst, int32_t d_in, in
     L.col_bytes = align_up((size_t)parts * d_out * 4, 256);
     L.G = bwd_ws_layout(ns, d_in, d_out, 0);      // (row splits as for fp32 operands: any count is valid)
     L.total = L.dz_bytes + L.ds_bytes + L.col_bytes + L.G.partial_bytes + L.G.bias_bytes;
-    if (L.cnt_bytes > 0) L.total += 2 * L.cnt_bytes + 256 + L.list_bytes + L.stat_bytes + L.sum_bytes + L.masked_bytes;
+    if (L.cnt_bytes > 0) L.total += 2 * L.cnt_bytes + 256 + L.list_bytes + L.piece_bytes + L.stat_bytes + L.sum_bytes + L.masked_bytes;
     return L;
 }
 
@@ -1968,7 +2018,7 @@ static hopgnn_status gat_bwd_typed(const void* Hsrc, int64_t n_src, const int64_
     }
     if (n_src == 0) return HOPGNN_OK;              // no entries anywhere: only the bias has a gradient
 
-    const int32_t src_blocks = (int32_t)gat_src_parts(n_src);
+    const int32_t src_blocks = (int32_t)gat_src_parts(n_src, n_dst);
     GatGate gate{nullptr, 0, 0};
     if (L.cnt_bytes > 0 && aligned(dOut, 16)) {
         gate = GatGate{indptr + n_dst, (int64_t)kGatListCap * n_dst, 0};
@@ -1977,7 +2027,8 @@ static hopgnn_status gat_bwd_typed(const void* Hsrc, int64_t n_src, const int64_
         int32_t* cnt = reinterpret_cast<int32_t*>(q += 256);
         int32_t* pos = reinterpret_cast<int32_t*>(q += L.cnt_bytes);
         int32_t* list = reinterpret_cast<int32_t*>(q += L.cnt_bytes);
-        float4* stat = reinterpret_cast<float4*>(q += L.list_bytes);
+        int2* pieces = reinterpret_cast<int2*>(q += L.list_bytes);
+        float4* stat = reinterpret_cast<float4*>(q += L.piece_bytes);
         float* sum_de = reinterpret_cast<float*>(q += L.stat_bytes);
         float* masked = reinterpret_cast<float*>(q += L.sum_bytes);
         const int32_t words = d_out / n_heads / 4;
@@ -1992,7 +2043,7 @@ static hopgnn_status gat_bwd_typed(const void* Hsrc, int64_t n_src, const int64_
                            n_src, n_src_dev, cnt, list, gate);
         HOPGNN_LAUNCH_CHECK();
         hipLaunchKernelGGL(gat_list_place, dim3((unsigned)ceil_div(n_src, kBwdThreads)), dim3(kBwdThreads), 0, s, cnt, pos,
-                           cursor, n_src, n_src_dev, gate);
+                           cursor, n_src, n_src_dev, pieces, dZ, d_out, gate);
         HOPGNN_LAUNCH_CHECK();
         hipLaunchKernelGGL(gat_list_entries<true>, by_row, dim3(kBwdThreads), 0, s, self_idx, indptr, idx, n_dst,
                            n_src, n_src_dev, pos, list, gate);
@@ -2004,7 +2055,7 @@ static hopgnn_status gat_bwd_typed(const void* Hsrc, int64_t n_src, const int64_
         HOPGNN_LAUNCH_CHECK();
         auto pull = words > kWave ? gat_bwd_pull<Tr, 2> : gat_bwd_pull<Tr, 1>;
         hipLaunchKernelGGL(pull, dim3((unsigned)src_blocks, groups), dim3(kBwdThreads), 0, s, Z, scores, relu ? masked : dOut, stat,
-                           sum_de, cnt, pos, list, static_cast<const T*>(a_src), static_cast<const T*>(a_dst), n_src, n_src_dev,
+                           sum_de, cnt, pos, list, pieces, cursor + 1, static_cast<const T*>(a_src), static_cast<const T*>(a_dst), n_src, n_src_dev,
                            d_out, n_heads, seg, dZ, col, gate);
         HOPGNN_LAUNCH_CHECK();
         gate.over = 1;           // the kernels below then run only for more entries than the lists hold

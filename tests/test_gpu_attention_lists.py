@@ -79,3 +79,29 @@ def test_entries_past_the_device_count_stay_inside_the_lists(hb, heads, d_out): 
     assert bool((res[1][4][live:] == 7.0).all())
     for x, y in zip(res[1][:4] + [res[1][4][:live]], res[0][:4] + [res[0][4][:live]]):     # the bound of the test above
         assert float((x - y).abs().max() / y.pow(2).mean().sqrt()) <= 1e-4
+
+
+HUBS = [  # as SHAPES
+    (700, 2400, 20, 24, 14, 6), (900, 3200, 16, 320, 9, 16), (800, 3000, 12, 260, 10, 1),
+    (3, 3000, 16, 64, 6, 4)]            # fewer source rows than a workgroup has wavefronts, all with long lists
+
+
+@pytest.mark.parametrize("dt", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("shape", HUBS)
+def test_long_lists_are_cut_into_pieces(hb, orc, monkeypatch, dt, shape):  # noqa: F811
+    """A third of the entries name one row, and rows 1..16 are named by 500..515 entries each (their own terms
+    come on top): lists on both sides of a piece's length and of many pieces."""
+    plain = general._rand_csr
+
+    def hubs(rng, n_dst, n_src, max_len, p_invalid=0.15):
+        indptr, idx = plain(rng, n_dst, n_src, max_len, p_invalid)
+        order = rng.permutation(len(idx))
+        cut = len(idx) // 3
+        idx[order[:cut]] = 0
+        for row in range(1, min(17, n_src)):
+            idx[order[cut:cut + 499 + row]] = row
+            cut += 499 + row
+        return indptr, idx
+
+    monkeypatch.setattr(general, "_rand_csr", hubs)
+    general.test_attention_backward_vs_oracle(hb, orc, dt, shape)
