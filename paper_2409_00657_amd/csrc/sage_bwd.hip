@@ -99,8 +99,12 @@ bwd_zero(float4* __restrict__ p, int64_t n4, const int64_t* __restrict__ n_rows_
 // to LDS, which keeps the loop free of branches.  The tile goes to partial[split]; workgroups
 // of the first k-tile row also produce the column sums of dZ.
 // v_mfma_f32_32x32x2_f32 needs 512 cycles of the matrix cores per 32 x 32 x 16 block, the eight products of the
-// split operands 256.  At 170 k rows x 2 x 100 -> 256 those are 56 of the kernel's 176 us: what it waits for is
-// the splitting and the adds (vector instructions) and the LDS, two workgroups to a CU, each step behind a barrier.
+// split operands 256.  At 170 k rows x 2 x 100 -> 256 those are 56 of the kernel's 168 us: what it waits for is
+// the splitting (vector instructions) and the LDS, two workgroups to a CU, each step behind a barrier.
+// Thousands of rows are summed in the instruction's accumulator.  Error of 170 k rows x 100 x 256 (normal / all
+// positive terms): 6.7e-7 / 6.9e-8 with the fp32 instruction, 2.4e-7 / 5.3e-8 so; summing every step from zero and
+// adding it to the tile by ordinary additions gives 2.0e-7 / 5.1e-8 for 9 us more, and 10 % of a whole training
+// iteration where the widths are odd (1346 roots, 6,21, fp16, 35-18: 137 us, 149 with the additions).
 // The host sizes the row splits for the capacity; when only the device knows how many rows exist,
 // the rows that do are dealt out evenly over the same number of splits (multiples of 32 rows, never
 // more than the host's figure), so that no split idles while another works through the whole input.
@@ -267,23 +271,7 @@ bwd_weight_grad(const typename Tr::store_t* __restrict__ Hsrc, const int32_t* __
                 fa[p][i] = tr_column8(&As[buf][p][0][0], kGradLd, 8 * g, (2 * wk + i) * 32, lane);
                 fb[2 - p][i] = tr_column8(&Bs[buf][2 - p][0][0], kGradLd, 8 * g, (2 * wn + i) * 32, lane);
             }
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            // Thousands of rows: the leading products of a step are summed from zero and added to the tile by
-            // ordinary additions, which round to nearest.  Error of 170 k rows x 100 x 256 (normal / all positive
-            // terms): 6.7e-7 / 6.9e-8 with the fp32 instruction, 2.4e-7 / 5.3e-8 with the tile as the
-            // instruction's own accumulator (9 us a training iteration of that shape less), 2.0e-7 / 5.1e-8 so.
-            floatx16 sum[1][2], lo1[1][2] = {{low[i][0], low[i][1]}};
-            zero_acc<1, 2>(sum);
-            const uint4 fi[3][1] = {{fa[0][i]}, {fa[1][i]}, {fa[2][i]}};
-            mma_pieces<1, 2, false>(sum, lo1, fi, fb);
-#pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                low[i][j] = lo1[0][j];
-#pragma unroll
-                for (int e = 0; e < 16; ++e) acc[i][j][e] += sum[0][j][e];
-            }
-        }
+        mma_pieces<2, 2, false>(acc, low, fa, fb);
         store(c + 1, s_cur, f, buf ^ 1);
         lds_barrier();
     }
