@@ -1,17 +1,19 @@
-"""The fp32 contractions (projection of the single-call pass, weight gradient, input gradient) as six bf16 products of split operands:
-tile edges, magnitudes at both ends of the type, and infinities, against 64-bit products."""
+"""The fp32 contractions (projection, weight gradient, input gradient) as eight bf16 products of split operands, against
+64-bit products: tile edges, magnitudes at both ends of the type, infinities, single products, sums of one sign, and
+the bits of a row beside different neighbours."""
 import pytest
 import torch
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 # A sum of K products in fp32: rounding errors of 2^-24 each, their square root over K of it; a factor of 4 for
-# the worst of a tensor's elements over the tensor's scale.  The three products left out stay below 2^-22.
+# the worst of a tensor's elements over the tensor's scale.  The partial product left out stays below 2^-33.
 BOUND = lambda K: 4 * max(K, 16) ** 0.5 * 2.0 ** -24
 
 # (rows, d_in, d_out): one row and word, remainders of the 64-row tile, widths off the 16-byte grid, the first
-# sizes of the 128-row tile (512 tiles and more) with remainders in every direction
-SHAPES = [(1, 4, 4), (63, 20, 12), (65, 7, 5), (129, 100, 256), (64, 16, 64), (33000, 36, 132), (65537, 12, 68)]
+# sizes of the 128-row tile (512 tiles and more) with remainders in every direction, on and off that grid
+SHAPES = [(1, 4, 4), (63, 20, 12), (65, 7, 5), (129, 100, 256), (64, 16, 64), (33000, 36, 132), (65537, 12, 68),
+          (33000, 37, 133), (65537, 13, 70), (33000, 67, 130)]
 
 
 @pytest.fixture(scope="module")

@@ -16,7 +16,8 @@ DEV = "cuda:0"
 CASES = [
     # fanouts, seeds per batch, group, merge, dtype, feature dim, hidden
     ([10, 10], 300, 1, False, torch.float32, 128, 128),       # 64-row tiles, 6 groups of 10 per tile
-    ([15, 10, 5], 120, 1, False, torch.float32, 100, 256),    # three layers; 128-row tiles on layer 1; 400-byte rows
+    ([15, 10, 5], 120, 1, False, torch.float32, 100, 256),    # three layers; 312 tiles of 128 rows on layer 1, so 64-row ones
+    ([15, 10, 5], 240, 1, False, torch.float32, 100, 256),    # three layers; 128-row tiles (624) on layer 1; 400-byte rows
     ([25, 10], 500, 1, False, torch.bfloat16, 256, 256),      # 256-row tiles: 10 groups of 25
     ([10, 10, 10], 64, 4, True, torch.float16, 128, 512),     # a merged group, N = 512
     ([10, 10, 10], 40, 3, False, torch.float16, 64, 64),      # batches of a group run one after the other
