@@ -44,7 +44,9 @@ GATHER_TRAFFIC_OVER_ALGORITHMIC = {256: 1.008, 400: 1.127, 512: 1.012}
 # output" (the self half of the operand is read from the gathered rows, which partly stay in cache)
 PROJECT_L1_TRAFFIC_OVER_IO = {3: (116153.2 + 32768.0) * 1024 / (169984 * 200 * 4 + 2 * 16384 * 256 * 4),
                               4: (68137.1 + 4096.0) * 1024 / (106496 * 512 * 2 + 2 * 4096 * 256 * 2)}
-MFMA_PEAK_TFLOPS = {"f32": 157.3, "bf16": 2500.0, "f16": 2500.0}
+# fp32 layers of the single-call pass run on the bf16 instruction, eight products of split operands for one fp32
+# product: their ceiling is an eighth of the bf16 rate (the fp32 instruction's own is 157.3)
+MFMA_PEAK_TFLOPS = {"f32": 2500.0 / 8, "bf16": 2500.0, "f16": 2500.0}
 DTYPE_NAME = {"torch.float32": "f32", "torch.bfloat16": "bf16", "torch.float16": "f16"}
 HEADLINE_CONFIG = 3
 PER_CONFIG = [(2, 1), (4, 1), (5, 8), (5, 16), (5, 32), (5, 64)]      # (workload shape, batches per pre-gather)
