@@ -370,8 +370,8 @@ hopgnn_status hopgnn_sage_fwd_agg(const void *Hsrc, hopgnn_dtype dt, int64_t n_s
  * rows past it are neither read nor written.  Used with hopgnn_sample_dedup, whose level sizes
  * depend on the data.  The identity-self check (n_src >= n_dst) applies to the capacity.
  * For fp32 this is also the forward call of a training step (n_dst_dev NULL where the host knows the
- * count): it stays on the fp32 matrix instruction, whose rounding decides the ReLU masks of rows
- * near zero, where hopgnn_sage_fwd_agg splits its operands (see hopgnn_sage_fwd).
+ * count): it stays on the fp32 matrix instruction, where hopgnn_sage_fwd_agg splits its operands
+ * (see hopgnn_sage_fwd), so that the ReLU masks a backward pass takes from its rows stay the same.
  */
 hopgnn_status hopgnn_sage_fwd_dev(const void *Hsrc, hopgnn_dtype dt, int64_t n_src, int32_t d_in,
                                   const int32_t *self_idx, const int32_t *indptr, const int32_t *idx,
