@@ -42,8 +42,8 @@ HBM_PEAK_GBPS = 8000.0
 GATHER_TRAFFIC_OVER_ALGORITHMIC = {256: 1.008, 400: 1.127, 512: 1.012}
 # the same for the first projection of the fused path: counter bytes per launch over "left operand once +
 # output" (the self half of the operand is read from the gathered rows, which partly stay in cache)
-PROJECT_L1_TRAFFIC_OVER_IO = {3: (116153.2 + 32768.0) * 1024 / (169984 * 200 * 4 + 2 * 16384 * 256 * 4),
-                              4: (68137.1 + 4096.0) * 1024 / (106496 * 512 * 2 + 2 * 4096 * 256 * 2)}
+PROJECT_L1_TRAFFIC_OVER_IO = {3: (116180.1 + 32768.0) * 1024 / (169984 * 200 * 4 + 2 * 16384 * 256 * 4),
+                              4: (67918.4 + 4096.0) * 1024 / (106496 * 512 * 2 + 2 * 4096 * 256 * 2)}
 # fp32 layers of the single-call pass run on the bf16 instruction, eight products of split operands for one fp32
 # product: their ceiling is an eighth of the bf16 rate (the fp32 instruction's own is 157.3)
 MFMA_PEAK_TFLOPS = {"f32": 2500.0 / 8, "bf16": 2500.0, "f16": 2500.0}

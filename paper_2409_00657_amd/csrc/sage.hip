@@ -573,9 +573,9 @@ sage_project_f32(const float* __restrict__ Hsrc, const int32_t* __restrict__ sel
 // eight v_mfma_f32_32x32x16_bf16 of the split operands 256.  Both operands are split on their way
 // to LDS (three pieces each, k contiguous, row stride conflict free for 128-bit reads), the weights in
 // this kernel too, so nothing derived from them outlives the call.
-// 170 k rows of 2 x 100 -> 256 with means: 172 us against 218 on the fp32 instruction (146 with six products in
+// 170 k rows of 2 x 100 -> 256 with means: 169 us against 218 on the fp32 instruction (146 with six products in
 // one accumulator, whose bits fell short of fp32's).  Small tiles wait for memory and gain nothing (16 k rows of
-// 2 x 256 -> 256 with means: 65 us against 59; 11 k of 2 x 128 -> 128: 17 against 17): they are split so that a
+// 2 x 256 -> 256 with means: 64 us against 59; 11 k of 2 x 128 -> 128: 17 against 17): they are split so that a
 // row's bits do not depend on the number of rows in its call.
 template <int BM, int BN, int BK, bool VEC, bool TREE>
 __global__ void __launch_bounds__(kProjThreads, 2)
