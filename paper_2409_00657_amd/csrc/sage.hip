@@ -358,7 +358,8 @@ __device__ __forceinline__ void tree_epilogue(floatx16 (&acc)[TM][TN], void* lds
     }
 }
 
-// fp32: v_mfma_f32_32x32x2_f32 (lane l feeds A[row l%32][k = l/32] and B[k = l/32][col l%32]).
+// fp32 on its own instruction, for the forward call of a training step and the GCN and attention layers:
+// v_mfma_f32_32x32x2_f32 (lane l feeds A[row l%32][k = l/32] and B[k = l/32][col l%32]).
 // LDS: A row-major [BM][BK+4] read as 128-bit words - lane group g = l/32 takes the four
 // k values 4g..4g+3 of an 8-wide K block and the four MFMAs of the block pair A's i-th
 // value with B row 4g+i, which only permutes the order in which k is summed.
