@@ -128,10 +128,254 @@ sample_micrographs(const OffT* __restrict__ offsets, const int32_t* __restrict__
     }
 }
 
+// The same micrographs with every level's parents taken once each.  Equal vertices on one level of a
+// micrograph draw the same children (the draws depend on key, root, vertex, hop and draw only), and with
+// replacement on skewed graphs most slots are such repeats: of the parents of the last hop 17 to 53 % are
+// distinct on power-law graphs, 66 to 78 % on uniform ones.  Per level:
+//   A  one thread per distinct parent: its row bounds, the reciprocal of its degree and the first hash round
+//   B  one thread per draw of a distinct parent: the second hash round, the remainder by a multiply-high with
+//      that reciprocal (exact, below), one neighbour read, the mark
+//   C  every slot copies its parent's draw out of LDS; a non-leaf level is then reduced to its distinct vertices
+//      (LDS hash table, the first slot of a vertex stands for it, distinct vertices numbered in slot order)
+// so that a slot costs an LDS read and its stores where it cost three loads, two hash rounds and a 64-bit remainder.
+// floor(x M / 2^64) with M = floor((2^64 - 1) / d) is floor(x / d) or one less: x M / 2^64 > x / d - 1.
+// The level lives in LDS throughout; the host takes this kernel where it fits (see lds_shape).
+struct DrawParent {
+    uint64_t first, degree, recip, hashed;      // row start, row length, M, first hash round
+};
+
+struct LdsShape {
+    int32_t n_parents;      // capacity: slots of the widest non-leaf level
+    int32_t table_mask;     // entries of the hash table - 1 (a power of two, at least twice n_parents)
+    int32_t draws_off, vert_off, rank_off, key_off, first_off;      // byte offsets behind the parents
+    int32_t bytes;
+    uint32_t f_magic[kMaxLayers + 1];      // c / f[h] = __umulhi(c, f_magic[h]) for c < 2^16; 0 for f[h] = 1
+};
+
+// Where it pays: with thousands of micrographs the chip is full of workgroups that wait for the graph (page
+// translations of random reads, 10 to 13 G/s), and what counts is how few reads they make and how many workgroups are
+// resident: two wavefronts (256 threads leave most lanes idle between the barriers of short levels).  With fewer
+// micrographs one workgroup's chain of reads is the whole time, and a thread per slot, no barriers between, is shorter.
+// us, sampling call alone, slot by slot / this with 256 / 128 / 64 threads:
+//   16384 x 10,10,10 (chung_lu, 20 M vertices)   128 / 125 / 95 / 94      4096 x 10,10,10 (100 M)   35 / 33 / 30 / 31
+//    4096 x 25,10 (rmat, 16 M)                    13.5 / 16.0 / 12.8 / 11.3     1024 x 15,10,5 (2.4 M)   11.9 / 13.3 / 15.6 / 18.9
+// (with marks, 4096 x 10,10,10: 63 / 53).
+constexpr int kLdsMaxParents = 512, kLdsMaxDraws = 4096, kLdsThreads = 128, kLdsMinMicrographs = 2048;
+
+template <typename OffT>
+__global__ void __launch_bounds__(kLdsThreads)
+sample_micrographs_lds(const OffT* __restrict__ offsets, const int32_t* __restrict__ indices,
+                       const int32_t* __restrict__ seeds, int32_t n_seeds, SampleShape sh, LdsShape ls, BatchKeys keys,
+                       int32_t* __restrict__ ids, int32_t* __restrict__ indptr, int32_t* __restrict__ slot_idx,
+                       int64_t slot_idx_stride, uint8_t* __restrict__ present, int32_t m_offset, int32_t seeds_per_key,
+                       int32_t has_edges) {
+    extern __shared__ __attribute__((aligned(16))) uint8_t lds_raw[];
+    constexpr int NT = kLdsThreads, kLdsRounds = kLdsMaxParents / NT, WAVES = NT / kWave;
+    __shared__ int32_t wave_reps[kLdsRounds][WAVES];
+    DrawParent* parent = reinterpret_cast<DrawParent*>(lds_raw);
+    int32_t* draws = reinterpret_cast<int32_t*>(lds_raw + ls.draws_off);      // [distinct parents][f]
+    int32_t* vert = reinterpret_cast<int32_t*>(lds_raw + ls.vert_off);        // distinct parents
+    uint16_t* rank = reinterpret_cast<uint16_t*>(lds_raw + ls.rank_off);      // parent slot -> distinct parent
+    int32_t* key = reinterpret_cast<int32_t*>(lds_raw + ls.key_off);
+    int32_t* first = reinterpret_cast<int32_t*>(lds_raw + ls.first_off);      // first slot of the key, then its number
+    constexpr uint16_t kNone = 0xFFFF;
+
+    const int32_t m = m_offset + (int32_t)blockIdx.x;
+    const int32_t B = n_seeds;
+    const uint32_t batch = blockIdx.y;
+    const uint64_t keyed = keys.keyed[batch + blockIdx.x / (uint32_t)seeds_per_key];
+    seeds += (int64_t)batch * B;
+    ids += (int64_t)batch * sh.base[sh.n_layers + 1];
+    if (slot_idx != nullptr) slot_idx += (int64_t)batch * slot_idx_stride;
+    if (batch != 0) indptr = nullptr;      // the segment offsets are the same for every batch of one shape
+    const int32_t root = seeds[m];
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+    if (tid == 0) {
+        ids[m] = root;
+        if (present != nullptr && root >= 0) present[root] = 1;   // the pre-gather's presence map
+        if (indptr != nullptr && m == 0) indptr[sh.base[sh.n_layers]] = sh.base[sh.n_layers + 1] - B;
+        vert[0] = root;
+        rank[0] = root >= 0 ? (uint16_t)0 : kNone;
+    }
+    int32_t n_distinct = root >= 0 ? 1 : 0;
+    __syncthreads();
+    for (int32_t h = 1; h <= sh.n_layers; ++h) {
+        const int32_t f = sh.f[h], P = sh.P[h];
+        const uint32_t magic = ls.f_magic[h];
+        auto over_f = [&](int32_t c) -> int32_t { return f == 1 ? c : (int32_t)__umulhi((uint32_t)c, magic); };
+        // A
+        for (int32_t i = tid; i < n_distinct; i += NT) {
+            const int32_t v = vert[i];
+            DrawParent p;
+            p.first = has_edges ? (uint64_t)offsets[v] : 0u;             // no edges: no vertex has a row to read
+            const uint64_t end = has_edges ? (uint64_t)offsets[(int64_t)v + 1] : 0u;
+            p.hashed = finalise64((keyed ^ (((uint64_t)(uint32_t)root << 32) | (uint32_t)v)) + 0x9E3779B97F4A7C15ull);
+            p.degree = (int64_t)end > (int64_t)p.first ? end - p.first : 0u;
+            p.recip = p.degree > 0 ? ~0ull / p.degree : 0u;
+            parent[i] = p;
+        }
+        const bool leaf = h == sh.n_layers;
+        __syncthreads();
+        if (!leaf)      // (behind the barrier: the level before may have been reading its numbers up to there)
+            for (int32_t i = tid; i <= ls.table_mask; i += NT) {
+                key[i] = -1;
+                first[i] = 0x7FFFFFFF;
+            }
+        // B: several draws per thread side by side, unconditional reads from in-bounds addresses
+        const int32_t n_draws = n_distinct * f;
+        auto draw = [&](auto unroll) {
+            constexpr int U = decltype(unroll)::value;
+            for (int32_t t0 = tid; t0 < n_draws; t0 += NT * U) {
+                int32_t child[U];
+                bool some[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int32_t t = t0 + u * NT < n_draws ? t0 + u * NT : t0;
+                    const int32_t q = over_f(t), j = t - q * f;
+                    const DrawParent p = parent[q];
+                    const uint64_t x = finalise64((p.hashed ^ (((uint64_t)(uint32_t)h << 32) | (uint32_t)j)) + 0x9E3779B97F4A7C15ull);
+                    uint64_t r = x - __umul64hi(x, p.recip) * p.degree;
+                    r = r >= p.degree ? r - p.degree : r;
+                    some[u] = p.degree > 0;
+                    child[u] = has_edges ? indices[some[u] ? p.first + r : 0u] : -1;
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int32_t t = t0 + u * NT;
+                    if (t >= n_draws) continue;
+                    if (!some[u]) child[u] = -1;
+                    draws[t] = child[u];
+                    if (present != nullptr && child[u] >= 0) present[child[u]] = 1;
+                }
+            }
+        };
+        if (n_draws > NT) draw(std::integral_constant<int, kSampleUnroll>{});
+        else draw(std::integral_constant<int, 1>{});
+        __syncthreads();
+        // C
+        int32_t* children = ids + sh.base[h] + (int64_t)m * P;
+        const int32_t slot0 = sh.base[h] + m * P, parent0 = sh.base[h - 1] + m * sh.P[h - 1];
+        int32_t q = over_f(tid), j = tid - q * f;      // slot c = q f + j; c advances by NT from call to call
+        const int32_t dq = over_f(NT), dj = NT - dq * f;
+        auto copy_out = [&](int32_t c) -> int32_t {
+            const int32_t i = rank[q];
+            const int32_t child = i != kNone ? draws[i * f + j] : -1;
+            children[c] = child;
+            if (slot_idx != nullptr && !leaf) slot_idx[slot0 + c - B] = child >= 0 ? slot0 + c : -1;   // its own row in later layers
+            if (indptr != nullptr && j == 0) indptr[parent0 + q] = slot0 + c - B;
+            j += dj;
+            q += dq;
+            if (j >= f) {
+                j -= f;
+                ++q;
+            }
+            return child;
+        };
+        if (leaf) {
+            for (int32_t c = tid; c < P; c += NT) copy_out(c);
+            break;
+        }
+        int32_t child[kLdsRounds], at[kLdsRounds];
+#pragma unroll
+        for (int u = 0; u < kLdsRounds; ++u) {
+            child[u] = -1;
+            at[u] = 0;
+            if (u * NT >= P) continue;        // uniform, as below
+            const int32_t c = u * NT + tid;
+            if (c < P) child[u] = copy_out(c);
+            if (child[u] >= 0) {
+                uint32_t s = ((uint32_t)child[u] * 2654435761u) >> 16;
+                for (;; ++s) {                // at most half of the entries are ever taken
+                    s &= (uint32_t)ls.table_mask;
+                    const int32_t was = atomicCAS(&key[s], -1, child[u]);
+                    if (was == -1 || was == child[u]) break;
+                }
+                at[u] = (int32_t)s;
+                atomicMin(&first[s], c);
+            }
+        }
+        __syncthreads();
+        uint64_t reps[kLdsRounds];
+#pragma unroll
+        for (int u = 0; u < kLdsRounds; ++u) {
+            if (u * NT >= P) continue;
+            reps[u] = __ballot(child[u] >= 0 && first[at[u]] == u * NT + tid);
+            if (lane == 0) wave_reps[u][wave] = __popcll(reps[u]);
+        }
+        __syncthreads();
+        int32_t before = 0;
+#pragma unroll
+        for (int u = 0; u < kLdsRounds; ++u) {
+            if (u * NT >= P) continue;
+            int32_t mine = before;
+#pragma unroll
+            for (int w = 0; w < WAVES; ++w) {
+                if (w < wave) mine += wave_reps[u][w];
+                before += wave_reps[u][w];
+            }
+            if ((reps[u] >> lane) & 1ull) {
+                const int32_t n = mine + __popcll(reps[u] & ((1ull << lane) - 1ull));
+                vert[n] = child[u];
+                first[at[u]] = n;
+            }
+        }
+        n_distinct = before;
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < kLdsRounds; ++u) {
+            const int32_t c = u * NT + tid;
+            if (c < P) rank[c] = child[u] >= 0 ? (uint16_t)first[at[u]] : kNone;
+        }
+        // (the next level's first barrier stands between these writes and their readers)
+    }
+}
+
 static uint64_t host_finalise64(uint64_t z) {
     z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
     z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
     return z ^ (z >> 31);
+}
+
+// LDS of sample_micrographs_lds for this shape, or false where a level does not fit: more than 512 slots on the widest
+// non-leaf level (four rounds of the workgroup, their state in registers) or more than 4096 leaves (16 KB; a larger
+// level leaves too few workgroups on a CU to hide its reads): the kernel above takes those.
+static bool lds_shape(const SampleShape& sh, LdsShape& ls) {
+    const int32_t L = sh.n_layers;
+    if (sh.P[L - 1] > kLdsMaxParents || sh.P[L] > kLdsMaxDraws) return false;
+    ls = LdsShape{};
+    ls.n_parents = sh.P[L - 1];
+    int32_t entries = 64;
+    while (entries < 2 * ls.n_parents) entries *= 2;
+    ls.table_mask = entries - 1;
+    int32_t o = ls.n_parents * (int32_t)sizeof(DrawParent);
+    ls.vert_off = o;
+    o += ls.n_parents * 4;
+    // the leaves' draws lie where the hash table was (which stands behind the draws of the levels that need it)
+    ls.draws_off = o;
+    ls.key_off = o + ls.n_parents * 4;
+    ls.first_off = ls.key_off + entries * 4;
+    const int32_t table_end = L > 1 ? ls.first_off + entries * 4 : o, draws_end = o + sh.P[L] * 4;
+    o = table_end > draws_end ? table_end : draws_end;
+    ls.rank_off = o;
+    o += ls.n_parents * 2;
+    ls.bytes = o;
+    for (int32_t h = 1; h <= L; ++h) ls.f_magic[h] = sh.f[h] > 1 ? (uint32_t)((((uint64_t)1 << 32) + sh.f[h] - 1) / sh.f[h]) : 0u;
+    return true;
+}
+
+template <typename OffT>
+static void launch_sample(dim3 grid, int threads, hipStream_t s, const hopgnn_csr* g, const int32_t* seeds, int32_t n_seeds,
+                          const SampleShape& sh, const BatchKeys& keys, int32_t* ids, int32_t* indptr, int32_t* slot_idx,
+                          int64_t slot_idx_stride, uint8_t* present, int32_t m_offset, int32_t seeds_per_key) {
+    const OffT* offsets = static_cast<const OffT*>(g->offsets);
+    const int32_t has_edges = g->n_edges > 0 ? 1 : 0;
+    LdsShape ls;
+    if ((int64_t)grid.x * grid.y >= kLdsMinMicrographs && lds_shape(sh, ls))
+        hipLaunchKernelGGL(sample_micrographs_lds<OffT>, grid, dim3(kLdsThreads), ls.bytes, s, offsets, g->indices, seeds, n_seeds,
+                           sh, ls, keys, ids, indptr, slot_idx, slot_idx_stride, present, m_offset, seeds_per_key, has_edges);
+    else
+        hipLaunchKernelGGL(sample_micrographs<OffT>, grid, dim3(threads), 0, s, offsets, g->indices, seeds, n_seeds, sh, keys,
+                           ids, indptr, slot_idx, slot_idx_stride, present, m_offset, seeds_per_key, has_edges);
 }
 
 }  // namespace hopgnn
@@ -190,14 +434,8 @@ hopgnn_status sample_batches(const hopgnn_csr* g, const int32_t* seeds, int32_t 
         int32_t* ip = b0 == 0 ? indptr : nullptr;
         int32_t* si = slot_idx != nullptr ? slot_idx + (int64_t)b0 * slot_idx_stride : nullptr;
         const dim3 grid((unsigned)n_seeds, (unsigned)nb);
-        if (g->offsets_i64)
-            hipLaunchKernelGGL(sample_micrographs<int64_t>, grid, dim3(threads), 0, s,
-                               static_cast<const int64_t*>(g->offsets), g->indices, sd, n_seeds, sh, bk, id, ip, si,
-                               slot_idx_stride, present, 0, n_seeds, g->n_edges > 0 ? 1 : 0);
-        else
-            hipLaunchKernelGGL(sample_micrographs<int32_t>, grid, dim3(threads), 0, s,
-                               static_cast<const int32_t*>(g->offsets), g->indices, sd, n_seeds, sh, bk, id, ip, si,
-                               slot_idx_stride, present, 0, n_seeds, g->n_edges > 0 ? 1 : 0);
+        (g->offsets_i64 ? launch_sample<int64_t> : launch_sample<int32_t>)(grid, threads, s, g, sd, n_seeds, sh, bk, id, ip, si,
+                                                                           slot_idx_stride, present, 0, n_seeds);
         HOPGNN_LAUNCH_CHECK();
     }
     return HOPGNN_OK;
@@ -236,14 +474,8 @@ hopgnn_status sample_merged(const hopgnn_csr* g, const int32_t* seeds, int32_t n
         const int64_t m0 = (int64_t)k0 * seeds_per_key;
         const int64_t count = (int64_t)nk * seeds_per_key < n_seeds - m0 ? (int64_t)nk * seeds_per_key : n_seeds - m0;
         const dim3 grid((unsigned)count, 1u);
-        if (g->offsets_i64)
-            hipLaunchKernelGGL(sample_micrographs<int64_t>, grid, dim3(threads), 0, s,
-                               static_cast<const int64_t*>(g->offsets), g->indices, seeds, n_seeds, sh, bk, ids, indptr,
-                               slot_idx, (int64_t)0, present, (int32_t)m0, seeds_per_key, g->n_edges > 0 ? 1 : 0);
-        else
-            hipLaunchKernelGGL(sample_micrographs<int32_t>, grid, dim3(threads), 0, s,
-                               static_cast<const int32_t*>(g->offsets), g->indices, seeds, n_seeds, sh, bk, ids, indptr,
-                               slot_idx, (int64_t)0, present, (int32_t)m0, seeds_per_key, g->n_edges > 0 ? 1 : 0);
+        (g->offsets_i64 ? launch_sample<int64_t> : launch_sample<int32_t>)(grid, threads, s, g, seeds, n_seeds, sh, bk, ids, indptr,
+                                                                           slot_idx, 0, present, (int32_t)m0, seeds_per_key);
         HOPGNN_LAUNCH_CHECK();
     }
     return HOPGNN_OK;
