@@ -86,6 +86,45 @@ present_mark(const int32_t* __restrict__ ids, int64_t n_ids, uint8_t* __restrict
     }
 }
 
+// The same marks for large inputs: a workgroup takes a contiguous run of ids and keeps those it has met in a
+// direct-mapped LDS table.  An id found there has been (or is being) marked by this workgroup and needs no store; a
+// lost or overwritten entry only costs a second one.  Ids come in micrograph order and a micrograph repeats its
+// vertices, so most stores go: they, not the reads, are the cost (each one a partial line of an L2, in up to eight L2s).
+// 18.2 M slots, a tenth of them distinct: 130 us with every store, 72 so; whole call 61 -> 56 us at 4.6 M slots, 51 -> 49.5
+// at 2.3 M (distinct ids, uniform graph: 51 -> 49.6), 47.1 -> 47.3 at 1.1 M, 32 -> 35 at 0.6 M.
+constexpr int kMarkTable = 4096;
+constexpr int64_t kMarkMinIds = 2000000;
+constexpr int64_t kMarkRun = 8192;           // shortest run of ids per workgroup
+template <int W>      // ids per load: 4 (16-byte aligned ids) or 1
+__global__ void __launch_bounds__(kPgThreads)
+present_mark_runs(const int32_t* __restrict__ ids, int64_t n_ids, int64_t run, uint8_t* __restrict__ present) {
+    __shared__ int32_t met[kMarkTable];
+    for (int i = threadIdx.x; i < kMarkTable; i += kPgThreads) met[i] = -1;
+    __syncthreads();
+    const int64_t i0 = (int64_t)blockIdx.x * run, i1 = i0 + run < n_ids ? i0 + run : n_ids;
+    auto mark = [&](int32_t v) {
+        if (v < 0) return;
+        const uint32_t s = ((uint32_t)v * 2654435761u) >> 20;
+        if (met[s] == v) return;
+        met[s] = v;
+        present[v] = 1;
+    };
+    static_assert(kMarkTable == 1 << 12, "the hash keeps 12 bits");
+    if (W == 4) {      // run is a multiple of 4
+        int64_t i = i0 + 4 * threadIdx.x;
+        for (; i + 3 < i1; i += 4 * kPgThreads) {
+            const int4 v = *reinterpret_cast<const int4*>(ids + i);
+            mark(v.x);
+            mark(v.y);
+            mark(v.z);
+            mark(v.w);
+        }
+        for (; i < i1; ++i) mark(ids[i]);      // of one thread: the rest of the last run
+    } else {
+        for (int64_t i = i0 + threadIdx.x; i < i1; i += kPgThreads) mark(ids[i]);
+    }
+}
+
 // 4 presence bytes (each 0 or 1) -> 4 bits: byte k lands on bit 24+k of x * 0x01020408.
 __device__ __forceinline__ uint32_t pack4(uint32_t x) { return ((x * 0x01020408u) >> 24) & 0xFu; }
 __device__ __forceinline__ uint32_t pack16(const uint4& q) {
@@ -238,7 +277,8 @@ bitmap_scan_sums(uint32_t* __restrict__ block_sum, uint32_t n_blocks, int64_t* _
 
 // Pass 2, one launch for both outputs.  Workgroups [0, n_emit_blocks) walk one chunk of the
 // bitmap each and write its set bits to uniq in word order; the others fill remap for a strided
-// share of the slots.
+// share of the slots, W slots at a time (4: 16-byte aligned ids and remap).
+template <int W>
 __global__ void __launch_bounds__(kPgThreads)
 bitmap_emit_remap(const uint2* __restrict__ word_rank, const uint32_t* __restrict__ block_base,
                   uint32_t n_emit_blocks, int32_t* __restrict__ uniq, const int32_t* __restrict__ ids, int64_t n_ids,
@@ -264,15 +304,22 @@ bitmap_emit_remap(const uint2* __restrict__ word_rank, const uint32_t* __restric
         }
         return;
     }
+    auto place = [&](int32_t v) -> int32_t {
+        if (v < 0) return -1;
+        const uint2 wr = word_rank[v >> 5];
+        return (int32_t)(block_base[v >> 15] + wr.y + __popc(wr.x & ((1u << (v & 31)) - 1u)));
+    };
     const int64_t stride = (int64_t)(gridDim.x - n_emit_blocks) * blockDim.x;
-    for (int64_t i = (int64_t)(blockIdx.x - n_emit_blocks) * blockDim.x + threadIdx.x; i < n_ids; i += stride) {
-        const int32_t v = ids[i];
-        int32_t pos = -1;
-        if (v >= 0) {
-            const uint2 wr = word_rank[v >> 5];
-            pos = (int32_t)(block_base[v >> 15] + wr.y + __popc(wr.x & ((1u << (v & 31)) - 1u)));
+    const int64_t i0 = (int64_t)(blockIdx.x - n_emit_blocks) * blockDim.x + threadIdx.x;
+    if (W == 4) {
+        const int64_t n4 = n_ids / 4;
+        for (int64_t i = i0; i < n4; i += stride) {
+            const int4 v = reinterpret_cast<const int4*>(ids)[i];
+            reinterpret_cast<int4*>(remap)[i] = make_int4(place(v.x), place(v.y), place(v.z), place(v.w));
         }
-        remap[i] = pos;
+        if (i0 < n_ids - 4 * n4) remap[4 * n4 + i0] = place(ids[4 * n4 + i0]);
+    } else {
+        for (int64_t i = i0; i < n_ids; i += stride) remap[i] = place(ids[i]);
     }
 }
 
@@ -297,8 +344,11 @@ static hopgnn_status bitmap_from_marks(const BitmapWs& L, bool unmark, const int
                            n_uniq_dev);
         HOPGNN_LAUNCH_CHECK();
     }
-    const unsigned remap_blocks = n_ids > 0 ? (unsigned)grid_for(n_ids, kPgThreads, 256 * 32) : 0u;
-    hipLaunchKernelGGL(bitmap_emit_remap, dim3((unsigned)L.n_blocks + remap_blocks), dim3(kPgThreads), 0, s, L.word_rank,
+    // four slots to a thread where that leaves 16 workgroups to a CU (us, one / four: 18.2 M slots 64 / 57, 4.6 M
+    // 27.9 / 24.9; 1.1 M 9.8 / 12.0: the reads of the ranks want wavefronts)
+    const bool wide = n_ids >= (int64_t)256 * 16 * kPgThreads * 4 && aligned(ids, 16) && aligned(remap, 16);
+    const unsigned remap_blocks = n_ids > 0 ? (unsigned)grid_for(n_ids, kPgThreads * (wide ? 4 : 1), 256 * 32) : 0u;
+    hipLaunchKernelGGL((wide ? bitmap_emit_remap<4> : bitmap_emit_remap<1>), dim3((unsigned)L.n_blocks + remap_blocks), dim3(kPgThreads), 0, s, L.word_rank,
                        L.block_sum, (uint32_t)L.n_blocks, uniq, ids, n_ids, remap);
     HOPGNN_LAUNCH_CHECK();
     return HOPGNN_OK;
@@ -313,7 +363,13 @@ static hopgnn_status pregather_bitmap(const int32_t* ids, int64_t n_ids, int64_t
     hipLaunchKernelGGL(present_clear, dim3(grid_for(n_vec, kPgThreads, 256 * 16)), dim3(kPgThreads), 0, s,
                        reinterpret_cast<uint4*>(L.present), n_vec, L.ticket, n_uniq_dev);
     HOPGNN_LAUNCH_CHECK();
-    if (n_ids > 0) {
+    if (n_ids >= kMarkMinIds) {
+        int64_t run = ceil_div(n_ids, 256 * 8);                // 8 workgroups to a CU
+        run = run < kMarkRun ? kMarkRun : (run + 3) / 4 * 4;
+        hipLaunchKernelGGL((aligned(ids, 16) ? present_mark_runs<4> : present_mark_runs<1>), dim3((unsigned)ceil_div(n_ids, run)),
+                           dim3(kPgThreads), 0, s, ids, n_ids, run, L.present);
+        HOPGNN_LAUNCH_CHECK();
+    } else if (n_ids > 0) {
         hipLaunchKernelGGL(present_mark, dim3(grid_for(n_ids, kPgThreads, 256 * 32)), dim3(kPgThreads), 0, s,
                            ids, n_ids, L.present);
         HOPGNN_LAUNCH_CHECK();
