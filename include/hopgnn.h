@@ -660,7 +660,10 @@ hopgnn_status hopgnn_sage_bwd_dev(const void *Hsrc, hopgnn_dtype dt, int64_t n_s
  *                               hands layer k+1 its neighbour means; layers >= 2 then run no
  *                               aggregation kernel, and the rows of layer k's deepest level - which
  *                               layer k+1 reads through those means only - are never written (H[k]
- *                               holds the rows of layer k+1's destinations).  Same last-layer bits as
+ *                               holds the rows of layer k+1's destinations).  Where the layers are large
+ *                               and the mean degree lets vertices repeat, the deepest level's rows are
+ *                               taken once per distinct vertex of a micrograph (equal vertices on one
+ *                               level of one micrograph have equal rows).  Same last-layer bits as
  *                               without the flag.  tree_ws: scratch of hopgnn_batch_tree_ws_bytes(plan)
  *                               (transposed weights, a zero row, two mean buffers), 256-byte aligned,
  *                               filled by hopgnn_batch_prepare(plan) once and again whenever the

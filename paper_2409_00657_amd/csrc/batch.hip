@@ -4,6 +4,8 @@
 // the library's own entry points.
 #include <hip/hip_runtime.h>
 
+#include <cmath>
+
 #include "pregather_internal.hpp"
 #include "sage_common.hpp"
 
@@ -18,7 +20,43 @@ struct TreeWs {
     size_t wt_off[kMaxLayers], zero_off, zero_bytes, mean_off[2], total;
     int32_t KP[kMaxLayers], NP[kMaxLayers];
     bool ok;
+    // Layers 1 .. n_distinct take the rows of their deepest level (level L - k of layer k) once per distinct vertex of a
+    // micrograph.  Per level: what the sampler says about it (DistinctOut) and the lists made from that (DistinctList),
+    // for a whole group; then, of one run, the source row of every destination row, and the distinct rows themselves
+    // (consecutive layers alternate between two buffers).
+    int32_t n_distinct;
+    size_t rank_off[kMaxLayers], slot_off[kMaxLayers], count_off[kMaxLayers], pre_off[kMaxLayers], list_off[kMaxLayers];
+    size_t self_off, rows_off[2];
 };
+
+// How many layers that is.  Only the device knows how many vertices repeat; expected from the mean degree d: f draws with
+// replacement from d neighbours leave d (1 - (1 - 1/d)^f) of them, level by level.  That is what uniform graphs show;
+// skewed ones repeat two to three times more (1024 x 15,10,5, chung_lu of degree 26: expected 0.65, found 0.45).  What is
+// saved, (1 - share) of the layer's products, has to pay for the lists, one more mean kernel and rows that are written
+// and read again; later layers share the lists.  Whole passes, us, every slot / distinct rows (saved products, 1e9):
+//   fp32    chung_lu 15,10,5 100-256 (2.8)  356 / 286    rmat 10,8,5 128-256 (2.1)  196 / 133    uniform, the same (2.1)
+//           259 / 254    uniform 10,8,5 128-128 (1.0)  184 / 197    uniform, degree 30, 10,8,5 128-256 (1.2)  280 / 299
+//   2-byte  rmat 25,10 256-256 (4.0)  157 / 129    chung_lu 8 x 10,10,10 128-512 (27)  662 / 455    rmat 10,8,5 256-256 (4.2)
+//           122 / 100    uniform, the same (4.2)  177 / 182    uniform, degree 30, the same (2.5)  205 / 221
+int32_t distinct_layers(const hopgnn_batch_plan* p) {
+    const int32_t L = p->n_layers, runs = p->merge_layers ? 1 : p->group;
+    if (!sample_gives_distinct(p->fanouts, L) || p->graph.n_vertices < 1) return 0;
+    double d = (double)p->graph.n_edges / (double)p->graph.n_vertices;
+    if (d < 1.0) d = 1.0;
+    int32_t n = 0;
+    for (int32_t k = 1; k < L && (int64_t)k * runs <= kMaxDistinctLists; ++k) {
+        double share = 1.0, slots = (double)p->n_seeds * (p->merge_layers ? p->group : 1);
+        for (int32_t h = 0; h < L - k; ++h) {
+            const double f = p->fanouts[h];
+            share *= d * (1.0 - pow(1.0 - 1.0 / d, f)) / f;
+            slots *= f;
+        }
+        const double work = slots * 2.0 * (k == 1 ? p->dim : p->d_out[k - 2]) * p->d_out[k - 1];
+        if ((1.0 - share) * work * (k == 1 ? 1.0 : 5.0) < (p->dt == HOPGNN_F32 ? 2e9 : 3.5e9)) break;
+        n = k;
+    }
+    return n;
+}
 
 bool tree_applies(const hopgnn_batch_plan* p) {
     const int32_t L = p->n_layers;
@@ -64,6 +102,32 @@ TreeWs tree_ws_layout(const hopgnn_batch_plan* p) {
     o += mean_bytes[0];
     W.mean_off[1] = o;
     o += mean_bytes[1];
+    W.n_distinct = distinct_layers(p);
+    if (W.n_distinct > 0) {
+        const int64_t mics = (int64_t)B * p->group, runs = p->group / scale;
+        auto take = [&](int64_t bytes) {
+            const size_t at = o;
+            o += align_up((size_t)bytes, 256);
+            return at;
+        };
+        size_t rows_bytes[2] = {0, 0};
+        for (int32_t k = 1; k <= W.n_distinct; ++k) {
+            const int32_t h = L - k;
+            const int64_t slots = level[h] / scale * p->group;      // of the whole group
+            W.rank_off[h] = take(slots * 2);
+            W.slot_off[h] = take(slots * 2);
+            W.count_off[h] = take(mics * 4);
+            W.pre_off[h] = take((mics + runs) * 4);
+            W.list_off[h] = take(slots * 4);
+            const size_t rb = (size_t)level[h] * p->d_out[k - 1] * es;
+            if (rb > rows_bytes[k & 1]) rows_bytes[k & 1] = rb;
+        }
+        int64_t n_dst = 0;
+        for (int h = 0; h < L; ++h) n_dst += level[h];
+        W.self_off = take(n_dst * 4);
+        W.rows_off[0] = take((int64_t)rows_bytes[0]);
+        W.rows_off[1] = take((int64_t)rows_bytes[1]);
+    }
     W.total = o;
     return W;
 }
@@ -228,17 +292,42 @@ extern "C" hopgnn_status hopgnn_batch_fwd(const hopgnn_batch_plan* p, const int3
     uint8_t* marks = p->pg_ws_clean ? pregather_marks_map(p->pg_ws, p->pg_ws_bytes, (int64_t)p->group * T,
                                                           p->graph.n_vertices, p->pg_algo)
                                     : nullptr;
+    const TreeWs TW = tree_ws_layout(p);
+    char* tws = static_cast<char*>(p->tree_ws);
+    const int32_t nd = TW.ok ? TW.n_distinct : 0;
+    DistinctOut dist{};
+    DistinctLists lists{};
+    auto list_of = [&](int32_t h, int32_t run) -> DistinctList {      // of level h
+        const int64_t m0 = (int64_t)run * B_run, P = level[h] / B;
+        return DistinctList{dist.count[h] + m0, dist.slot[h] + m0 * P, reinterpret_cast<int32_t*>(tws + TW.pre_off[h]) + run * (int64_t)(B_run + 1),
+                            reinterpret_cast<int32_t*>(tws + TW.list_off[h]) + m0 * P, (int32_t)P};
+    };
+    if (TW.ok) {
+        if (p->tree_ws == nullptr || !aligned(p->tree_ws, 256)) return HOPGNN_EINVAL;
+        if (p->tree_ws_bytes < TW.total) return HOPGNN_ENOMEM_WS;
+        if (mstage >= HOPGNN_MARK_AGGREGATE + 2 && mstage < HOPGNN_MARK_PROJECT) return HOPGNN_EINVAL;   // no such kernel
+        lists.micrographs = B_run;
+        for (int32_t k = 1; k <= nd; ++k) {
+            const int32_t h = L - k;
+            dist.rank[h] = reinterpret_cast<uint16_t*>(tws + TW.rank_off[h]);
+            dist.slot[h] = reinterpret_cast<uint16_t*>(tws + TW.slot_off[h]);
+            dist.count[h] = reinterpret_cast<int32_t*>(tws + TW.count_off[h]);
+            for (int32_t b = 0; b < n_runs; ++b) lists.at[lists.n++] = list_of(h, b);
+        }
+    }
     if (!rec(HOPGNN_MARK_SAMPLE, true)) return HOPGNN_EHIP;
     hopgnn_status rc =
         merged ? sample_merged(&p->graph, seeds, B_run, B, p->fanouts, L, keys, p->ids, p->indptr,
-                               L > 1 ? p->slot_idx : nullptr, marks, stream)
+                               L > 1 ? p->slot_idx : nullptr, marks, stream, dist)
                : sample_batches(&p->graph, seeds, B, p->fanouts, L, keys, n_batches, p->ids, p->indptr,
-                                L > 1 ? p->slot_idx : nullptr, slot_idx_stride, marks, stream);
+                                L > 1 ? p->slot_idx : nullptr, slot_idx_stride, marks, stream, dist);
     if (rc != HOPGNN_OK) return rc;
     if (!rec(HOPGNN_MARK_SAMPLE, false) || !rec(HOPGNN_MARK_PREGATHER, true)) return HOPGNN_EHIP;
     if (marks != nullptr)
         rc = pregather_from_marks(p->ids, n_batches * T, p->graph.n_vertices, p->uniq, p->n_uniq, p->remap, p->pg_ws,
-                                  p->pg_ws_bytes, st);
+                                  p->pg_ws_bytes, st, lists);
+    else if (lists.n > 0 && (rc = launch_distinct_lists(lists, st)) != HOPGNN_OK)
+        return rc;
     else
         rc = hopgnn_pregather(p->ids, n_batches * T, p->graph.n_vertices, p->pg_algo, p->uniq, p->n_uniq, p->remap,
                               p->pg_ws, p->pg_ws_bytes, stream);
@@ -252,18 +341,16 @@ extern "C" hopgnn_status hopgnn_batch_fwd(const hopgnn_batch_plan* p, const int3
 
     const int32_t d_last = p->d_out[L - 1];
     const int64_t rows_scale = merged ? n_batches : 1;         // level sizes of one run = B_run / B times a batch's
-    const TreeWs TW = tree_ws_layout(p);
     if (TW.ok) {
         // The slot tree's shape leaves work out: see fuse_tree in the header.  Layer 1 aggregates with the
         // segmented-mean kernel (its neighbours are scattered rows of Xu); every projection but the last
-        // also writes the next layer's neighbour means and skips the rows only those means read.
-        if (p->tree_ws == nullptr || !aligned(p->tree_ws, 256)) return HOPGNN_EINVAL;
-        if (p->tree_ws_bytes < TW.total) return HOPGNN_ENOMEM_WS;
-        if (mstage >= HOPGNN_MARK_AGGREGATE + 2 && mstage < HOPGNN_MARK_PROJECT) return HOPGNN_EINVAL;   // no such kernel
-        char* tws = static_cast<char*>(p->tree_ws);
+        // also writes the next layer's neighbour means and skips the rows only those means read.  A layer that takes
+        // its deepest rows once per distinct vertex writes those, densely, to scratch instead; its means and the
+        // next layer's then come from the kernel that finds rows through the sampler's numbers.
         const void* zero = tws + TW.zero_off;
         for (int32_t b = 0; b < n_runs; ++b) {
             const int32_t* rb = p->remap + b * T;
+            const int32_t* ids = p->ids + (merged ? 0 : (int64_t)b * T);
             const void* src = p->Xu;
             int64_t n_src = p->uniq_capacity;
             int32_t d_in = p->dim;
@@ -275,27 +362,66 @@ extern "C" hopgnn_status hopgnn_batch_fwd(const hopgnn_batch_plan* p, const int3
                 void* mean = tws + TW.mean_off[(k - 1) & 1];
                 const uint16_t* Wt = reinterpret_cast<const uint16_t*>(tws + TW.wt_off[k - 1]);
                 const bool mk = b == 0 && k == mark_layer;
-                if (k == 1) {
-                    if (mk && mark_agg && hipEventRecord(ev_a, st) != hipSuccess) return HOPGNN_EHIP;
+                if (mk && mark_agg && k == 1 && hipEventRecord(ev_a, st) != hipSuccess) return HOPGNN_EHIP;
+                if (nd > 0 && k <= nd + 1) {
+                    TreeMeans tm{};
+                    tm.n_levels = L - k + 1;
+                    int64_t row = 0;
+                    for (int h = 0; h <= tm.n_levels; ++h) {
+                        tm.row0[h] = row;
+                        tm.f[h] = h ? p->fanouts[h - 1] : 1;
+                        row += level[h] * rows_scale;
+                    }
+                    tm.P_own = (int32_t)(level[L - k] / B);
+                    tm.self_out = reinterpret_cast<int32_t*>(tws + TW.self_off);
+                    if (k <= nd) {
+                        const DistinctList own = list_of(L - k, b);
+                        tm.list = own.list;
+                        tm.n_list = own.off + B_run;
+                    }
+                    if (k == 1) {
+                        tm.slot_row = rb;
+                    } else {
+                        const DistinctList below = list_of(L - k + 1, b);
+                        tm.ids = ids;
+                        tm.rank = dist.rank[L - k + 1] + (int64_t)b * B_run * below.P;
+                        tm.off = below.off;
+                        tm.rows = tws + TW.rows_off[(k - 1) & 1];
+                    }
+                    rc = launch_tree_means(p->dt, src, tm, n_dst, d_in, mean, k == 1 ? tws + TW.zero_off : nullptr,
+                                           k == 1 ? TW.zero_bytes : 0, st);
+                    if (rc != HOPGNN_OK) return rc;
+                } else if (k == 1) {
                     const AggSpec spec{nullptr, 0, kAggOpMean};
                     void* zr = const_cast<void*>(zero);
                     if (p->dt == HOPGNN_F32) rc = launch_mean<TrF32>(src, p->indptr, rb + B_run, n_dst, d_in, mean, zr, TW.zero_bytes, TransposeJob{}, 0, st, spec, nullptr);
                     else if (p->dt == HOPGNN_BF16) rc = launch_mean<TrBF16>(src, p->indptr, rb + B_run, n_dst, d_in, mean, zr, TW.zero_bytes, TransposeJob{}, 0, st, spec, nullptr);
                     else rc = launch_mean<TrF16>(src, p->indptr, rb + B_run, n_dst, d_in, mean, zr, TW.zero_bytes, TransposeJob{}, 0, st, spec, nullptr);
                     if (rc != HOPGNN_OK) return rc;
-                    if (mk && mark_agg && hipEventRecord(ev_b, st) != hipSuccess) return HOPGNN_EHIP;
                 }
+                if (mk && mark_agg && k == 1 && hipEventRecord(ev_b, st) != hipSuccess) return HOPGNN_EHIP;
                 TreeLayer tree{};
-                tree.n_levels = L - k + 1;
-                for (int h = 0; h < tree.n_levels; ++h) {
-                    tree.level_rows[h] = level[h] * rows_scale;
-                    tree.fan[h] = h ? p->fanouts[h - 1] : 1;
-                }
-                tree.ids = p->ids + (merged ? 0 : (int64_t)b * T);
-                tree.mean_next = tws + TW.mean_off[k & 1];
+                tree.ids = ids;
                 tree.n_src = n_src;
+                const int32_t* self_rows = k == 1 ? rb : nullptr;
+                if (k <= nd) {      // two stretches of rows: the slots above, the distinct rows
+                    tree.n_levels = 2;
+                    tree.level_rows[1] = level[L - k] * rows_scale;
+                    tree.level_rows[0] = n_dst - tree.level_rows[1];
+                    tree.fan[1] = 1;
+                    tree.last_rows = list_of(L - k, b).off + B_run;
+                    tree.last_out = tws + TW.rows_off[k & 1];
+                    self_rows = reinterpret_cast<const int32_t*>(tws + TW.self_off);
+                } else {
+                    tree.n_levels = L - k + 1;
+                    for (int h = 0; h < tree.n_levels; ++h) {
+                        tree.level_rows[h] = level[h] * rows_scale;
+                        tree.fan[h] = h ? p->fanouts[h - 1] : 1;
+                    }
+                    tree.mean_next = tws + TW.mean_off[k & 1];
+                }
                 if (mk && !mark_agg && hipEventRecord(ev_a, st) != hipSuccess) return HOPGNN_EHIP;
-                rc = project_dispatch(p->dt, st, src, k == 1 ? rb : nullptr, mean, p->W_self[k - 1], p->W_neigh[k - 1], Wt,
+                rc = project_dispatch(p->dt, st, src, self_rows, mean, p->W_self[k - 1], p->W_neigh[k - 1], Wt,
                                       TW.KP[k - 1], p->bias[k - 1], n_dst, d_in, 2 * d_in, p->d_out[k - 1], k < L ? 1 : 0,
                                       zero, dst, 0, nullptr, k < L ? &tree : nullptr, true);
                 if (rc != HOPGNN_OK) return rc;

@@ -162,6 +162,59 @@ __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t x, uint32_t* l
     return base + inc - x;
 }
 
+// The prefix sums of one list, by one workgroup.
+__device__ __forceinline__ void distinct_scan(const DistinctList& l, int32_t micrographs, uint32_t* lds4) {
+    uint32_t carry = 0;
+    for (int32_t i0 = 0; i0 < micrographs; i0 += kPgThreads * 4) {      // four neighbouring counts to a thread
+        uint32_t c[4], sum = 0;
+        const int32_t i = i0 + threadIdx.x * 4;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            c[k] = i + k < micrographs ? (uint32_t)l.count[i + k] : 0u;
+            sum += c[k];
+        }
+        uint32_t total;
+        uint32_t at = carry + block_exclusive_scan(sum, lds4, total);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            if (i + k < micrographs) l.off[i + k] = (int32_t)at;
+            at += c[k];
+        }
+        carry += total;
+    }
+    if (threadIdx.x == 0) l.off[micrographs] = (int32_t)carry;
+}
+
+// ... and its slots, a strided share of them.
+__device__ __forceinline__ void distinct_fill(const DistinctList& l, int32_t micrographs, uint32_t first, uint32_t stride) {
+    const uint32_t n = (uint32_t)micrographs * (uint32_t)l.P;
+    for (uint32_t t = first; t < n; t += stride) {
+        const uint32_t m = t / (uint32_t)l.P, k = t - m * (uint32_t)l.P;
+        if ((int32_t)k < l.count[m]) l.list[l.off[m] + (int32_t)k] = (int32_t)(m * (uint32_t)l.P + l.slot[t]);
+    }
+}
+
+// Workgroups that fill the lists, the same number for each (in a launch's order: list by list).
+static uint32_t fill_blocks(const DistinctLists& d) {
+    int64_t most = 0;
+    for (int32_t i = 0; i < d.n; ++i) most = d.at[i].P > most ? d.at[i].P : most;
+    const int64_t want = ceil_div(most * d.micrographs, 2 * kPgThreads);
+    return (uint32_t)(want < 1024 ? want : 1024);
+}
+__device__ __forceinline__ void distinct_fill(const DistinctLists& d, uint32_t block, uint32_t per_list) {
+    distinct_fill(d.at[block / per_list], d.micrographs, (block % per_list) * kPgThreads + threadIdx.x, per_list * kPgThreads);
+}
+
+__global__ void __launch_bounds__(kPgThreads)
+distinct_scan_lists(DistinctLists d) {
+    __shared__ uint32_t lds4[kPgThreads / kWave];
+    distinct_scan(d.at[blockIdx.x], d.micrographs, lds4);
+}
+__global__ void __launch_bounds__(kPgThreads)
+distinct_fill_lists(DistinctLists d, uint32_t per_list) {
+    distinct_fill(d, blockIdx.x, per_list);
+}
+
 // Pass 1: pack the presence bytes into bitmap words, rank every word inside its 1024-word chunk
 // and count the chunk; the workgroup that finishes last turns the chunk counts into exclusive
 // chunk bases and publishes U.  With UNMARK the marks are wiped as they are read (only the
@@ -170,9 +223,13 @@ __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t x, uint32_t* l
 template <bool UNMARK, bool TICKET>
 __global__ void __launch_bounds__(kPgThreads)
 bitmap_pack_count(uint4* __restrict__ present16, uint2* __restrict__ word_rank, uint32_t* block_sum,
-                  uint32_t* ticket, int64_t* n_uniq, uint32_t n_blocks) {
+                  uint32_t* ticket, int64_t* n_uniq, uint32_t n_blocks, uint32_t grid, DistinctLists lists) {
     __shared__ uint32_t lds4[kPgThreads / kWave];
     __shared__ bool is_last;
+    if (blockIdx.x >= grid) {      // workgroups behind the pass's own: the lists' prefix sums
+        distinct_scan(lists.at[blockIdx.x - grid], lists.micrographs, lds4);
+        return;
+    }
     // A wave covers 8 KiB of presence bytes = 256 bitmap words.  Load k of lane l is the
     // 16-byte piece k*64+l of that range (fully coalesced) = one half of word k*32 + l/2;
     // lanes 2j and 2j+1 exchange halves and the even lane owns the word.
@@ -180,7 +237,7 @@ bitmap_pack_count(uint4* __restrict__ present16, uint2* __restrict__ word_rank, 
     // end (one ticket per chunk serialised thousands of same-address atomics on large graphs).
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = threadIdx.x / kWave;
-    for (uint32_t chunk = blockIdx.x; chunk < n_blocks; chunk += gridDim.x) {
+    for (uint32_t chunk = blockIdx.x; chunk < n_blocks; chunk += grid) {
         const int64_t wave_id = (int64_t)chunk * (kPgThreads / kWave) + wave;
         uint4* src = present16 + wave_id * (kWave * 8);
         uint2* dst = word_rank + wave_id * (kWave * kWordsPerThread);
@@ -231,7 +288,7 @@ bitmap_pack_count(uint4* __restrict__ present16, uint2* __restrict__ word_rank, 
     if (!TICKET) return;      // the chunk counts are scanned by a launch of their own
     if (threadIdx.x == 0) {
         __threadfence();
-        is_last = atomicAdd(ticket, 1u) == gridDim.x - 1;
+        is_last = atomicAdd(ticket, 1u) == grid - 1;
     }
     __syncthreads();
     if (!is_last) return;
@@ -282,15 +339,20 @@ template <int W>
 __global__ void __launch_bounds__(kPgThreads)
 bitmap_emit_remap(const uint2* __restrict__ word_rank, const uint32_t* __restrict__ block_base,
                   uint32_t n_emit_blocks, int32_t* __restrict__ uniq, const int32_t* __restrict__ ids, int64_t n_ids,
-                  int32_t* __restrict__ remap) {
-    if (blockIdx.x < n_emit_blocks) {
-        const int64_t t = (int64_t)blockIdx.x * kPgThreads + threadIdx.x;
+                  int32_t* __restrict__ remap, uint32_t n_fill, uint32_t fill_per_list, DistinctLists lists) {
+    if (blockIdx.x < n_fill) {      // workgroups before the pass's own: the lists' slots
+        distinct_fill(lists, blockIdx.x, fill_per_list);
+        return;
+    }
+    const uint32_t block = blockIdx.x - n_fill;
+    if (block < n_emit_blocks) {
+        const int64_t t = (int64_t)block * kPgThreads + threadIdx.x;
         const uint4* wr = reinterpret_cast<const uint4*>(word_rank + t * kWordsPerThread);
         const uint4 a = wr[0], b = wr[1];              // (bits, rank) of words 4t .. 4t+3
         const uint32_t wd[4] = {a.x, a.z, b.x, b.z};
         const uint32_t rk[4] = {a.y, a.w, b.y, b.w};
         if ((wd[0] | wd[1] | wd[2] | wd[3]) == 0u) return;
-        const uint32_t base = block_base[blockIdx.x];
+        const uint32_t base = block_base[block];
 #pragma unroll
         for (int k = 0; k < kWordsPerThread; ++k) {
             uint32_t bits = wd[k];
@@ -309,8 +371,8 @@ bitmap_emit_remap(const uint2* __restrict__ word_rank, const uint32_t* __restric
         const uint2 wr = word_rank[v >> 5];
         return (int32_t)(block_base[v >> 15] + wr.y + __popc(wr.x & ((1u << (v & 31)) - 1u)));
     };
-    const int64_t stride = (int64_t)(gridDim.x - n_emit_blocks) * blockDim.x;
-    const int64_t i0 = (int64_t)(blockIdx.x - n_emit_blocks) * blockDim.x + threadIdx.x;
+    const int64_t stride = (int64_t)(gridDim.x - n_fill - n_emit_blocks) * blockDim.x;
+    const int64_t i0 = (int64_t)(block - n_emit_blocks) * blockDim.x + threadIdx.x;
     if (W == 4) {
         const int64_t n4 = n_ids / 4;
         for (int64_t i = i0; i < n4; i += stride) {
@@ -331,13 +393,14 @@ static int grid_for(int64_t n, int per_block, int cap) {
 
 // Packing pass + the fused second pass, from a presence map that holds the marks of `ids`.
 static hopgnn_status bitmap_from_marks(const BitmapWs& L, bool unmark, const int32_t* ids, int64_t n_ids,
-                                       int32_t* uniq, int64_t* n_uniq_dev, int32_t* remap, hipStream_t s) {
-    const dim3 pack_grid((unsigned)(L.n_blocks < kMaxPackGrid ? L.n_blocks : kMaxPackGrid));
+                                       int32_t* uniq, int64_t* n_uniq_dev, int32_t* remap, hipStream_t s,
+                                       const DistinctLists& lists = DistinctLists{}) {
+    const uint32_t pack_grid = (uint32_t)(L.n_blocks < kMaxPackGrid ? L.n_blocks : kMaxPackGrid);
     const bool ticket = L.n_blocks <= kTicketChunks;
     auto pack = unmark ? (ticket ? bitmap_pack_count<true, true> : bitmap_pack_count<true, false>)
                        : (ticket ? bitmap_pack_count<false, true> : bitmap_pack_count<false, false>);
-    hipLaunchKernelGGL(pack, pack_grid, dim3(kPgThreads), 0, s, reinterpret_cast<uint4*>(L.present), L.word_rank,
-                       L.block_sum, L.ticket, n_uniq_dev, (uint32_t)L.n_blocks);
+    hipLaunchKernelGGL(pack, dim3(pack_grid + (uint32_t)lists.n), dim3(kPgThreads), 0, s, reinterpret_cast<uint4*>(L.present),
+                       L.word_rank, L.block_sum, L.ticket, n_uniq_dev, (uint32_t)L.n_blocks, pack_grid, lists);
     HOPGNN_LAUNCH_CHECK();
     if (!ticket) {
         hipLaunchKernelGGL(bitmap_scan_sums, dim3(1), dim3(kPgThreads), 0, s, L.block_sum, (uint32_t)L.n_blocks,
@@ -348,8 +411,10 @@ static hopgnn_status bitmap_from_marks(const BitmapWs& L, bool unmark, const int
     // 27.9 / 24.9; 1.1 M 9.8 / 12.0: the reads of the ranks want wavefronts)
     const bool wide = n_ids >= (int64_t)256 * 16 * kPgThreads * 4 && aligned(ids, 16) && aligned(remap, 16);
     const unsigned remap_blocks = n_ids > 0 ? (unsigned)grid_for(n_ids, kPgThreads * (wide ? 4 : 1), 256 * 32) : 0u;
-    hipLaunchKernelGGL((wide ? bitmap_emit_remap<4> : bitmap_emit_remap<1>), dim3((unsigned)L.n_blocks + remap_blocks), dim3(kPgThreads), 0, s, L.word_rank,
-                       L.block_sum, (uint32_t)L.n_blocks, uniq, ids, n_ids, remap);
+    const uint32_t per_list = fill_blocks(lists), n_fill = per_list * (uint32_t)lists.n;
+    hipLaunchKernelGGL((wide ? bitmap_emit_remap<4> : bitmap_emit_remap<1>), dim3(n_fill + (unsigned)L.n_blocks + remap_blocks),
+                       dim3(kPgThreads), 0, s, L.word_rank, L.block_sum, (uint32_t)L.n_blocks, uniq, ids, n_ids, remap, n_fill,
+                       per_list, lists);
     HOPGNN_LAUNCH_CHECK();
     return HOPGNN_OK;
 }
@@ -822,13 +887,23 @@ uint8_t* pregather_marks_map(void* ws, size_t ws_bytes, int64_t n_ids, int64_t n
 }
 
 hopgnn_status pregather_from_marks(const int32_t* ids, int64_t n_ids, int64_t n_vertices, int32_t* uniq,
-                                   int64_t* n_uniq_dev, int32_t* remap, void* ws, size_t ws_bytes, hipStream_t s) {
+                                   int64_t* n_uniq_dev, int32_t* remap, void* ws, size_t ws_bytes, hipStream_t s,
+                                   const DistinctLists& lists) {
     if (n_ids < 0 || n_vertices < 0 || n_uniq_dev == nullptr || ws == nullptr) return HOPGNN_EINVAL;
     if (n_ids > 0 && (ids == nullptr || remap == nullptr || uniq == nullptr)) return HOPGNN_EINVAL;
     if (n_ids >= ((int64_t)1 << 31) || n_vertices > ((int64_t)1 << 31)) return HOPGNN_ERANGE;
     const BitmapWs L = bitmap_layout(ws, n_vertices);
     if (ws_bytes < L.bytes) return HOPGNN_ENOMEM_WS;
-    return bitmap_from_marks(L, true, ids, n_ids, uniq, n_uniq_dev, remap, s);
+    return bitmap_from_marks(L, true, ids, n_ids, uniq, n_uniq_dev, remap, s, lists);
+}
+
+hopgnn_status launch_distinct_lists(const DistinctLists& lists, hipStream_t s) {
+    hipLaunchKernelGGL(distinct_scan_lists, dim3((unsigned)lists.n), dim3(kPgThreads), 0, s, lists);
+    HOPGNN_LAUNCH_CHECK();
+    const uint32_t per_list = fill_blocks(lists);
+    hipLaunchKernelGGL(distinct_fill_lists, dim3(per_list * (unsigned)lists.n), dim3(kPgThreads), 0, s, lists, per_list);
+    HOPGNN_LAUNCH_CHECK();
+    return HOPGNN_OK;
 }
 
 }  // namespace hopgnn

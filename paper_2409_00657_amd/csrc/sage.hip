@@ -240,7 +240,12 @@ __device__ __forceinline__ bool tree_tile_rows(const TreeTiles& tt, uint32_t mt,
     tile_in_level = mt - tt.tile0[lvl];
     const int64_t per_tile = lvl == 0 ? (int64_t)BM : (int64_t)tt.g[lvl] * tt.f[lvl];
     row0 = tt.row0[lvl] + (int64_t)tile_in_level * per_tile;
-    const int64_t level_end = tt.row0[lvl] + tt.rows[lvl];
+    int64_t level_end = tt.row0[lvl] + tt.rows[lvl];
+    if (tt.last_rows != nullptr && lvl == tt.n_levels - 1) {
+        const int64_t live = tt.row0[lvl] + *tt.last_rows;
+        level_end = live < level_end ? live : level_end;
+        if (row0 >= level_end) return false;
+    }
     row_end = row0 + per_tile < level_end ? row0 + per_tile : level_end;
     return true;
 }
@@ -269,6 +274,7 @@ __device__ __forceinline__ void tree_epilogue(floatx16 (&acc)[TM][TN], void* lds
     const int n_rows = (int)(row_end - row0);
     const bool make_means = lvl >= 1 && tt.mean_next != nullptr;
     const bool store_rows = lvl < tt.store_levels;
+    if (tt.last_out != nullptr && lvl == tt.n_levels - 1) out = static_cast<T*>(tt.last_out) - tt.row0[lvl] * d_out;
     if (make_means && tid < BM) vld[tid] = my_id >= 0 ? 1 : 0;
 #pragma unroll 1
     for (int c_lo = 0; c_lo < BN; c_lo += PW) {
@@ -1228,6 +1234,123 @@ sage_project_16_walk(const uint16_t* __restrict__ Hsrc, const int32_t* __restric
     }
 }
 
+// ------------------------------------------------ means over distinct rows --
+//
+// Neighbour means of the layers of a slot tree whose deepest rows are taken once per distinct vertex (see TreeMeans).
+// FIRST: the first layer, children are scattered rows named by slot_row.  Otherwise children of the last level are found
+// through their numbers, the others are rows in slot order.  Sum in child order over the valid children, one division,
+// one rounding: the segmented mean's arithmetic.  How many rows there are only the device knows: a grid that fills the
+// chip walks over them (one workgroup per block of the capacity, most of them leaving at once: 88 us against 71 on 45 k +
+// 107 k of 410 k first-layer rows of 10 children, fp16; every slot's row 148).  Bound by the reads of rows from L2 and
+// memory-side cache, later layers by the length of the chain list -> number -> row (16 k rows of 10 children of 1 KB:
+// 48 us).  XCDs take turns at runs of workgroups' rows: see sage_mean_vec.
+template <typename Tr, bool FIRST>
+__global__ void __launch_bounds__(kMeanThreads)
+tree_means(const uint4* __restrict__ H, TreeMeans tm, int32_t words, int32_t group, uint4* __restrict__ Mean,
+           uint32_t* __restrict__ zero_row, int32_t zero_words) {
+    if (blockIdx.x == 0)
+        for (int32_t i = threadIdx.x; i < zero_words; i += kMeanThreads) zero_row[i] = 0u;
+    const int last = tm.n_levels - 1;
+    const int64_t first = tm.row0[last];
+    const int64_t n_rows = first + (tm.list != nullptr ? (int64_t)*tm.n_list : tm.row0[last + 1] - first);
+    constexpr uint32_t run = kMeanXcdRun;
+    constexpr int U = FIRST ? MeanUnroll<Tr>::value : 5;
+    for (uint32_t vb = blockIdx.x;; vb += gridDim.x) {      // gridDim.x is a multiple of 8 run
+        const uint32_t seq = vb >> 3, round = seq / run;
+        if ((int64_t)round * 8 * run * kMeanThreads >= n_rows * group) return;
+        const int64_t lb = ((int64_t)round * 8 + (vb & 7u)) * run + seq % run;
+        const int64_t gid = lb * kMeanThreads + threadIdx.x;
+        const int64_t r = gid / group;
+        const int32_t g = (int32_t)(gid - r * group);
+        if (r >= n_rows) continue;
+        int lvl = 0;
+        while (lvl < last && r >= tm.row0[lvl + 1]) ++lvl;
+        int64_t own = r - tm.row0[lvl];                     // the row's slot, within its level
+        if (lvl == last && tm.list != nullptr) own = tm.list[own];
+        const int32_t f = tm.f[lvl + 1];
+        const int64_t child0 = own * f;                     // its first child, within the next level
+        const bool numbered = !FIRST && lvl == last;
+        const int32_t* names = FIRST ? tm.slot_row + tm.row0[lvl + 1] + child0 : tm.ids + tm.row0[lvl + 1] + child0;
+        const uint16_t* ranks = tm.rank + child0;
+        const uint4* base = H;
+        if (!FIRST) base = numbered ? static_cast<const uint4*>(tm.rows) + (int64_t)tm.off[own / tm.P_own] * words
+                                    : H + (tm.row0[lvl + 1] + child0) * words;
+        if (g == 0) tm.self_out[r] = FIRST ? tm.slot_row[tm.row0[lvl] + own] : (int32_t)(tm.row0[lvl] + own);
+        for (int32_t c = g; c < words; c += group) {
+            float acc[Tr::kPer16];
+#pragma unroll
+            for (int i = 0; i < Tr::kPer16; ++i) acc[i] = 0.f;
+            int32_t cnt = 0;
+            Pack16<Tr> v[U];
+            auto add = [&](const int32_t (&u)[U]) {
+#pragma unroll
+                for (int k = 0; k < U; ++k)
+                    if (u[k] >= 0) {
+#pragma unroll
+                        for (int i = 0; i < Tr::kPer16; ++i) acc[i] = acc[i] + Tr::to_f(v[k].e[i]);
+                        ++cnt;
+                    }
+            };
+            if constexpr (FIRST) {
+                for (int32_t e = 0; e < f; e += U) {
+                    int32_t u[U];
+#pragma unroll
+                    for (int k = 0; k < U; ++k) u[k] = e + k < f ? names[e + k] : -1;
+#pragma unroll
+                    for (int k = 0; k < U; ++k)
+                        if (u[k] >= 0) v[k].v = H[(int64_t)u[k] * words + c];
+                    add(u);
+                }
+            } else {      // few rows and long chains: the next children are asked for before the rows are waited for
+                int32_t u[U], next[U];
+                auto children = [&](int32_t e, int32_t (&n)[U]) {      // rows of children e .. e + U - 1, -1: none
+#pragma unroll
+                    for (int k = 0; k < U; ++k) {
+                        const int32_t i = e + k < f ? e + k : f - 1;
+                        int32_t x = numbered ? (int32_t)ranks[i] : names[i];
+                        if (numbered) x = x != 0xFFFF ? x : -1;
+                        else x = x >= 0 ? i : -1;
+                        n[k] = e + k < f ? x : -1;
+                    }
+                };
+                children(0, u);
+                for (int32_t e = 0; e < f; e += U) {
+#pragma unroll
+                    for (int k = 0; k < U; ++k)
+                        if (u[k] >= 0) v[k].v = base[(int64_t)u[k] * words + c];
+                    if (e + U < f) children(e + U, next);
+                    add(u);
+#pragma unroll
+                    for (int k = 0; k < U; ++k) u[k] = next[k];
+                }
+            }
+            Pack16<Tr> o;
+            const float fc = (float)cnt;
+#pragma unroll
+            for (int i = 0; i < Tr::kPer16; ++i) o.e[i] = Tr::from_f(cnt > 0 ? acc[i] / fc : 0.f);
+            Mean[r * words + c] = o.v;
+        }
+    }
+}
+
+hopgnn_status launch_tree_means(hopgnn_dtype dt, const void* Hsrc, const TreeMeans& tm, int64_t cap_rows, int32_t d, void* mean,
+                                void* zero_row, size_t zero_bytes, hipStream_t s) {
+    const int32_t words = d / (dt == HOPGNN_F32 ? 4 : 8);
+    const int32_t group = words < 64 ? words : 64;
+    constexpr int64_t turn = 8 * kMeanXcdRun;
+    int64_t blocks = ceil_div(ceil_div(cap_rows * group, kMeanThreads), turn) * turn;
+    const bool first = tm.slot_row != nullptr;
+    const int64_t resident = (first ? 16 : 8) * turn;      // 8 or 4 workgroups to a CU: see the launch bounds
+    if (blocks > resident) blocks = resident;
+    auto kern = dt == HOPGNN_F32    ? (first ? tree_means<TrF32, true> : tree_means<TrF32, false>)
+                : dt == HOPGNN_BF16 ? (first ? tree_means<TrBF16, true> : tree_means<TrBF16, false>)
+                                    : (first ? tree_means<TrF16, true> : tree_means<TrF16, false>);
+    hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(kMeanThreads), 0, s, static_cast<const uint4*>(Hsrc), tm, words, group,
+                       static_cast<uint4*>(mean), static_cast<uint32_t*>(zero_row), (int32_t)(zero_bytes / 4));
+    HOPGNN_LAUNCH_CHECK();
+    return HOPGNN_OK;
+}
+
 // ------------------------------------------------------------------ launch --
 
 static uint32_t project_grid(int64_t m_tiles, uint32_t n_tiles_n) {
@@ -1241,6 +1364,8 @@ static int64_t tree_tiles(const TreeLayer& t, int BM, TreeTiles& tt) {
     tt.store_levels = t.mean_next != nullptr ? t.n_levels - 1 : t.n_levels;
     tt.ids = t.ids;
     tt.mean_next = t.mean_next;
+    tt.last_rows = t.last_rows;
+    tt.last_out = t.last_out;
     int64_t row = 0, tiles = 0;
     for (int h = 0; h < t.n_levels; ++h) {
         tt.row0[h] = row;
@@ -1381,7 +1506,9 @@ hopgnn_status project_dispatch(hopgnn_dtype dt, hipStream_t s, const void* Hsrc,
                                int32_t d_out, int relu, const void* zero, void* out, int out_f32,
                                const int64_t* n_rows_dev, const TreeLayer* tree, bool split) {
     const int per16 = dt == HOPGNN_F32 ? 4 : 8;
-    const int64_t work = ceil_div(n_dst, 128) * ceil_div(d_out, 128);   // 128 x 128 output tiles
+    // 128 x 128 output tiles; where only the device knows how many rows of the last level exist, half of them
+    const int64_t rows = tree != nullptr && tree->last_rows != nullptr ? n_dst - tree->level_rows[tree->n_levels - 1] / 2 : n_dst;
+    const int64_t work = ceil_div(rows, 128) * ceil_div(d_out, 128);
     bool vec = d_in % per16 == 0 && aligned(Hsrc, 16) && aligned(mean, 16);
     if (dt == HOPGNN_F32) vec = vec && d_out % per16 == 0 && aligned(W_self, 16) && aligned(W_neigh, 16);
     if (tree != nullptr) {      // the slot-tree kernels are built for the vector path only

@@ -481,6 +481,8 @@ struct TreeTiles {
     int32_t g[kMaxLayers + 1];           // groups per tile on level h
     const int32_t* ids;                  // DEVICE: vertex of every slot (negative = invalid slot, no term of a mean)
     void* mean_next;                     // DEVICE out [slots of levels 0 .. n_levels-2][d_out]; NULL: no means
+    const int32_t* last_rows;            // DEVICE: rows that exist on the last level (at most rows[]); NULL: all of them
+    void* last_out;                      // the last level's rows go here, from its first row on; NULL: to `out` like the rest
 };
 
 // Host description of the same, before a tile height is chosen.
@@ -491,6 +493,8 @@ struct TreeLayer {
     const int32_t* ids;
     void* mean_next;
     int64_t n_src;                       // rows of the layer's source array (bounds what self_idx may name)
+    const int32_t* last_rows;            // as in TreeTiles
+    void* last_out;
 };
 constexpr int kTreeMaxFan = 64;          // a group of siblings must fit the smallest row tile
 
@@ -510,6 +514,31 @@ hopgnn_status project_dispatch(hopgnn_dtype dt, hipStream_t s, const void* Hsrc,
                                int32_t KP, const void* bias, int64_t n_dst, int32_t d_in, int32_t k_total,
                                int32_t d_out, int relu, const void* zero, void* out, int out_f32,
                                const int64_t* n_rows_dev, const TreeLayer* tree = nullptr, bool split = false);
+
+// Slot trees whose deepest rows are taken once per distinct vertex of a micrograph (equal vertices on one level of one
+// micrograph have equal rows): the destination rows of layer k are the slots of levels 0 .. L-k-1 as they are, then the
+// distinct ones of level L-k, densely, in the order of `list`.
+struct TreeMeans {
+    int32_t n_levels;                    // L-k+1
+    int64_t row0[kMaxLayers + 2];        // first slot of level h, h <= n_levels
+    int32_t f[kMaxLayers + 2];           // children per slot of level h-1, h <= n_levels
+    const int32_t* list;                 // DEVICE: slots of the last level, counted within it; NULL: all of them
+    const int32_t* n_list;               // DEVICE: how many
+    int32_t* self_out;                   // DEVICE: source row of every destination row
+    // layer 1: the source row of every slot (negative: none)
+    const int32_t* slot_row;
+    // later layers: source rows are slots of levels < n_levels; the last level's children are found through their
+    // numbers, row `off[micrograph] + rank` of `rows`
+    const int32_t* ids;                  // vertex of every slot
+    const uint16_t* rank;                // 0xFFFF: invalid slot
+    const int32_t* off;
+    const void* rows;
+    int32_t P;                           // children a micrograph
+    int32_t P_own;                       // slots a micrograph on the last level
+};
+// mean[r] for all of them (cap_rows: their largest number), and zero_row cleared if given.
+hopgnn_status launch_tree_means(hopgnn_dtype dt, const void* Hsrc, const TreeMeans& tm, int64_t cap_rows, int32_t d, void* mean,
+                                void* zero_row, size_t zero_bytes, hipStream_t s);
 
 // Writes the transposed, zero-padded weights of one 2-byte layer (job.Wt, see TransposeJob) and
 // clears `zero_row` (zero_bytes, may be 0): what the segmented-mean kernel does as a side job, as

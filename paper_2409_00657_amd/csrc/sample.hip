@@ -160,17 +160,17 @@ struct LdsShape {
 //   16384 x 10,10,10 (chung_lu, 20 M vertices)   128 / 125 / 95 / 94      4096 x 10,10,10 (100 M)   35 / 33 / 30 / 31
 //    4096 x 25,10 (rmat, 16 M)                    13.5 / 16.0 / 12.8 / 11.3     1024 x 15,10,5 (2.4 M)   11.9 / 13.3 / 15.6 / 18.9
 // (with marks, 4096 x 10,10,10: 63 / 53).
-constexpr int kLdsMaxParents = 512, kLdsMaxDraws = 4096, kLdsThreads = 128, kLdsMinMicrographs = 2048;
+constexpr int kLdsMaxParents = 512, kLdsMaxDraws = 4096, kLdsMinMicrographs = 2048;
 
-template <typename OffT>
-__global__ void __launch_bounds__(kLdsThreads)
+template <typename OffT, int NT>
+__global__ void __launch_bounds__(NT)
 sample_micrographs_lds(const OffT* __restrict__ offsets, const int32_t* __restrict__ indices,
                        const int32_t* __restrict__ seeds, int32_t n_seeds, SampleShape sh, LdsShape ls, BatchKeys keys,
                        int32_t* __restrict__ ids, int32_t* __restrict__ indptr, int32_t* __restrict__ slot_idx,
                        int64_t slot_idx_stride, uint8_t* __restrict__ present, int32_t m_offset, int32_t seeds_per_key,
-                       int32_t has_edges) {
+                       int32_t has_edges, DistinctOut distinct) {
     extern __shared__ __attribute__((aligned(16))) uint8_t lds_raw[];
-    constexpr int NT = kLdsThreads, kLdsRounds = kLdsMaxParents / NT, WAVES = NT / kWave;
+    constexpr int kLdsRounds = kLdsMaxParents / NT, WAVES = NT / kWave;
     __shared__ int32_t wave_reps[kLdsRounds][WAVES];
     DrawParent* parent = reinterpret_cast<DrawParent*>(lds_raw);
     int32_t* draws = reinterpret_cast<int32_t*>(lds_raw + ls.draws_off);      // [distinct parents][f]
@@ -189,6 +189,7 @@ sample_micrographs_lds(const OffT* __restrict__ offsets, const int32_t* __restri
     if (slot_idx != nullptr) slot_idx += (int64_t)batch * slot_idx_stride;
     if (batch != 0) indptr = nullptr;      // the segment offsets are the same for every batch of one shape
     const int32_t root = seeds[m];
+    const int64_t mic = (int64_t)batch * B + m;
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
     if (tid == 0) {
         ids[m] = root;
@@ -317,6 +318,7 @@ sample_micrographs_lds(const OffT* __restrict__ offsets, const int32_t* __restri
                 const int32_t n = mine + __popcll(reps[u] & ((1ull << lane) - 1ull));
                 vert[n] = child[u];
                 first[at[u]] = n;
+                if (distinct.rank[h] != nullptr) distinct.slot[h][mic * P + n] = (uint16_t)(u * NT + tid);
             }
         }
         n_distinct = before;
@@ -324,8 +326,11 @@ sample_micrographs_lds(const OffT* __restrict__ offsets, const int32_t* __restri
 #pragma unroll
         for (int u = 0; u < kLdsRounds; ++u) {
             const int32_t c = u * NT + tid;
-            if (c < P) rank[c] = child[u] >= 0 ? (uint16_t)first[at[u]] : kNone;
+            if (c >= P) continue;
+            rank[c] = child[u] >= 0 ? (uint16_t)first[at[u]] : kNone;
+            if (distinct.rank[h] != nullptr) distinct.rank[h][mic * P + c] = rank[c];
         }
+        if (distinct.rank[h] != nullptr && tid == 0) distinct.count[h][mic] = n_distinct;
         // (the next level's first barrier stands between these writes and their readers)
     }
 }
@@ -366,13 +371,16 @@ static bool lds_shape(const SampleShape& sh, LdsShape& ls) {
 template <typename OffT>
 static void launch_sample(dim3 grid, int threads, hipStream_t s, const hopgnn_csr* g, const int32_t* seeds, int32_t n_seeds,
                           const SampleShape& sh, const BatchKeys& keys, int32_t* ids, int32_t* indptr, int32_t* slot_idx,
-                          int64_t slot_idx_stride, uint8_t* present, int32_t m_offset, int32_t seeds_per_key) {
+                          int64_t slot_idx_stride, uint8_t* present, int32_t m_offset, int32_t seeds_per_key,
+                          const DistinctOut& distinct) {
     const OffT* offsets = static_cast<const OffT*>(g->offsets);
     const int32_t has_edges = g->n_edges > 0 ? 1 : 0;
     LdsShape ls;
-    if ((int64_t)grid.x * grid.y >= kLdsMinMicrographs && lds_shape(sh, ls))
-        hipLaunchKernelGGL(sample_micrographs_lds<OffT>, grid, dim3(kLdsThreads), ls.bytes, s, offsets, g->indices, seeds, n_seeds,
-                           sh, ls, keys, ids, indptr, slot_idx, slot_idx_stride, present, m_offset, seeds_per_key, has_edges);
+    const bool many = (int64_t)grid.x * grid.y >= kLdsMinMicrographs;
+    if ((many || distinct.rank[sh.n_layers - 1] != nullptr) && lds_shape(sh, ls))
+        hipLaunchKernelGGL((many ? sample_micrographs_lds<OffT, 128> : sample_micrographs_lds<OffT, 256>), grid,
+                           dim3(many ? 128 : 256), ls.bytes, s, offsets, g->indices, seeds, n_seeds, sh, ls, keys, ids, indptr,
+                           slot_idx, slot_idx_stride, present, m_offset, seeds_per_key, has_edges, distinct);
     else
         hipLaunchKernelGGL(sample_micrographs<OffT>, grid, dim3(threads), 0, s, offsets, g->indices, seeds, n_seeds, sh, keys,
                            ids, indptr, slot_idx, slot_idx_stride, present, m_offset, seeds_per_key, has_edges);
@@ -396,9 +404,23 @@ extern "C" int64_t hopgnn_slots_per_seed(const int32_t* fanouts, int32_t n_layer
 
 namespace hopgnn {
 
+bool sample_gives_distinct(const int32_t* fanouts, int32_t n_layers) {
+    if (n_layers < 2 || n_layers > kMaxLayers || hopgnn_slots_per_seed(fanouts, n_layers) < 0) return false;
+    SampleShape sh{};
+    sh.n_layers = n_layers;
+    sh.P[0] = 1;
+    for (int32_t h = 1; h <= n_layers; ++h) {
+        sh.f[h] = fanouts[h - 1];
+        sh.P[h] = sh.P[h - 1] * sh.f[h];
+    }
+    LdsShape ls;
+    return lds_shape(sh, ls);
+}
+
 hopgnn_status sample_batches(const hopgnn_csr* g, const int32_t* seeds, int32_t n_seeds, const int32_t* fanouts,
                              int32_t n_layers, const uint64_t* keys, int32_t n_batches, int32_t* ids, int32_t* indptr,
-                             int32_t* slot_idx, int64_t slot_idx_stride, uint8_t* present, void* stream) {
+                             int32_t* slot_idx, int64_t slot_idx_stride, uint8_t* present, void* stream,
+                             const DistinctOut& distinct) {
     if (g == nullptr || fanouts == nullptr || n_seeds < 0 || n_batches < 0) return HOPGNN_EINVAL;
     const int64_t t_seed = hopgnn_slots_per_seed(fanouts, n_layers);
     if (t_seed < 0) return HOPGNN_EINVAL;
@@ -434,8 +456,16 @@ hopgnn_status sample_batches(const hopgnn_csr* g, const int32_t* seeds, int32_t 
         int32_t* ip = b0 == 0 ? indptr : nullptr;
         int32_t* si = slot_idx != nullptr ? slot_idx + (int64_t)b0 * slot_idx_stride : nullptr;
         const dim3 grid((unsigned)n_seeds, (unsigned)nb);
+        DistinctOut dn = distinct;
+        for (int32_t h = 1; h < n_layers; ++h) {
+            if (dn.rank[h] == nullptr) continue;
+            const int64_t m0 = (int64_t)b0 * n_seeds;
+            dn.rank[h] += m0 * sh.P[h];
+            dn.slot[h] += m0 * sh.P[h];
+            dn.count[h] += m0;
+        }
         (g->offsets_i64 ? launch_sample<int64_t> : launch_sample<int32_t>)(grid, threads, s, g, sd, n_seeds, sh, bk, id, ip, si,
-                                                                           slot_idx_stride, present, 0, n_seeds);
+                                                                           slot_idx_stride, present, 0, n_seeds, dn);
         HOPGNN_LAUNCH_CHECK();
     }
     return HOPGNN_OK;
@@ -443,7 +473,8 @@ hopgnn_status sample_batches(const hopgnn_csr* g, const int32_t* seeds, int32_t 
 
 hopgnn_status sample_merged(const hopgnn_csr* g, const int32_t* seeds, int32_t n_seeds, int32_t seeds_per_key,
                             const int32_t* fanouts, int32_t n_layers, const uint64_t* keys, int32_t* ids,
-                            int32_t* indptr, int32_t* slot_idx, uint8_t* present, void* stream) {
+                            int32_t* indptr, int32_t* slot_idx, uint8_t* present, void* stream,
+                            const DistinctOut& distinct) {
     if (g == nullptr || fanouts == nullptr || n_seeds < 0 || seeds_per_key < 1) return HOPGNN_EINVAL;
     const int64_t t_seed = hopgnn_slots_per_seed(fanouts, n_layers);
     if (t_seed < 0) return HOPGNN_EINVAL;
@@ -475,7 +506,7 @@ hopgnn_status sample_merged(const hopgnn_csr* g, const int32_t* seeds, int32_t n
         const int64_t count = (int64_t)nk * seeds_per_key < n_seeds - m0 ? (int64_t)nk * seeds_per_key : n_seeds - m0;
         const dim3 grid((unsigned)count, 1u);
         (g->offsets_i64 ? launch_sample<int64_t> : launch_sample<int32_t>)(grid, threads, s, g, seeds, n_seeds, sh, bk, ids, indptr,
-                                                                           slot_idx, 0, present, (int32_t)m0, seeds_per_key);
+                                                                           slot_idx, 0, present, (int32_t)m0, seeds_per_key, distinct);
         HOPGNN_LAUNCH_CHECK();
     }
     return HOPGNN_OK;
