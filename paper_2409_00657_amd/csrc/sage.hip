@@ -111,18 +111,33 @@ __device__ __forceinline__ void project_epilogue_f32out(floatx16 (&acc)[TM][TN],
     }
 }
 
+// Eight 2-byte elements of a staged row to columns col .. col + 7 of an output row.  `whole`: rows are whole 16-byte words
+// on 16-byte boundaries; otherwise from any alignment, the row's last few elements one by one.
+template <typename T>
+__device__ __forceinline__ void store_word(T* row, const T* staged, int32_t col, int32_t d_out, bool whole) {
+    const uint4 v = *reinterpret_cast<const uint4*>(staged);
+    if (whole) {
+        if (col < d_out) *reinterpret_cast<uint4*>(row + col) = v;
+    } else if (col + 8 <= d_out) {
+        __builtin_memcpy(row + col, &v, 16);
+    } else {
+        for (int e = 0; e < 8; ++e)
+            if (col + e < d_out) row[col + e] = staged[e];
+    }
+}
+
 // 2-byte outputs: a lane of an MFMA tile holds single elements of 16 different rows, so
 // storing them directly issues 2-byte writes (64-byte pieces of two rows per instruction).
 // Instead each wave passes one 32-row band of its tiles through a private piece of LDS
 // ([32][32*TN + 8] elements) and writes it out as 128-bit words, whole rows at a time.
-// Requires d_out % 8 == 0.  `band` points at this wave's LDS piece; waves do not share it,
+// `band` points at this wave's LDS piece; waves do not share it,
 // so only this wave's own LDS traffic has to be waited for.
 template <typename Tr, int TM, int TN>
 __device__ __forceinline__ void project_epilogue_staged(floatx16 (&acc)[TM][TN], int64_t row0, int32_t col0,
                                                         int lane, int64_t n_dst, int32_t d_out,
                                                         const float* bias, int relu,
                                                         typename Tr::store_t* out,
-                                                        typename Tr::store_t* band) {
+                                                        typename Tr::store_t* band, bool whole) {
     using T = typename Tr::store_t;
     constexpr int W = 32 * TN, LDW = W + 8;          // band width in elements, padded row
     constexpr int WORDS = W / 8;                     // 16-byte words per band row
@@ -145,9 +160,7 @@ __device__ __forceinline__ void project_epilogue_staged(floatx16 (&acc)[TM][TN],
             const int w = j * 64 + lane;
             const int r = w / WORDS, c = (w % WORDS) * 8;
             const int64_t row = row0 + tm * 32 + r;
-            const uint4 v = *reinterpret_cast<const uint4*>(&band[r * LDW + c]);
-            if (row < n_dst && col0 + c < d_out)
-                *reinterpret_cast<uint4*>(&out[row * d_out + col0 + c]) = v;
+            if (row < n_dst) store_word<T>(out + row * d_out, &band[r * LDW + c], col0 + c, d_out, whole);
         }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // band is rewritten by the next tm
     }
@@ -198,12 +211,12 @@ __device__ __forceinline__ uint2 pack_run(const floatx16& a, int q, const float*
 }
 
 // 2-byte outputs through a per-wave band of LDS ([32][32*TN + 8] elements) so that rows leave as
-// 128-bit words.  Requires d_out % 8 == 0.  Waves do not share a band, so only this wave's own
-// LDS traffic has to be waited for.
+// 128-bit words.  Waves do not share a band, so only this wave's own LDS traffic has to be waited for.
 template <typename Tr, int TM, int TN>
 __device__ __forceinline__ void epilogue16_staged(floatx16 (&acc)[TM][TN], int64_t row0, int32_t col0, int lane,
                                                   int64_t row_end, int32_t d_out, const float* bias,
-                                                  int relu, typename Tr::store_t* out, typename Tr::store_t* band) {
+                                                  int relu, typename Tr::store_t* out, typename Tr::store_t* band,
+                                                  bool whole) {
     constexpr int W = 32 * TN, LDW = W + 8;          // band width in elements, padded row
     constexpr int WORDS = W / 8;                     // 16-byte words per band row
 #pragma unroll
@@ -222,9 +235,7 @@ __device__ __forceinline__ void epilogue16_staged(floatx16 (&acc)[TM][TN], int64
             const int w = j * 64 + lane;
             const int r = w / WORDS, c = (w % WORDS) * 8;
             const int64_t row = row0 + tm * 32 + r;
-            const uint4 v = *reinterpret_cast<const uint4*>(&band[r * LDW + c]);
-            if (row < row_end && col0 + c < d_out)
-                *reinterpret_cast<uint4*>(&out[row * d_out + col0 + c]) = v;
+            if (row < row_end) store_word<typename Tr::store_t>(out + row * d_out, &band[r * LDW + c], col0 + c, d_out, whole);
         }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // band is rewritten by the next tm
     }
@@ -449,11 +460,7 @@ sage_project_f32(const float* __restrict__ Hsrc, const int32_t* __restrict__ sel
         b_self[it] = Wself + n;
         b_neigh[it] = Wneigh + n - (int64_t)d_in * d_out;
     }
-    auto a_elem = [&](int it, int k) -> float {   // one element of the concatenated row
-        if (k < d_in) return a_self[it] >= 0 ? Hsrc[a_self[it] + k] : 0.f;
-        if (k < K) return a_mean[it] >= 0 ? Mean[a_mean[it] + (k - d_in)] : 0.f;
-        return 0.f;
-    };
+    auto a_at = [&](int it, int k) { return k < K ? (k < d_in ? p_self[it] : p_mean[it]) + k : Zero; };
     auto load_tile = [&](Regs& r, int t) {
         const int k0 = t * BK;
 #pragma unroll
@@ -464,8 +471,10 @@ sage_project_f32(const float* __restrict__ Hsrc, const int32_t* __restrict__ sel
             if (VEC) {   // d_in % 4 == 0: a float4 never straddles the self/mean boundary
                 const float* p = (k < d_in ? p_self[it] : p_mean[it]) + k;
                 v = *reinterpret_cast<const float4*>(k < K ? p : Zero);
+            } else if (k + 4 <= d_in || (k >= d_in && k + 4 <= K)) {      // a word of one half, from any alignment
+                __builtin_memcpy(&v, (k < d_in ? p_self[it] : p_mean[it]) + k, 16);
             } else {
-                v = make_float4(a_elem(it, k), a_elem(it, k + 1), a_elem(it, k + 2), a_elem(it, k + 3));
+                v = make_float4(*a_at(it, k), *a_at(it, k + 1), *a_at(it, k + 2), *a_at(it, k + 3));
             }
             r.a[it] = v;
         }
@@ -478,12 +487,16 @@ sage_project_f32(const float* __restrict__ Hsrc, const int32_t* __restrict__ sel
             if (VEC) {   // d_out % 4 == 0; one multiply-add and selects, no control flow
                 const float* p = (k < d_in ? b_self[it] : b_neigh[it]) + (int64_t)k * d_out;
                 v = *reinterpret_cast<const float4*>((k < K && n < d_out) ? p : Zero);
-            } else if (k < K) {
-                const float* p = (k < d_in ? Wself + (int64_t)k * d_out : Wneigh + (int64_t)(k - d_in) * d_out) + n;
-                if (n + 0 < d_out) v.x = p[0];
-                if (n + 1 < d_out) v.y = p[1];
-                if (n + 2 < d_out) v.z = p[2];
-                if (n + 3 < d_out) v.w = p[3];
+            } else {
+                const float* p = (k < d_in ? b_self[it] : b_neigh[it]) + (int64_t)k * d_out;
+                if (n + 4 <= d_out || k >= K) {      // from any alignment
+                    __builtin_memcpy(&v, k < K ? p : Zero, 16);
+                } else {
+                    v.x = *(n + 0 < d_out ? p + 0 : Zero);
+                    v.y = *(n + 1 < d_out ? p + 1 : Zero);
+                    v.z = *(n + 2 < d_out ? p + 2 : Zero);
+                    v.w = *(n + 3 < d_out ? p + 3 : Zero);
+                }
             }
             r.b[it] = v;
         }
@@ -679,6 +692,7 @@ sage_project_split(const float* __restrict__ Hsrc, const int32_t* __restrict__ s
     auto b_at = [&](int it, int k) {
         return k < K && b_in[it] ? (k < d_in ? b_self[it] : b_neigh[it]) + (int64_t)k * d_out : Zero;
     };
+    auto one_half = [&](int k) { return k + 4 <= d_in || (k >= d_in && k + 4 <= K); };      // four k in one half
     auto load_tile = [&](Regs& r, int t) {
         const int k0 = t * BK;
 #pragma unroll
@@ -689,6 +703,8 @@ sage_project_split(const float* __restrict__ Hsrc, const int32_t* __restrict__ s
                 if (VEC) {   // d_in % 4 == 0: four k never straddle the self/mean boundary
                     const float4 v = *reinterpret_cast<const float4*>(a_at(it, k + h));
                     r.a[it][h] = v.x, r.a[it][h + 1] = v.y, r.a[it][h + 2] = v.z, r.a[it][h + 3] = v.w;
+                } else if (one_half(k + h)) {      // from any alignment
+                    __builtin_memcpy(&r.a[it][h], a_at(it, k + h), 16);
                 } else {
 #pragma unroll
                     for (int e = 0; e < 4; ++e) r.a[it][h + e] = *a_at(it, k + h + e);
@@ -700,7 +716,7 @@ sage_project_split(const float* __restrict__ Hsrc, const int32_t* __restrict__ s
             const int k = k0 + ((it * kProjThreads + tid) / BN) * 8;
 #pragma unroll
             for (int h = 0; h < 8; h += 4) {
-                if (VEC) {   // four k lie in one weight matrix
+                if (VEC || one_half(k + h)) {   // four k lie in one weight matrix
                     const float* p = b_at(it, k + h);
                     const int64_t step = k + h < K && b_in[it] ? d_out : 0;
 #pragma unroll
@@ -866,11 +882,7 @@ sage_project_16(const uint16_t* __restrict__ Hsrc, const int32_t* __restrict__ s
         p_self[it] = a_self[it] >= 0 ? Hsrc + a_self[it] : Zero;
         p_mean[it] = a_mean[it] >= 0 ? Mean + a_mean[it] - d_in : Zero;   // indexed by the concatenated k
     }
-    auto a_elem = [&](int it, int k) -> uint16_t {
-        if (k < d_in) return a_self[it] >= 0 ? Hsrc[a_self[it] + k] : (uint16_t)0;
-        if (k < K) return a_mean[it] >= 0 ? Mean[a_mean[it] + (k - d_in)] : (uint16_t)0;
-        return 0;
-    };
+    auto a_at = [&](int it, int k) { return k < K ? (k < d_in ? p_self[it] : p_mean[it]) + k : Zero; };
     auto load_tile = [&](Regs& r, int t) {
         const int k0 = t * BK;
 #pragma unroll
@@ -881,9 +893,11 @@ sage_project_16(const uint16_t* __restrict__ Hsrc, const int32_t* __restrict__ s
             if (VEC) {   // d_in % 8 == 0: a 16-byte word never straddles the self/mean boundary
                 const uint16_t* p = (k < d_in ? p_self[it] : p_mean[it]) + k;
                 v.v = *reinterpret_cast<const uint4*>(k < K ? p : Zero);
-            } else {
+            } else if (k + 8 <= d_in || (k >= d_in && k + 8 <= K)) {      // a word of one half, from any alignment
+                __builtin_memcpy(&v.v, a_at(it, k), 16);
+            } else {                // of both halves, or past the end (two or three words of a row): branch-free elements
 #pragma unroll
-                for (int j = 0; j < 8; ++j) v.e[j] = a_elem(it, k + j);
+                for (int j = 0; j < 8; ++j) v.e[j] = *a_at(it, k + j);
             }
             r.a[it] = v.v;
         }
@@ -989,16 +1003,14 @@ sage_project_16(const uint16_t* __restrict__ Hsrc, const int32_t* __restrict__ s
     } else if (out_f32) {     // `out` is a float array: unrounded result
         if constexpr (SW) epilogue16_direct<Tr, float, TM, TN>(acc, wrow0, wcol0, lane, row_end, d_out, wbias, relu, reinterpret_cast<float*>(out));
         else project_epilogue_f32out<Tr, TM, TN>(acc, wrow0, wcol0, lane, row_end, d_out, wbias, relu, reinterpret_cast<float*>(out));
-    } else if (VEC && (d_out & 7) == 0) {
+    } else {
         // every wave is past its last LDS read of the tiles: reuse that LDS, one band per wave
         constexpr int BAND = 32 * (32 * TN + 8);
         static_assert((size_t)WM * WN * BAND <= (size_t)2 * (BM + BN) * LD, "epilogue bands exceed the tile LDS");
         typename Tr::store_t* band = reinterpret_cast<typename Tr::store_t*>(lds16) + wave * BAND;
-        if constexpr (SW) epilogue16_staged<Tr, TM, TN>(acc, wrow0, wcol0, lane, row_end, d_out, wbias, relu, out, band);
-        else project_epilogue_staged<Tr, TM, TN>(acc, wrow0, wcol0, lane, row_end, d_out, wbias, relu, out, band);
-    } else {
-        if constexpr (SW) epilogue16_direct<Tr, typename Tr::store_t, TM, TN>(acc, wrow0, wcol0, lane, row_end, d_out, wbias, relu, out);
-        else project_epilogue<Tr, TM, TN>(acc, wrow0, wcol0, lane, row_end, d_out, wbias, relu, out);
+        const bool whole = VEC && (d_out & 7) == 0;
+        if constexpr (SW) epilogue16_staged<Tr, TM, TN>(acc, wrow0, wcol0, lane, row_end, d_out, wbias, relu, out, band, whole);
+        else project_epilogue_staged<Tr, TM, TN>(acc, wrow0, wcol0, lane, row_end, d_out, wbias, relu, out, band, whole);
     }
 }
 

@@ -282,12 +282,14 @@ constexpr int kMeanUnrollElem = 4;       // the element-wise path
 // 25, 10: long runs leave the XCDs with unequal levels); 149 / 147 / 145 / 146 / 146 us on 455 k rows of 256 bytes.
 constexpr int kMeanXcdRun = 16;
 
-template <typename Tr, int OP>
+// LOOSE: rows of d_in elements that are no whole number of words, or not on 16-byte boundaries; the words come from and go
+// to addresses of any alignment, and the last one of a row ends with the row (it overlaps the one before: the same sums).
+template <typename Tr, int OP, bool LOOSE = false>
 __global__ void __launch_bounds__(kMeanThreads)
 sage_mean_vec(const uint4* __restrict__ Hsrc, const int32_t* __restrict__ indptr,
               const int32_t* __restrict__ idx, int64_t n_dst, int32_t words_per_row, int32_t group,
               uint4* __restrict__ Mean, uint32_t* __restrict__ zero_row, int32_t zero_words, TransposeJob job,
-              AggSpec agg, const int64_t* __restrict__ n_rows_dev, uint32_t xcd_run) {
+              AggSpec agg, const int64_t* __restrict__ n_rows_dev, uint32_t xcd_run, int32_t d_in) {
     if (blockIdx.x >= job.first_block) {
         transpose_w_tile(job, blockIdx.x - job.first_block);
         return;
@@ -313,6 +315,14 @@ sage_mean_vec(const uint4* __restrict__ Hsrc, const int32_t* __restrict__ indptr
     int64_t self_row = -1;
     if (agg.with_self) self_row = agg.self_idx != nullptr ? (int64_t)agg.self_idx[r] : r;
     for (int32_t c = g; c < words_per_row; c += group) {
+        using T = typename Tr::store_t;
+        const int32_t col = c * Tr::kPer16 <= d_in - Tr::kPer16 ? c * Tr::kPer16 : d_in - Tr::kPer16;      // LOOSE: first column
+        auto word = [&](int64_t row) -> uint4 {
+            if (!LOOSE) return Hsrc[row * words_per_row + c];
+            uint4 v;
+            __builtin_memcpy(&v, reinterpret_cast<const T*>(Hsrc) + row * d_in + col, 16);
+            return v;
+        };
         float acc[Tr::kPer16];
 #pragma unroll
         for (int i = 0; i < Tr::kPer16; ++i) acc[i] = 0.f;
@@ -320,7 +330,7 @@ sage_mean_vec(const uint4* __restrict__ Hsrc, const int32_t* __restrict__ indptr
         constexpr bool is_max = OP == kAggOpMax;
         if (self_row >= 0) {     // first term: the sum starts from 0, the maximum from this row
             Pack16<Tr> v;
-            v.v = Hsrc[self_row * words_per_row + c];
+            v.v = word(self_row);
 #pragma unroll
             for (int i = 0; i < Tr::kPer16; ++i) acc[i] = Tr::to_f(v.e[i]);
             ++cnt;
@@ -332,7 +342,7 @@ sage_mean_vec(const uint4* __restrict__ Hsrc, const int32_t* __restrict__ indptr
             for (int k = 0; k < MeanUnroll<Tr>::value; ++k) u[k] = (e + k < end) ? idx[e + k] : -1;
 #pragma unroll
             for (int k = 0; k < MeanUnroll<Tr>::value; ++k)
-                if (u[k] >= 0) v[k].v = Hsrc[(int64_t)u[k] * words_per_row + c];
+                if (u[k] >= 0) v[k].v = word(u[k]);
 #pragma unroll
             for (int k = 0; k < MeanUnroll<Tr>::value; ++k)
                 if (u[k] >= 0) {
@@ -348,11 +358,12 @@ sage_mean_vec(const uint4* __restrict__ Hsrc, const int32_t* __restrict__ indptr
         const float fc = OP == kAggOpMean ? (float)cnt : 1.f;
 #pragma unroll
         for (int i = 0; i < Tr::kPer16; ++i) o.e[i] = Tr::from_f(cnt > 0 ? acc[i] / fc : 0.f);
-        Mean[r * words_per_row + c] = o.v;
+        if (!LOOSE) Mean[r * words_per_row + c] = o.v;
+        else __builtin_memcpy(reinterpret_cast<T*>(Mean) + r * d_in + col, &o.v, 16);
     }
 }
 
-// Element path for rows that are not a whole number of 16-byte words.
+// Element path for rows shorter than a 16-byte word.
 template <typename Tr, int OP>
 __global__ void __launch_bounds__(kMeanThreads)
 sage_mean_elem(const typename Tr::store_t* __restrict__ Hsrc, const int32_t* __restrict__ indptr,
@@ -410,8 +421,9 @@ static hopgnn_status launch_mean(const void* Hsrc, const int32_t* indptr, const 
                                  size_t zero_bytes, TransposeJob job, uint32_t n_transpose_tiles, hipStream_t s,
                                  AggSpec agg = kAggMean, const int64_t* n_rows_dev = nullptr) {
     using T = typename Tr::store_t;
-    const bool vec = (d_in % Tr::kPer16 == 0) && aligned(Hsrc, 16) && aligned(mean, 16);
-    const int units = vec ? d_in / Tr::kPer16 : d_in;
+    const bool whole = (d_in % Tr::kPer16 == 0) && aligned(Hsrc, 16) && aligned(mean, 16);
+    const bool vec = d_in >= Tr::kPer16;
+    const int units = vec ? (int)ceil_div(d_in, Tr::kPer16) : d_in;
     // lanes per destination row: one per 16-byte word (no lane idles on rows that are not a power of two
     // words long: 25 words of a 400-byte row on 32 lanes left 7 of them without work), at most a wavefront
     const int group = vec ? (units < 64 ? units : 64) : mean_group(units);
@@ -420,15 +432,17 @@ static hopgnn_status launch_mean(const void* Hsrc, const int32_t* indptr, const 
     if (mean_blocks + n_transpose_tiles >= ((int64_t)1 << 31)) return HOPGNN_ERANGE;
     job.first_block = (uint32_t)mean_blocks;
     const int64_t blocks = mean_blocks + n_transpose_tiles;
-    auto kv = agg.op == kAggOpMean ? sage_mean_vec<Tr, kAggOpMean>
-              : agg.op == kAggOpSum ? sage_mean_vec<Tr, kAggOpSum> : sage_mean_vec<Tr, kAggOpMax>;
+    auto kv = whole ? (agg.op == kAggOpMean  ? sage_mean_vec<Tr, kAggOpMean>
+                       : agg.op == kAggOpSum ? sage_mean_vec<Tr, kAggOpSum> : sage_mean_vec<Tr, kAggOpMax>)
+                    : (agg.op == kAggOpMean  ? sage_mean_vec<Tr, kAggOpMean, true>
+                       : agg.op == kAggOpSum ? sage_mean_vec<Tr, kAggOpSum, true> : sage_mean_vec<Tr, kAggOpMax, true>);
     auto ke = agg.op == kAggOpMean ? sage_mean_elem<Tr, kAggOpMean>
               : agg.op == kAggOpSum ? sage_mean_elem<Tr, kAggOpSum> : sage_mean_elem<Tr, kAggOpMax>;
     if (vec)
         hipLaunchKernelGGL(kv, dim3((unsigned)blocks), dim3(kMeanThreads), 0, s,
                            static_cast<const uint4*>(Hsrc), indptr, idx, n_dst, units, group,
                            static_cast<uint4*>(mean), static_cast<uint32_t*>(zero_row), (int32_t)(zero_bytes / 4), job,
-                           agg, n_rows_dev, (uint32_t)xcd_run);
+                           agg, n_rows_dev, (uint32_t)xcd_run, d_in);
     else
         hipLaunchKernelGGL(ke, dim3((unsigned)blocks), dim3(kMeanThreads), 0, s,
                            static_cast<const T*>(Hsrc), indptr, idx, n_dst, d_in, group,
