@@ -263,10 +263,17 @@ bitmap_pack_count(uint4* __restrict__ present16, uint2* __restrict__ word_rank, 
             const uint32_t half = pack16(q[k]);
             const uint32_t other = __shfl_xor(half, 1, kWave);
             word[k] = half | (other << 16);
-            const uint32_t cnt = (lane & 1) == 0 ? __popc(word[k]) : 0u;
-            const uint32_t inc = wave_inclusive_scan(cnt);
-            rank[k] = wave_total + inc - cnt;
-            wave_total += __shfl(inc, kWave - 1, kWave);
+        }
+        // two rows to a scan, a row's at most 1024 set bits in half a register each
+#pragma unroll
+        for (int k = 0; k < 8; k += 2) {
+            const uint32_t c0 = (lane & 1) == 0 ? __popc(word[k]) : 0u, c1 = (lane & 1) == 0 ? __popc(word[k + 1]) : 0u;
+            const uint32_t inc = wave_inclusive_scan(c0 | (c1 << 16));
+            const uint32_t row = __shfl(inc, kWave - 1, kWave);
+            rank[k] = wave_total + (inc & 0xFFFFu) - c0;
+            wave_total += row & 0xFFFFu;
+            rank[k + 1] = wave_total + (inc >> 16) - c1;
+            wave_total += row >> 16;
         }
         if (lane == 0) lds4[wave] = wave_total;
         __syncthreads();

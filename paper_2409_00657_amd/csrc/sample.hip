@@ -159,8 +159,10 @@ struct LdsShape {
 // us, sampling call alone, slot by slot / this with 256 / 128 / 64 threads:
 //   16384 x 10,10,10 (chung_lu, 20 M vertices)   128 / 125 / 95 / 94      4096 x 10,10,10 (100 M)   35 / 33 / 30 / 31
 //    4096 x 25,10 (rmat, 16 M)                    13.5 / 16.0 / 12.8 / 11.3     1024 x 15,10,5 (2.4 M)   11.9 / 13.3 / 15.6 / 18.9
-// (with marks, 4096 x 10,10,10: 63 / 53).
+// (with marks, 4096 x 10,10,10: 63 / 53; 3296 x 12,16 on a uniform graph of degree 27, 0.7 M slots, whole fetch: 50.1 / 52.1).
+// A caller that wants the distinct vertices takes it at any size.
 constexpr int kLdsMaxParents = 512, kLdsMaxDraws = 4096, kLdsMinMicrographs = 2048;
+constexpr int64_t kLdsMinSlots = 2000000;
 
 template <typename OffT, int NT>
 __global__ void __launch_bounds__(NT)
@@ -377,7 +379,8 @@ static void launch_sample(dim3 grid, int threads, hipStream_t s, const hopgnn_cs
     const int32_t has_edges = g->n_edges > 0 ? 1 : 0;
     LdsShape ls;
     const bool many = (int64_t)grid.x * grid.y >= kLdsMinMicrographs;
-    if ((many || distinct.rank[sh.n_layers - 1] != nullptr) && lds_shape(sh, ls))
+    const bool large = many && (int64_t)grid.x * grid.y * (sh.base[sh.n_layers + 1] / n_seeds) >= kLdsMinSlots;
+    if ((large || distinct.rank[sh.n_layers - 1] != nullptr) && lds_shape(sh, ls))
         hipLaunchKernelGGL((many ? sample_micrographs_lds<OffT, 128> : sample_micrographs_lds<OffT, 256>), grid,
                            dim3(many ? 128 : 256), ls.bytes, s, offsets, g->indices, seeds, n_seeds, sh, ls, keys, ids, indptr,
                            slot_idx, slot_idx_stride, present, m_offset, seeds_per_key, has_edges, distinct);

@@ -1,5 +1,5 @@
 """hopgnn_sample around the sizes where it changes its way: levels held in LDS with every distinct vertex drawn once
-(from 2048 micrographs, up to 512 slots on the widest non-leaf level and 4096 leaves), levels walked in memory
+(from 2048 micrographs and 2 M slots, up to 512 slots on the widest non-leaf level and 4096 leaves), levels walked in memory
 otherwise; bit for bit the oracle."""
 import numpy as np
 import pytest
