@@ -154,7 +154,7 @@ extern "C" hopgnn_status hopgnn_batch_prepare(const hopgnn_batch_plan* p, void* 
         if (p->dt != HOPGNN_F32)
             job = TransposeJob{static_cast<const uint16_t*>(p->W_self[k - 1]), static_cast<const uint16_t*>(p->W_neigh[k - 1]),
                                reinterpret_cast<uint16_t*>(ws + W.wt_off[k - 1]), d_in, p->d_out[k - 1], W.KP[k - 1],
-                               W.NP[k - 1], 0u, 2 * d_in};
+                               W.NP[k - 1], 0u, 2 * d_in, 0};
         const hopgnn_status rc = launch_prep_weights(job, k == 1 ? ws + W.zero_off : nullptr, k == 1 ? W.zero_bytes : 0,
                                                      static_cast<hipStream_t>(stream));
         if (rc != HOPGNN_OK) return rc;
@@ -348,7 +348,23 @@ extern "C" hopgnn_status hopgnn_batch_fwd(const hopgnn_batch_plan* p, const int3
         // its deepest rows once per distinct vertex writes those, densely, to scratch instead; its means and the
         // next layer's then come from the kernel that finds rows through the sampler's numbers.
         const void* zero = tws + TW.zero_off;
+        // fp32 weights as pieces, of the weights as they are now: three layers along with the first means, others before
+        TransposeJob split_jobs[kMaxLayers];
+        TransposeJobs first_jobs{};
+        uint32_t first_tiles = 0;
+        if (p->dt == HOPGNN_F32) {
+            int32_t d_in = p->dim;
+            for (int32_t k = 1; k <= L; ++k) {
+                split_jobs[k - 1] = TransposeJob{static_cast<const uint16_t*>(p->W_self[k - 1]), static_cast<const uint16_t*>(p->W_neigh[k - 1]),
+                                                 reinterpret_cast<uint16_t*>(tws + TW.wt_off[k - 1]), d_in, p->d_out[k - 1],
+                                                 TW.KP[k - 1], TW.NP[k - 1], 0u, 2 * d_in, 1};
+                d_in = p->d_out[k - 1];
+                if (k > 3 && (rc = launch_prep_weights(split_jobs[k - 1], nullptr, 0, st)) != HOPGNN_OK) return rc;
+            }
+            first_jobs = transpose_jobs(split_jobs, L < 3 ? L : 3, first_tiles);
+        }
         for (int32_t b = 0; b < n_runs; ++b) {
+            if (b > 0) first_jobs = TransposeJobs{}, first_tiles = 0;
             const int32_t* rb = p->remap + b * T;
             const int32_t* ids = p->ids + (merged ? 0 : (int64_t)b * T);
             const void* src = p->Xu;
@@ -389,14 +405,15 @@ extern "C" hopgnn_status hopgnn_batch_fwd(const hopgnn_batch_plan* p, const int3
                         tm.rows = tws + TW.rows_off[(k - 1) & 1];
                     }
                     rc = launch_tree_means(p->dt, src, tm, n_dst, d_in, mean, k == 1 ? tws + TW.zero_off : nullptr,
-                                           k == 1 ? TW.zero_bytes : 0, st);
+                                           k == 1 ? TW.zero_bytes : 0, k == 1 ? first_jobs : TransposeJobs{},
+                                           k == 1 ? first_tiles : 0u, st);
                     if (rc != HOPGNN_OK) return rc;
                 } else if (k == 1) {
                     const AggSpec spec{nullptr, 0, kAggOpMean};
                     void* zr = const_cast<void*>(zero);
-                    if (p->dt == HOPGNN_F32) rc = launch_mean<TrF32>(src, p->indptr, rb + B_run, n_dst, d_in, mean, zr, TW.zero_bytes, TransposeJob{}, 0, st, spec, nullptr);
-                    else if (p->dt == HOPGNN_BF16) rc = launch_mean<TrBF16>(src, p->indptr, rb + B_run, n_dst, d_in, mean, zr, TW.zero_bytes, TransposeJob{}, 0, st, spec, nullptr);
-                    else rc = launch_mean<TrF16>(src, p->indptr, rb + B_run, n_dst, d_in, mean, zr, TW.zero_bytes, TransposeJob{}, 0, st, spec, nullptr);
+                    if (p->dt == HOPGNN_F32) rc = launch_mean<TrF32>(src, p->indptr, rb + B_run, n_dst, d_in, mean, zr, TW.zero_bytes, first_jobs, first_tiles, st, spec, nullptr);
+                    else if (p->dt == HOPGNN_BF16) rc = launch_mean<TrBF16>(src, p->indptr, rb + B_run, n_dst, d_in, mean, zr, TW.zero_bytes, first_jobs, first_tiles, st, spec, nullptr);
+                    else rc = launch_mean<TrF16>(src, p->indptr, rb + B_run, n_dst, d_in, mean, zr, TW.zero_bytes, first_jobs, first_tiles, st, spec, nullptr);
                     if (rc != HOPGNN_OK) return rc;
                 }
                 if (mk && mark_agg && k == 1 && hipEventRecord(ev_b, st) != hipSuccess) return HOPGNN_EHIP;

@@ -244,7 +244,7 @@ static hopgnn_status launch_prep(hopgnn_dtype dt, const void* W, uint16_t* Wt, c
     uint32_t n_tr = 0;
     if (dt != HOPGNN_F32) {
         job = TransposeJob{static_cast<const uint16_t*>(W), static_cast<const uint16_t*>(W), Wt, d_in, d_out, P.KP,
-                           P.NP, 0u, d_in};
+                           P.NP, 0u, d_in, 0};
         n_tr = (uint32_t)(P.KP / 32) * (uint32_t)(P.NP / 32);
     }
     sw.n_blocks = sw.Wscore != nullptr ? (uint32_t)ceil_div((int64_t)sw.d_in * 2 * sw.n_heads, kLayerThreads) : 0u;
@@ -341,12 +341,12 @@ extern "C" hopgnn_status hopgnn_gcn_fwd_dev(const void* Hsrc, hopgnn_dtype dt, i
     void* zero = static_cast<char*>(ws) + L.agg_bytes + L.wt_bytes;
     if (n_src == 0) Hsrc = zero;   // nothing is read from it unmasked
 
-    TransposeJob job{};
+    TransposeJobs job{};
     uint32_t n_tr = 0;
     if (dt != HOPGNN_F32) {
-        job = TransposeJob{static_cast<const uint16_t*>(W), static_cast<const uint16_t*>(W), Wt, d_in, d_out, L.KP, L.NP,
-                           0u, d_in};
-        n_tr = (uint32_t)(L.KP / 32) * (uint32_t)(L.NP / 32);
+        const TransposeJob j{static_cast<const uint16_t*>(W), static_cast<const uint16_t*>(W), Wt, d_in, d_out, L.KP, L.NP,
+                             0u, d_in, 0};
+        job = transpose_jobs(&j, 1, n_tr);
     }
     // with n_src == 0 every self index must be negative; identity self was rejected above
     const AggSpec spec{self_idx, 1, norm ? kAggOpMean : kAggOpSum};

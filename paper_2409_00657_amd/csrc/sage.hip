@@ -590,13 +590,13 @@ sage_project_f32(const float* __restrict__ Hsrc, const int32_t* __restrict__ sel
 }
 
 // The fp32 layer on the bf16 instruction.  v_mfma_f32_32x32x2_f32 needs 512 cycles per 32 x 32 x 16 block,
-// eight v_mfma_f32_32x32x16_bf16 of the split operands 256.  Both operands are split on their way
-// to LDS (three pieces each, k contiguous, row stride conflict free for 128-bit reads), the weights in
-// this kernel too, so nothing derived from them outlives the call.
-// 170 k rows of 2 x 100 -> 256 with means: 169 us against 218 on the fp32 instruction (146 with six products in
-// one accumulator, whose bits fell short of fp32's).  Small tiles wait for memory and gain nothing (16 k rows of
-// 2 x 256 -> 256 with means: 64 us against 59; 11 k of 2 x 128 -> 128: 17 against 17): they are split so that a
-// row's bits do not depend on the number of rows in its call.
+// eight v_mfma_f32_32x32x16_bf16 of the split operands 256.  The left operand is split on its way to LDS (three pieces,
+// k contiguous, row stride conflict free for 128-bit reads); the weights' pieces are formed once per call by a side job of
+// the launch before (TransposeJob::split; nothing derived from them outlives the call) and only copied here: splitting
+// them in every workgroup made 8.3 vector instructions per MFMA, of which the matrix pipe hides six, now 4.5.
+// 85 k rows of 2 x 100 -> 256: 88 -> 84 us; 12 k rows of 2 x 256 -> 256 39 -> 35, 1 k rows 16.5 -> 13.2; 11 k of
+// 2 x 128 -> 128 17 -> 15.  What is left is the hand-over of a K tile through LDS behind a barrier, 13 times a tile.
+// Small tiles take the split too, so that a row's bits do not depend on the number of rows in its call.
 template <int BM, int BN, int BK, bool VEC, bool TREE>
 __global__ void __launch_bounds__(kProjThreads, 2)
 sage_project_split(const float* __restrict__ Hsrc, const int32_t* __restrict__ self_idx,
@@ -604,7 +604,7 @@ sage_project_split(const float* __restrict__ Hsrc, const int32_t* __restrict__ s
                  const float* __restrict__ Wneigh, const float* __restrict__ bias, int64_t n_dst,
                  int32_t d_in, int32_t k_total, int32_t d_out, int relu, uint32_t n_tiles_n,
                  const float* __restrict__ Zero, float* __restrict__ out, const int64_t* __restrict__ n_rows_dev,
-                 TreeTiles tt) {
+                 TreeTiles tt, const uint16_t* __restrict__ W3, int32_t KP, int64_t w3_piece) {
     constexpr int LD = BK + 8;                            // LD / 8 odd: conflict-free 128-bit reads
     static_assert(BK % 16 == 0 && (LD / 8) % 2 == 1, "K tile");
     constexpr int TM = BM / 64, TN = BN / 64;
@@ -659,8 +659,9 @@ sage_project_split(const float* __restrict__ Hsrc, const int32_t* __restrict__ s
     zero_acc<TM, TN>(acc);
     zero_acc<TM, TN>(low);
 
-    struct Regs {
-        float a[A_ITEMS][8], b[B_ITEMS][8];
+    struct Regs {      // (one struct: a weights array of its own ends up in scratch memory)
+        float a[A_ITEMS][8];
+        uint4 p[B_ITEMS][3];
     };
     const int n_tiles = (K + BK - 1) / BK;
 
@@ -675,23 +676,8 @@ sage_project_split(const float* __restrict__ Hsrc, const int32_t* __restrict__ s
         p_self[it] = a_self[it] >= 0 ? Hsrc + a_self[it] : Zero;
         p_mean[it] = a_mean[it] >= 0 ? Mean + a_mean[it] - d_in : Zero;   // indexed by the concatenated k
     }
-    // this thread's weight column by the concatenated k: row k of W_self for k < d_in, row k - d_in of
-    // W_neigh after
-    const float* b_self[B_ITEMS];
-    const float* b_neigh[B_ITEMS];
-    bool b_in[B_ITEMS];
-#pragma unroll
-    for (int it = 0; it < B_ITEMS; ++it) {
-        const int n = col0 + (it * kProjThreads + tid) % BN;
-        b_in[it] = n < d_out;
-        b_self[it] = Wself + n;
-        b_neigh[it] = Wneigh + n - (int64_t)d_in * d_out;
-    }
-    // the concatenated element k of this thread's row / weight column
+    // the concatenated element k of this thread's row
     auto a_at = [&](int it, int k) { return k < K ? (k < d_in ? p_self[it] : p_mean[it]) + k : Zero; };
-    auto b_at = [&](int it, int k) {
-        return k < K && b_in[it] ? (k < d_in ? b_self[it] : b_neigh[it]) + (int64_t)k * d_out : Zero;
-    };
     auto one_half = [&](int k) { return k + 4 <= d_in || (k >= d_in && k + 4 <= K); };      // four k in one half
     auto load_tile = [&](Regs& r, int t) {
         const int k0 = t * BK;
@@ -711,24 +697,22 @@ sage_project_split(const float* __restrict__ Hsrc, const int32_t* __restrict__ s
                 }
             }
         }
-#pragma unroll
-        for (int it = 0; it < B_ITEMS; ++it) {
-            const int k = k0 + ((it * kProjThreads + tid) / BN) * 8;
-#pragma unroll
-            for (int h = 0; h < 8; h += 4) {
-                if (VEC || one_half(k + h)) {   // four k lie in one weight matrix
-                    const float* p = b_at(it, k + h);
-                    const int64_t step = k + h < K && b_in[it] ? d_out : 0;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) r.b[it][h + e] = p[e * step];
-                } else {
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) r.b[it][h + e] = *b_at(it, k + h + e);
-                }
-            }
-        }
     };
-    auto store_tile = [&](const Regs& r, int st) {
+    // the weights' pieces (L2 resident): items of eight k of one column; tiles past the end re-read the last one
+    const uint16_t* bp[B_ITEMS];
+#pragma unroll
+    for (int it = 0; it < B_ITEMS; ++it) {
+        const int i = it * kProjThreads + tid;
+        bp[it] = W3 + (int64_t)(col0 + i / (BK / 8)) * KP + (i % (BK / 8)) * 8;
+    }
+    auto load_b = [&](Regs& r, int t) {
+        const int k0 = t * BK < KP ? t * BK : KP - BK;
+#pragma unroll
+        for (int it = 0; it < B_ITEMS; ++it)
+#pragma unroll
+            for (int q = 0; q < 3; ++q) r.p[it][q] = *reinterpret_cast<const uint4*>(bp[it] + q * w3_piece + k0);
+    };
+    auto store_tile = [&](const Regs& r, const Regs& w, int st) {
         uint16_t* s = lds16 + st * STAGE;
 #pragma unroll
         for (int it = 0; it < A_ITEMS; ++it) {
@@ -738,7 +722,9 @@ sage_project_split(const float* __restrict__ Hsrc, const int32_t* __restrict__ s
 #pragma unroll
         for (int it = 0; it < B_ITEMS; ++it) {
             const int i = it * kProjThreads + tid;
-            stage_split8<B_PIECE>(r.b[it], s + 3 * A_PIECE + (i % BN) * LD + (i / BN) * 8);
+            uint16_t* dst = s + 3 * A_PIECE + (i / (BK / 8)) * LD + (i % (BK / 8)) * 8;
+#pragma unroll
+            for (int q = 0; q < 3; ++q) *reinterpret_cast<uint4*>(dst + q * B_PIECE) = w.p[it][q];
         }
     };
     const int fg = lane >> 5, fl32 = lane & 31;
@@ -748,20 +734,26 @@ sage_project_split(const float* __restrict__ Hsrc, const int32_t* __restrict__ s
         mma_split<TM, TN, BK, LD, A_PIECE, B_PIECE, TREE>(acc, low, sa, sb);
     };
 
-    // Two register sets and two LDS stages.  Iteration t: the loads of tile t+2 are issued first (into
-    // the set tile t has left), tile t is multiplied from LDS stage t&1, and only then is tile t+1 -
-    // loaded an iteration ago - split and moved to the other stage.  Tiles at or beyond n_tiles load
-    // as zeros and are never multiplied.
+    // Two register sets and two LDS stages.  Iteration t: tile t is multiplied from LDS stage t&1 while the left operand
+    // of tile t+1 - loaded an iteration ago - is split and moved to the other stage with the weights' pieces; the loads
+    // of tile t+2 go to the sets tile t has left.  The large tile has registers for one set of pieces, loaded in the
+    // iteration they are moved in (with two: 89 against 84 us on 85 k rows of 2 x 100 -> 256; the small one 35 against
+    // 38 on 12 k rows of 2 x 256 -> 256).  Tiles at or beyond n_tiles load as zeros and are never multiplied.
+    constexpr int DB = BM == 128 ? 1 : 2;
     Regs r[2];
+    load_b(r[0], 0);
     load_tile(r[0], 0);
     stage_bias<TrF32, BN, kProjThreads>(lds_bias, bias, col0, d_out, tid);
-    store_tile(r[0], 0);
+    store_tile(r[0], r[0], 0);
+    if (DB == 2) load_b(r[1], 1);
     load_tile(r[1], 1);
     lds_barrier();
     auto iter = [&](int t, int i) {     // i = t % 2, a constant after unrolling
+        load_b(r[DB == 2 ? i : 0], t + DB);
         load_tile(r[i], t + 2);
+        asm volatile("" ::: "memory");
         compute(i);
-        store_tile(r[i ^ 1], i ^ 1);
+        store_tile(r[i ^ 1], r[DB == 2 ? i ^ 1 : 0], i ^ 1);
         lds_barrier();
     };
     int t = 0;
@@ -1259,7 +1251,11 @@ sage_project_16_walk(const uint16_t* __restrict__ Hsrc, const int32_t* __restric
 template <typename Tr, bool FIRST>
 __global__ void __launch_bounds__(kMeanThreads)
 tree_means(const uint4* __restrict__ H, TreeMeans tm, int32_t words, int32_t group, uint4* __restrict__ Mean,
-           uint32_t* __restrict__ zero_row, int32_t zero_words) {
+           uint32_t* __restrict__ zero_row, int32_t zero_words, TransposeJobs jobs) {
+    if (blockIdx.x >= jobs.first_block) {
+        transpose_w_tile(jobs, blockIdx.x - jobs.first_block);
+        return;
+    }
     if (blockIdx.x == 0)
         for (int32_t i = threadIdx.x; i < zero_words; i += kMeanThreads) zero_row[i] = 0u;
     const int last = tm.n_levels - 1;
@@ -1267,7 +1263,7 @@ tree_means(const uint4* __restrict__ H, TreeMeans tm, int32_t words, int32_t gro
     const int64_t n_rows = first + (tm.list != nullptr ? (int64_t)*tm.n_list : tm.row0[last + 1] - first);
     constexpr uint32_t run = kMeanXcdRun;
     constexpr int U = FIRST ? MeanUnroll<Tr>::value : 5;
-    for (uint32_t vb = blockIdx.x;; vb += gridDim.x) {      // gridDim.x is a multiple of 8 run
+    for (uint32_t vb = blockIdx.x;; vb += jobs.first_block) {      // a multiple of 8 run
         const uint32_t seq = vb >> 3, round = seq / run;
         if ((int64_t)round * 8 * run * kMeanThreads >= n_rows * group) return;
         const int64_t lb = ((int64_t)round * 8 + (vb & 7u)) * run + seq % run;
@@ -1346,7 +1342,7 @@ tree_means(const uint4* __restrict__ H, TreeMeans tm, int32_t words, int32_t gro
 }
 
 hopgnn_status launch_tree_means(hopgnn_dtype dt, const void* Hsrc, const TreeMeans& tm, int64_t cap_rows, int32_t d, void* mean,
-                                void* zero_row, size_t zero_bytes, hipStream_t s) {
+                                void* zero_row, size_t zero_bytes, TransposeJobs jobs, uint32_t n_tiles, hipStream_t s) {
     const int32_t words = d / (dt == HOPGNN_F32 ? 4 : 8);
     const int32_t group = words < 64 ? words : 64;
     constexpr int64_t turn = 8 * kMeanXcdRun;
@@ -1357,8 +1353,9 @@ hopgnn_status launch_tree_means(hopgnn_dtype dt, const void* Hsrc, const TreeMea
     auto kern = dt == HOPGNN_F32    ? (first ? tree_means<TrF32, true> : tree_means<TrF32, false>)
                 : dt == HOPGNN_BF16 ? (first ? tree_means<TrBF16, true> : tree_means<TrBF16, false>)
                                     : (first ? tree_means<TrF16, true> : tree_means<TrF16, false>);
-    hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(kMeanThreads), 0, s, static_cast<const uint4*>(Hsrc), tm, words, group,
-                       static_cast<uint4*>(mean), static_cast<uint32_t*>(zero_row), (int32_t)(zero_bytes / 4));
+    jobs.first_block = (uint32_t)blocks;
+    hipLaunchKernelGGL(kern, dim3((unsigned)blocks + n_tiles), dim3(kMeanThreads), 0, s, static_cast<const uint4*>(Hsrc), tm, words,
+                       group, static_cast<uint4*>(mean), static_cast<uint32_t*>(zero_row), (int32_t)(zero_bytes / 4), jobs);
     HOPGNN_LAUNCH_CHECK();
     return HOPGNN_OK;
 }
@@ -1397,7 +1394,8 @@ template <int BM, int BN, int BK, bool SPLIT>
 static hopgnn_status launch_project_f32(bool vec, hipStream_t s, const void* Hsrc, const int32_t* self_idx,
                                         const void* mean, const void* Ws, const void* Wn, const void* bias,
                                         int64_t n_dst, int32_t d_in, int32_t k_total, int32_t d_out, int relu,
-                                        const void* zero, void* out, const int64_t* n_rows_dev, const TreeLayer* tree) {
+                                        const void* zero, void* out, const int64_t* n_rows_dev, const TreeLayer* tree,
+                                        const uint16_t* W3, int32_t KP) {
     const uint32_t ntn = (uint32_t)ceil_div(d_out, BN);
     TreeTiles tt{};
     const int64_t m_tiles = tree != nullptr ? tree_tiles(*tree, BM, tt) : ceil_div(n_dst, BM);
@@ -1421,7 +1419,7 @@ static hopgnn_status launch_project_f32(bool vec, hipStream_t s, const void* Hsr
             return HOPGNN_EHIP;
         if constexpr (SPLIT)
             hipLaunchKernelGGL(kern, grid, dim3(kProjThreads), lds, s, a, self_idx, m, ws, wn, b, n_dst, d_in, k_total, d_out,
-                               relu, ntn, z, o, n_rows_dev, tt);
+                               relu, ntn, z, o, n_rows_dev, tt, W3, KP, (int64_t)KP * ceil_div(d_out, 256) * 256);
         else
             hipLaunchKernelGGL(kern, grid, dim3(kProjThreads), lds, s, a, self_idx, m, ws, wn, b, n_dst, d_in, k_total, d_out,
                                relu, ntn, z, o, n_rows_dev);
@@ -1506,7 +1504,7 @@ ProjWs proj_ws_layout(hopgnn_dtype dt, int64_t n_rows, int32_t d_in, int32_t k_t
     L.agg_bytes = align_up((size_t)n_rows * (size_t)d_in * dtype_size(dt), 256);
     L.KP = (int32_t)(ceil_div((int64_t)k_total, kKPad16) * kKPad16);
     L.NP = (int32_t)(ceil_div(d_out, 256) * 256);
-    L.wt_bytes = dt == HOPGNN_F32 ? 0 : align_up((size_t)L.KP * (size_t)L.NP * 2, 256);
+    L.wt_bytes = align_up((size_t)L.KP * (size_t)L.NP * 2 * (dt == HOPGNN_F32 ? 3 : 1), 256);
     L.zero_bytes = align_up(((size_t)2 * d_in + 64) * dtype_size(dt), 256);
     L.total = L.agg_bytes + L.wt_bytes + L.zero_bytes;
     return L;
@@ -1522,7 +1520,7 @@ hopgnn_status project_dispatch(hopgnn_dtype dt, hipStream_t s, const void* Hsrc,
     const int64_t rows = tree != nullptr && tree->last_rows != nullptr ? n_dst - tree->level_rows[tree->n_levels - 1] / 2 : n_dst;
     const int64_t work = ceil_div(rows, 128) * ceil_div(d_out, 128);
     bool vec = d_in % per16 == 0 && aligned(Hsrc, 16) && aligned(mean, 16);
-    if (dt == HOPGNN_F32) vec = vec && d_out % per16 == 0 && aligned(W_self, 16) && aligned(W_neigh, 16);
+    if (dt == HOPGNN_F32 && !split) vec = vec && d_out % per16 == 0 && aligned(W_self, 16) && aligned(W_neigh, 16);
     if (tree != nullptr) {      // the slot-tree kernels are built for the vector path only
         if (!vec || (dt == HOPGNN_F32 && !split) || out_f32 || n_rows_dev != nullptr || d_out % per16 != 0 || !aligned(out, 16) ||
             (tree->mean_next != nullptr && !aligned(tree->mean_next, 16)) || tree->n_levels < 1 ||
@@ -1539,7 +1537,7 @@ hopgnn_status project_dispatch(hopgnn_dtype dt, hipStream_t s, const void* Hsrc,
         auto launch = split ? (big ? launch_project_f32<128, 128, 16, true> : launch_project_f32<64, 64, 32, true>)
                             : (big ? launch_project_f32<128, 128, 16, false> : launch_project_f32<64, 64, 32, false>);
         return launch(vec, s, Hsrc, self_idx, mean, W_self, W_neigh, bias, n_dst, d_in, k_total, d_out, relu, zero, out,
-                      n_rows_dev, tree);
+                      n_rows_dev, tree, Wt, KP);
     }
     const bool huge = d_out > 128 && work >= 1024;   // 256 x 256 tiles once they still fill 256 CUs
     const bool big = d_out > 64 && work >= 512;
@@ -1647,12 +1645,12 @@ hopgnn_status sage_fwd_marked(const void* Hsrc, hopgnn_dtype dt, int64_t n_src, 
     uint16_t* Wt = reinterpret_cast<uint16_t*>(static_cast<char*>(ws) + L.agg_bytes);
     void* zero = static_cast<char*>(ws) + L.agg_bytes + L.wt_bytes;
 
-    TransposeJob job{};
+    TransposeJobs job{};
     uint32_t n_tr = 0;
-    if (dt != HOPGNN_F32) {
-        job = TransposeJob{static_cast<const uint16_t*>(W_self), static_cast<const uint16_t*>(W_neigh), Wt, d_in,
-                           d_out, L.KP, L.NP, 0u, 2 * d_in};
-        n_tr = (uint32_t)(L.KP / 32) * (uint32_t)(L.NP / 32);
+    if (dt != HOPGNN_F32 || split) {
+        const TransposeJob j{static_cast<const uint16_t*>(W_self), static_cast<const uint16_t*>(W_neigh), Wt, d_in,
+                             d_out, L.KP, L.NP, 0u, 2 * d_in, dt == HOPGNN_F32};
+        job = transpose_jobs(&j, 1, n_tr);
     }
     hopgnn_status st;
     const AggSpec spec{nullptr, 0, agg};     // the C ABI's aggregator codes are the kernel's op codes

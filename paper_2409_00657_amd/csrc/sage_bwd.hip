@@ -1137,7 +1137,7 @@ static hopgnn_status sage_bwd_typed(const void* Hsrc, int64_t n_src, int32_t d_i
         const AggSpec spec = kind.scatter == kScatterGcn ? AggSpec{self_idx, 1, kind.norm ? kAggOpMean : kAggOpSum}
                              : kind.scatter == kScatterSum ? AggSpec{nullptr, 0, kAggOpSum}
                              : kind.scatter == kScatterMax ? AggSpec{nullptr, 0, kAggOpMax} : kAggMean;
-        hopgnn_status st = launch_mean<Tr>(Hsrc, indptr, idx, n_dst, d_in, mean, zero, L.zero_bytes, TransposeJob{}, 0, s,
+        hopgnn_status st = launch_mean<Tr>(Hsrc, indptr, idx, n_dst, d_in, mean, zero, L.zero_bytes, TransposeJobs{}, 0, s,
                                            spec, n_dst_dev);
         if (st != HOPGNN_OK) return st;
     }

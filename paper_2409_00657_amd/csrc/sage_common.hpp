@@ -224,7 +224,26 @@ struct TransposeJob {
     int32_t d_in, d_out, KP, NP;
     uint32_t first_block;   // workgroups >= first_block transpose; n_tiles_k = KP / 32
     int32_t k_total;
+    int32_t split;          // fp32 weights, written as three bf16 pieces NP * KP elements apart (split2_bf16)
 };
+static inline uint32_t transpose_tiles(const TransposeJob& J) { return J.Wt != nullptr ? (uint32_t)(J.KP / 32) * (uint32_t)(J.NP / 32) : 0u; }
+// Up to three layers' jobs ride along with one launch.
+struct TransposeJobs {
+    TransposeJob at[3];
+    uint32_t first_block, first[3];      // workgroups >= first_block work on a tile; at[j]'s begin at tile first[j]
+};
+static inline TransposeJobs transpose_jobs(const TransposeJob* jobs, int n, uint32_t& n_tiles) {
+    TransposeJobs J{};
+    n_tiles = 0;
+    for (int j = 0; j < 3; ++j) {
+        J.first[j] = j < n ? n_tiles : ~0u;
+        if (j < n) {
+            J.at[j] = jobs[j];
+            n_tiles += transpose_tiles(jobs[j]);
+        }
+    }
+    return J;
+}
 
 // What the segmented aggregation combines and how:  op 0 = sum divided by the number of terms
 // (mean), 1 = plain sum, 2 = element-wise maximum; with_self adds the destination's own source
@@ -239,6 +258,32 @@ constexpr int kAggOpMean = 0, kAggOpSum = 1, kAggOpMax = 2;
 constexpr AggSpec kAggMean{nullptr, 0, kAggOpMean};
 
 __device__ __forceinline__ void transpose_w_tile(const TransposeJob& J, uint32_t tile_id) {
+    if (J.split) {
+        __shared__ float ftile[32][33];
+        const uint32_t tiles_k = J.KP / 32;
+        const int k0 = (tile_id % tiles_k) * 32, n0 = (tile_id / tiles_k) * 32;
+        const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+        const float* Ws = reinterpret_cast<const float*>(J.Wself);
+        const float* Wn = reinterpret_cast<const float*>(J.Wneigh);
+        for (int j = ty; j < 32; j += 8) {
+            const int k = k0 + j, n = n0 + tx;
+            float v = 0.f;
+            if (k < J.k_total && n < J.d_out) v = k < J.d_in ? Ws[(int64_t)k * J.d_out + n] : Wn[(int64_t)(k - J.d_in) * J.d_out + n];
+            ftile[j][tx] = v;
+        }
+        __syncthreads();
+        const int kk = 2 * (threadIdx.x & 15);       // two k at a time
+        for (int j = threadIdx.x >> 4; j < 32; j += 16) {
+            uint32_t h, m, l;
+            split2_bf16(ftile[kk][j], ftile[kk + 1][j], h, m, l);
+            uint32_t* dst = reinterpret_cast<uint32_t*>(J.Wt + (int64_t)(n0 + j) * J.KP + k0 + kk);
+            const int64_t piece = (int64_t)J.NP * J.KP / 2;
+            dst[0] = h;
+            dst[piece] = m;
+            dst[2 * piece] = l;
+        }
+        return;
+    }
     __shared__ uint16_t tile[32][33];
     const uint32_t tiles_k = J.KP / 32;
     const int k0 = (tile_id % tiles_k) * 32, n0 = (tile_id / tiles_k) * 32;
@@ -257,6 +302,10 @@ __device__ __forceinline__ void transpose_w_tile(const TransposeJob& J, uint32_t
     }
 }
 
+__device__ __forceinline__ void transpose_w_tile(const TransposeJobs& J, uint32_t t) {
+    const int j = t >= J.first[2] ? 2 : t >= J.first[1] ? 1 : 0;
+    transpose_w_tile(J.at[j], t - J.first[j]);
+}
 
 constexpr int kMeanThreads = 256;
 // Neighbour rows a lane has in flight per round.  Fanouts are mostly multiples of 5 (5, 10, 15, 25), so 5
@@ -288,7 +337,7 @@ template <typename Tr, int OP, bool LOOSE = false>
 __global__ void __launch_bounds__(kMeanThreads)
 sage_mean_vec(const uint4* __restrict__ Hsrc, const int32_t* __restrict__ indptr,
               const int32_t* __restrict__ idx, int64_t n_dst, int32_t words_per_row, int32_t group,
-              uint4* __restrict__ Mean, uint32_t* __restrict__ zero_row, int32_t zero_words, TransposeJob job,
+              uint4* __restrict__ Mean, uint32_t* __restrict__ zero_row, int32_t zero_words, TransposeJobs job,
               AggSpec agg, const int64_t* __restrict__ n_rows_dev, uint32_t xcd_run, int32_t d_in) {
     if (blockIdx.x >= job.first_block) {
         transpose_w_tile(job, blockIdx.x - job.first_block);
@@ -369,7 +418,7 @@ __global__ void __launch_bounds__(kMeanThreads)
 sage_mean_elem(const typename Tr::store_t* __restrict__ Hsrc, const int32_t* __restrict__ indptr,
                const int32_t* __restrict__ idx, int64_t n_dst, int32_t d_in, int32_t group,
                typename Tr::store_t* __restrict__ Mean, uint32_t* __restrict__ zero_row, int32_t zero_words,
-               TransposeJob job, AggSpec agg, const int64_t* __restrict__ n_rows_dev) {
+               TransposeJobs job, AggSpec agg, const int64_t* __restrict__ n_rows_dev) {
     if (blockIdx.x >= job.first_block) {
         transpose_w_tile(job, blockIdx.x - job.first_block);
         return;
@@ -418,7 +467,7 @@ static inline int mean_group(int units) {   // lanes per destination row: power 
 template <typename Tr>
 static hopgnn_status launch_mean(const void* Hsrc, const int32_t* indptr, const int32_t* idx,
                                  int64_t n_dst, int32_t d_in, void* mean, void* zero_row,
-                                 size_t zero_bytes, TransposeJob job, uint32_t n_transpose_tiles, hipStream_t s,
+                                 size_t zero_bytes, TransposeJobs job, uint32_t n_transpose_tiles, hipStream_t s,
                                  AggSpec agg = kAggMean, const int64_t* n_rows_dev = nullptr) {
     using T = typename Tr::store_t;
     const bool whole = (d_in % Tr::kPer16 == 0) && aligned(Hsrc, 16) && aligned(mean, 16);
@@ -452,7 +501,7 @@ static hopgnn_status launch_mean(const void* Hsrc, const int32_t* indptr, const 
     return HOPGNN_OK;
 }
 
-// Workspace of a projection: [ aggregate : n_rows x d_in ][ Wt : NP x KP, 2-byte types only ][ zero row ]
+// Workspace of a projection: [ aggregate : n_rows x d_in ][ Wt : NP x KP, for fp32 three pieces of that ][ zero row ]
 struct ProjWs {
     size_t agg_bytes, wt_bytes, zero_bytes, total;
     int32_t KP, NP;
@@ -515,7 +564,7 @@ constexpr int kTreeMaxFan = 64;          // a group of siblings must fit the sma
 // out = act( [x_self | agg][:, :k_total] * [W_self ; W_neigh][:k_total] + bias ) on MFMA (defined with
 // the projection kernels).  k_total = 2*d_in is the two-matrix GraphSAGE layer, k_total = d_in a
 // plain rows-times-W product over the rows Hsrc[self_idx[r]].  For 2-byte types Wt (row stride KP)
-// must already hold the transposed weights; `zero` is a zeroed row of at least 2*d_in+64 elements.
+// must already hold the transposed weights, for fp32 with `split` their three transposed pieces; `zero` is a zeroed row of at least 2*d_in+64 elements.
 // out_f32 != 0: `out` is a float array and receives the unrounded result whatever dt is.
 // n_rows_dev (DEVICE, may be NULL): when given, only the first min(n_dst, *n_rows_dev) rows exist.
 // tree (may be NULL): the rows are the slots of a slot tree; rows are tiled level by level in whole
@@ -552,7 +601,7 @@ struct TreeMeans {
 };
 // mean[r] for all of them (cap_rows: their largest number), and zero_row cleared if given.
 hopgnn_status launch_tree_means(hopgnn_dtype dt, const void* Hsrc, const TreeMeans& tm, int64_t cap_rows, int32_t d, void* mean,
-                                void* zero_row, size_t zero_bytes, hipStream_t s);
+                                void* zero_row, size_t zero_bytes, TransposeJobs jobs, uint32_t n_tiles, hipStream_t s);
 
 // Writes the transposed, zero-padded weights of one 2-byte layer (job.Wt, see TransposeJob) and
 // clears `zero_row` (zero_bytes, may be 0): what the segmented-mean kernel does as a side job, as
