@@ -342,7 +342,11 @@ bitmap_scan_sums(uint32_t* __restrict__ block_sum, uint32_t n_blocks, int64_t* _
 // Pass 2, one launch for both outputs.  Workgroups [0, n_emit_blocks) walk one chunk of the
 // bitmap each and write its set bits to uniq in word order; the others fill remap for a strided
 // share of the slots, W slots at a time (4: 16-byte aligned ids and remap).
-template <int W>
+// EW: bitmap words per thread.  A thread writes its words' bits one after the other and a wavefront's stores go to as many
+// lines as it has lanes, so a dense chunk (the hubs are the low ids) takes as long as its fullest thread: 128 stores with
+// four words, 32 with one.  us, four words / one: 2.4 M
+// vertices (chung_lu) 19.4 / 8.5, 2^20 (rmat) 5.4 / 3.6, 2^24 (rmat) 10.0 / 7.6, 20 M and 18 M slots 57 / 55.5.
+template <int W, int EW>
 __global__ void __launch_bounds__(kPgThreads)
 bitmap_emit_remap(const uint2* __restrict__ word_rank, const uint32_t* __restrict__ block_base,
                   uint32_t n_emit_blocks, int32_t* __restrict__ uniq, const int32_t* __restrict__ ids, int64_t n_ids,
@@ -353,18 +357,23 @@ bitmap_emit_remap(const uint2* __restrict__ word_rank, const uint32_t* __restric
     }
     const uint32_t block = blockIdx.x - n_fill;
     if (block < n_emit_blocks) {
-        const int64_t t = (int64_t)block * kPgThreads + threadIdx.x;
-        const uint4* wr = reinterpret_cast<const uint4*>(word_rank + t * kWordsPerThread);
-        const uint4 a = wr[0], b = wr[1];              // (bits, rank) of words 4t .. 4t+3
-        const uint32_t wd[4] = {a.x, a.z, b.x, b.z};
-        const uint32_t rk[4] = {a.y, a.w, b.y, b.w};
-        if ((wd[0] | wd[1] | wd[2] | wd[3]) == 0u) return;
-        const uint32_t base = block_base[block];
+        constexpr int N = EW;      // words per thread
+        const int64_t t = ((int64_t)block * kPgThreads + threadIdx.x) * N;
+        uint32_t wd[N], rk[N], any = 0u;
 #pragma unroll
-        for (int k = 0; k < kWordsPerThread; ++k) {
+        for (int k = 0; k < N; ++k) {
+            const uint2 wr = word_rank[t + k];
+            wd[k] = wr.x;
+            rk[k] = wr.y;
+            any |= wr.x;
+        }
+        if (any == 0u) return;
+        const uint32_t base = block_base[t / kWordsPerBlock];
+#pragma unroll
+        for (int k = 0; k < N; ++k) {
             uint32_t bits = wd[k];
             uint32_t r = base + rk[k];
-            const int32_t v0 = (int32_t)((t * kWordsPerThread + k) << 5);
+            const int32_t v0 = (int32_t)((t + k) << 5);
             while (bits) {
                 const int bit = __ffs((int)bits) - 1;
                 uniq[r++] = v0 + bit;
@@ -419,9 +428,12 @@ static hopgnn_status bitmap_from_marks(const BitmapWs& L, bool unmark, const int
     const bool wide = n_ids >= (int64_t)256 * 16 * kPgThreads * 4 && aligned(ids, 16) && aligned(remap, 16);
     const unsigned remap_blocks = n_ids > 0 ? (unsigned)grid_for(n_ids, kPgThreads * (wide ? 4 : 1), 256 * 32) : 0u;
     const uint32_t per_list = fill_blocks(lists), n_fill = per_list * (uint32_t)lists.n;
-    hipLaunchKernelGGL((wide ? bitmap_emit_remap<4> : bitmap_emit_remap<1>), dim3(n_fill + (unsigned)L.n_blocks + remap_blocks),
-                       dim3(kPgThreads), 0, s, L.word_rank, L.block_sum, (uint32_t)L.n_blocks, uniq, ids, n_ids, remap, n_fill,
-                       per_list, lists);
+    const bool spread = L.n_blocks <= kMaxPackGrid;      // beyond it four times the workgroups, most of them idle, cost more
+    const uint32_t emit_blocks = (uint32_t)L.n_blocks * (spread ? 4u : 1u);
+    auto kern = wide ? (spread ? bitmap_emit_remap<4, 1> : bitmap_emit_remap<4, 4>)
+                     : (spread ? bitmap_emit_remap<1, 1> : bitmap_emit_remap<1, 4>);
+    hipLaunchKernelGGL(kern, dim3(n_fill + emit_blocks + remap_blocks), dim3(kPgThreads), 0, s, L.word_rank, L.block_sum,
+                       emit_blocks, uniq, ids, n_ids, remap, n_fill, per_list, lists);
     HOPGNN_LAUNCH_CHECK();
     return HOPGNN_OK;
 }
