@@ -1380,36 +1380,46 @@ col_sum_rows(const float* __restrict__ dOut, const typename Tr::store_t* __restr
     }
 }
 
-// out[i] += sum over p < n_parts of partial[p * part_stride + i], i < width, in a fixed order (wave q
-// takes the parts q, q + 16, ...; the sixteen sums are added in wave order): bit-stable.  The parts are a
-// chain of dependent adds behind independent loads: sixteen waves with four loads each in flight (four
-// waves with one took 33 us a call on the attention layers' parts).
-constexpr int kReduceWaves = 16;
-__global__ void __launch_bounds__(kReduceWaves * kWave)
-reduce_parts_add(const float* __restrict__ partial, int64_t part_stride, int32_t n_parts, int32_t width,
-                 float* __restrict__ out) {
-    __shared__ float part[kReduceWaves][kWave];
-    const int lane = threadIdx.x & 63, q = threadIdx.x >> 6;
-    const int32_t i = blockIdx.x * kWave + lane;
+// out[i] += sum over p < n_parts of partial[p * part_stride + i], i < width, in a fixed order: bit-stable.  blockIdx.y picks
+// one of two sums of the same shape.  The parts are a chain of dependent adds behind independent loads, and the chain is
+// the whole time: a workgroup takes 16 columns with 64 chains each, eight loads in flight (64 columns, 16 chains, four loads
+// in flight, a launch per sum: 11 us each on 2048 to 2656 parts of 256 columns, 100 us of an attention training iteration;
+// now 5).
+constexpr int kReduceCols = 16, kReduceChains = 64;
+__global__ void __launch_bounds__(kReduceCols * kReduceChains)
+reduce_parts_add(const float* __restrict__ partial0, const float* __restrict__ partial1, int64_t part_stride, int32_t n_parts,
+                 int32_t width, float* __restrict__ out0, float* __restrict__ out1) {
+    __shared__ float part[kReduceChains][kReduceCols + 1];
+    const int c = threadIdx.x % kReduceCols, q = threadIdx.x / kReduceCols;
+    const int32_t i = blockIdx.x * kReduceCols + c;
     float s = 0.f;
     if (i < width) {
-        const float* src = partial + i;
+        const float* src = (blockIdx.y ? partial1 : partial0) + i;
         int32_t p = q;
-        for (; p + 3 * kReduceWaves < n_parts; p += 4 * kReduceWaves) {
-            const float v0 = src[(int64_t)p * part_stride], v1 = src[(int64_t)(p + kReduceWaves) * part_stride];
-            const float v2 = src[(int64_t)(p + 2 * kReduceWaves) * part_stride];
-            const float v3 = src[(int64_t)(p + 3 * kReduceWaves) * part_stride];
-            s = (((s + v0) + v1) + v2) + v3;
+        for (; p + 7 * kReduceChains < n_parts; p += 8 * kReduceChains) {
+            float v[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) v[k] = src[(int64_t)(p + k * kReduceChains) * part_stride];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) s += v[k];
         }
-        for (; p < n_parts; p += kReduceWaves) s += src[(int64_t)p * part_stride];
+        for (; p < n_parts; p += kReduceChains) s += src[(int64_t)p * part_stride];
     }
-    part[q][lane] = s;
+    part[q][c] = s;
+    __syncthreads();
+    if (q < 8) {
+        s = 0.f;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) s += part[q * 8 + k][c];
+    }
+    __syncthreads();
+    if (q < 8) part[q][c] = s;
     __syncthreads();
     if (q == 0 && i < width) {
         float sum = 0.f;
 #pragma unroll
-        for (int w = 0; w < kReduceWaves; ++w) sum += part[w][lane];
-        out[i] += sum;
+        for (int k = 0; k < 8; ++k) sum += part[k][c];
+        (blockIdx.y ? out1 : out0)[i] += sum;
     }
 }
 
@@ -1482,14 +1492,15 @@ gat_list_zero(int32_t* __restrict__ cnt, int32_t* __restrict__ cursor, int64_t n
     if (i < n_src && (n_rows_dev == nullptr || i < *n_rows_dev)) cnt[i] = 0;
 }
 
-// FILL = false: cnt[u] = entries naming u.  true: list[pos[u]++] = destination row (its complement for the
-// row's own term).  Eight lanes per destination row.  An entry that names a row past the source rows that
+// FILL = false: cnt[u] = entries naming u, and every entry keeps how many came before it.  true: list[pos[u] + that] =
+// destination row (its complement for the row's own term), without atomics (with a second atomic per entry this pass took
+// 79 us on 1.1 M entries).  Eight lanes per destination row; entry e of row r is number e + r + 1.  An entry that names a row past the source rows that
 // exist is listed nowhere: such a row has no piece of the list (and no gradient that anything reads).
 template <bool FILL>
 __global__ void __launch_bounds__(kBwdThreads)
 gat_list_entries(const int32_t* __restrict__ self_idx, const int32_t* __restrict__ indptr, const int32_t* __restrict__ idx,
                  int64_t n_dst, int64_t n_src, const int64_t* __restrict__ n_rows_dev, int32_t* __restrict__ at,
-                 int32_t* __restrict__ list, GatGate gate) {
+                 int32_t* __restrict__ list, int32_t* __restrict__ before, GatGate gate) {
     if (gate_closed(gate)) return;
     if (n_rows_dev != nullptr && *n_rows_dev < n_src) n_src = *n_rows_dev;
     const int64_t gid = (int64_t)blockIdx.x * kBwdThreads + threadIdx.x;
@@ -1500,8 +1511,8 @@ gat_list_entries(const int32_t* __restrict__ self_idx, const int32_t* __restrict
     for (int32_t e = beg - 1 + (int32_t)(gid & 7); e < end; e += 8) {
         const int32_t u = gat_entry(e, beg, end, s, idx);
         if (u < 0 || u >= n_src) continue;
-        const int32_t p = atomicAdd(&at[u], 1);
-        if (FILL) list[p] = e < beg ? ~(int32_t)r : (int32_t)r;
+        if (!FILL) before[e + r + 1] = atomicAdd(&at[u], 1);
+        else list[at[u] + before[e + r + 1]] = e < beg ? ~(int32_t)r : (int32_t)r;
     }
 }
 
@@ -1528,7 +1539,7 @@ gat_list_place(const int32_t* __restrict__ cnt, int32_t* __restrict__ pos, int32
     if (threadIdx.x == 0) {
         int32_t total = 0;
         for (int w = 0; w < kBwdThreads / kWave; ++w) total += wave_total[w];
-        base = atomicAdd(cursor, total);
+        base = total > 0 ? atomicAdd(cursor, total) : 0;      // (rows past the count come in whole workgroups: 44 us with theirs)
     }
     __syncthreads();
     int32_t before = base;
@@ -1674,11 +1685,11 @@ gat_bwd_pull(const float* __restrict__ Z, const float* __restrict__ scores, cons
             const int2 p = pieces[t];
             u = p.x;
             beg = p.y;
-            end = pos[u] < beg + kGatPiece ? pos[u] : beg + kGatPiece;
+            end = pos[u] + cnt[u] < beg + kGatPiece ? pos[u] + cnt[u] : beg + kGatPiece;
         } else {
             if (cnt[u] > kGatPiece) continue;     // its pieces have it
-            end = pos[u];
-            beg = end - cnt[u];
+            beg = pos[u];
+            end = beg + cnt[u];
         }
         float4 z[NW], acc[NW];
 #pragma unroll
@@ -1968,6 +1979,7 @@ static GatBwdWs gat_bwd_ws_layout(int64_t n_src, int64_t n_dst, int32_t d_in, in
         L.stat_bytes = align_up((size_t)nd * n_heads * 16, 256);
         L.sum_bytes = align_up((size_t)nd * n_heads * 4, 256);
         L.masked_bytes = align_up((size_t)nd * d_out * 4, 256);
+        if (L.masked_bytes < L.list_bytes) L.masked_bytes = L.list_bytes;      // first the entries' numbers, then the masked gradient
     }
     L.col_bytes = align_up((size_t)parts * d_out * 4, 256);
     L.G = bwd_ws_layout(ns, d_in, d_out, 0);      // (row splits as for fp32 operands: any count is valid)
@@ -2000,8 +2012,8 @@ static hopgnn_status gat_bwd_typed(const void* Hsrc, int64_t n_src, const int64_
         hipLaunchKernelGGL(col_sum_rows<Tr>, dim3((unsigned)parts), dim3(kBwdThreads), 0, s, dOut,
                            static_cast<const T*>(out_fwd), relu, n_dst, d_out, col);
         HOPGNN_LAUNCH_CHECK();
-        hipLaunchKernelGGL(reduce_parts_add, dim3((unsigned)ceil_div(d_out, kWave)), dim3(kReduceWaves * kWave), 0, s, col,
-                           (int64_t)d_out, parts, d_out, gbias);
+        hipLaunchKernelGGL(reduce_parts_add, dim3((unsigned)ceil_div(d_out, kReduceCols)), dim3(kReduceCols * kReduceChains), 0, s,
+                           col, nullptr, (int64_t)d_out, parts, d_out, gbias, nullptr);
         HOPGNN_LAUNCH_CHECK();
     }
     if (n_src == 0) return HOPGNN_OK;              // no entries anywhere: only the bias has a gradient
@@ -2019,6 +2031,7 @@ static hopgnn_status gat_bwd_typed(const void* Hsrc, int64_t n_src, const int64_
         float4* stat = reinterpret_cast<float4*>(q += L.piece_bytes);
         float* sum_de = reinterpret_cast<float*>(q += L.stat_bytes);
         float* masked = reinterpret_cast<float*>(q += L.sum_bytes);
+        int32_t* before = reinterpret_cast<int32_t*>(masked);      // used up before that is written
         const int32_t words = d_out / n_heads / 4;
         int32_t seg = 1;
         while (seg < words && seg < kWave) seg *= 2;
@@ -2028,13 +2041,13 @@ static hopgnn_status gat_bwd_typed(const void* Hsrc, int64_t n_src, const int64_
                            n_src, n_src_dev);
         HOPGNN_LAUNCH_CHECK();
         hipLaunchKernelGGL(gat_list_entries<false>, by_row, dim3(kBwdThreads), 0, s, self_idx, indptr, idx, n_dst,
-                           n_src, n_src_dev, cnt, list, gate);
+                           n_src, n_src_dev, cnt, nullptr, before, gate);
         HOPGNN_LAUNCH_CHECK();
         hipLaunchKernelGGL(gat_list_place, dim3((unsigned)ceil_div(n_src, kBwdThreads)), dim3(kBwdThreads), 0, s, cnt, pos,
                            cursor, n_src, n_src_dev, pieces, dZ, d_out, gate);
         HOPGNN_LAUNCH_CHECK();
         hipLaunchKernelGGL(gat_list_entries<true>, by_row, dim3(kBwdThreads), 0, s, self_idx, indptr, idx, n_dst,
-                           n_src, n_src_dev, pos, list, gate);
+                           n_src, n_src_dev, pos, list, before, gate);
         HOPGNN_LAUNCH_CHECK();
         auto stats = words > kWave ? gat_bwd_stats<Tr, 2> : gat_bwd_stats<Tr, 1>;
         hipLaunchKernelGGL(stats, dim3((unsigned)ceil_div(n_dst, kBwdThreads / kWave), groups), dim3(kBwdThreads), 0, s, Z, scores,
@@ -2061,11 +2074,8 @@ static hopgnn_status gat_bwd_typed(const void* Hsrc, int64_t n_src, const int64_
     hipLaunchKernelGGL(gat_bwd_src<Tr>, dim3((unsigned)src_blocks), dim3(kBwdThreads), 0, s, Z, ds,
                        static_cast<const T*>(a_src), static_cast<const T*>(a_dst), n_src, n_src_dev, d_out, n_heads, dZ, col, gate);
     HOPGNN_LAUNCH_CHECK();
-    hipLaunchKernelGGL(reduce_parts_add, dim3((unsigned)ceil_div(d_out, kWave)), dim3(kReduceWaves * kWave), 0, s, col,
-                       (int64_t)2 * d_out, src_blocks, d_out, ga_src);
-    HOPGNN_LAUNCH_CHECK();
-    hipLaunchKernelGGL(reduce_parts_add, dim3((unsigned)ceil_div(d_out, kWave)), dim3(kReduceWaves * kWave), 0, s, col + d_out,
-                       (int64_t)2 * d_out, src_blocks, d_out, ga_dst);
+    hipLaunchKernelGGL(reduce_parts_add, dim3((unsigned)ceil_div(d_out, kReduceCols), 2), dim3(kReduceCols * kReduceChains), 0, s,
+                       col, col + d_out, (int64_t)2 * d_out, src_blocks, d_out, ga_src, ga_dst);
     HOPGNN_LAUNCH_CHECK();
 
     // gW += Hsrc^T dz: one matrix (k_self = 0), the "aggregate" operand is Hsrc itself, rows = source rows
