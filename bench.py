@@ -23,6 +23,7 @@ Prints ONE JSON line.
 from __future__ import annotations
 
 import argparse
+import ctypes
 import json
 import os
 import sys
@@ -40,10 +41,6 @@ HBM_PEAK_GBPS = 8000.0
 # size) over algorithmic bytes, per row size, measured on this command's own inputs
 # (profiles/batch_traffic_pmc.txt: workloads 5, 3 and 4)
 GATHER_TRAFFIC_OVER_ALGORITHMIC = {256: 1.008, 400: 1.127, 512: 1.012}
-# the same for the first projection of the fused path: counter bytes per launch over "left operand once +
-# output" (the self half of the operand is read from the gathered rows, which partly stay in cache)
-PROJECT_L1_TRAFFIC_OVER_IO = {3: (116180.1 + 32768.0) * 1024 / (169984 * 200 * 4 + 2 * 16384 * 256 * 4),
-                              4: (67918.4 + 4096.0) * 1024 / (106496 * 512 * 2 + 2 * 4096 * 256 * 2)}
 # fp32 layers of the single-call pass run on the bf16 instruction, eight products of split operands for one fp32
 # product: their ceiling is an eighth of the bf16 rate (the fp32 instruction's own is 157.3)
 MFMA_PEAK_TFLOPS = {"f32": 2500.0 / 8, "bf16": 2500.0, "f16": 2500.0}
@@ -326,6 +323,24 @@ def run_workload(cfg_id, group, args, cache, cpu_budget, stats_steps=6):
                 break
     wall_timed = time.perf_counter() - t_begin
 
+    # Layers that take their deepest level's rows once per distinct vertex of a micrograph: the plan's scratch then holds
+    # those rows, their lists and every row's source, which the same plan over a graph too dense for repeats does not.
+    def distinct_layers():
+        if not hp.fused:
+            return 0
+        size = lambda: int(hp._lib.hopgnn_batch_tree_ws_bytes(ctypes.byref(hp.plan)))
+        have, edges = size(), hp.plan.graph.n_edges
+        hp.plan.graph.n_edges = 1 << 40
+        extra = have - size()
+        hp.plan.graph.n_edges = edges
+        def want(n):
+            rows = [max([sh.levels[L - k] * hidden * es for k in range(1, n + 1) if k % 2 == par], default=0) for par in (0, 1)]
+            return sum(rows) + sum(8 * sh.levels[L - k] * hp.group for k in range(1, n + 1)) + 4 * sh.n_dst(1)
+        return max((n for n in range(1, L) if want(n) <= extra), default=0)
+
+    n_distinct = distinct_layers()
+    distinct_level = [0.0] * (L + 1)       # distinct vertices of a level, micrograph by micrograph, per layer launch
+
     # untimed replay of a few steps: U, valid slots per level, what per-batch pre-gathering would fetch
     U_sum = valid_sum = U_per_batch_sum = 0
     valid_level = [0] * (L + 1)
@@ -338,6 +353,11 @@ def run_workload(cfg_id, group, args, cache, cpu_budget, stats_steps=6):
         ok = (hp.ids >= 0).view(hp.layer_batches, -1)      # one row per separately laid out batch
         for h in range(L + 1):
             valid_level[h] += int(ok[:, level_off[h]:level_off[h + 1]].sum().item())
+            if n_distinct and 1 <= h < L:
+                lv = hp.ids[level_off[h]:level_off[h + 1]].view(sh.n_seeds, -1).sort(1).values
+                fresh = torch.ones_like(lv, dtype=torch.bool)
+                fresh[:, 1:] = lv[:, 1:] != lv[:, :-1]
+                distinct_level[h] += int((fresh & (lv >= 0)).sum().item()) / n_stats
         if group > 1:
             for b in range(group):
                 if merge:   # batch b's slots of every level of the merged level-major array
@@ -383,18 +403,21 @@ def run_workload(cfg_id, group, args, cache, cpu_budget, stats_steps=6):
     for k in range(1, L + 1):
         n_dst, nnz = sh.n_dst(k), sh.nnz(k)
         nnz_valid = sum(valid_level[1:L - k + 2]) / runs
+        if k <= n_distinct:      # what is computed: the slots above, the distinct rows of the deepest level
+            below = valid_level[L - k + 1] / max(valid_level[L - k], 1)      # valid children per valid slot
+            nnz_valid += distinct_level[L - k] * below - valid_level[L - k + 1] / runs
+            nnz -= (sh.levels[L - k] - distinct_level[L - k]) * cfg.fanouts[L - k]
+            n_dst = sh.n_dst(k + 1) + distinct_level[L - k]
         flops = 2.0 * n_dst * 2 * din * hidden
         # left operand once + output (fused slot-tree layers store the next layer's destination rows and
         # as many rows of neighbour means instead of every row)
-        out_rows = 2 * sh.n_dst(k + 1) if (hp.fused and k < L) else n_dst
+        out_rows = n_dst if k <= n_distinct else 2 * sh.n_dst(k + 1) if (hp.fused and k < L) else n_dst
         io = n_dst * 2 * din * es + out_rows * hidden * es
         add("project_l%d" % k, "mfma", flops, MFMA_PEAK_TFLOPS[dname] * 1.0, "TFLOP/s",
-            {"kernel": "sage_project", "M": n_dst, "K": 2 * din, "N": hidden,
+            {"kernel": "sage_project", "M": n_dst, "M_slots": sh.n_dst(k), "K": 2 * din, "N": hidden,
              "hbm_bytes_operand_once_plus_output": io})
         kernels["project_l%d" % k]["hbm_GBps"] = io / (kernels["project_l%d" % k]["avg_launch_ms"] * 1e-3) * 1e-9
         kernels["project_l%d" % k]["hbm_frac"] = kernels["project_l%d" % k]["hbm_GBps"] / HBM_PEAK_GBPS
-        if k == 1 and hp.fused and group == 1 and cfg_id in PROJECT_L1_TRAFFIC_OVER_IO:
-            kernels["project_l1"]["traffic"] = io * PROJECT_L1_TRAFFIC_OVER_IO[cfg_id]
         if "aggregate_l%d" % k not in stage_ms:
             din = hidden
             continue
