@@ -317,7 +317,6 @@ template <typename Tr>
 struct MeanUnroll {
     static constexpr int value = sizeof(typename Tr::store_t) == 4 ? 5 : 4;
 };
-constexpr int kMeanUnrollElem = 4;       // the element-wise path
 
 // Vector path: d_in * sizeof(elem) is a multiple of 16.  `group` lanes (a power of
 // two <= 64) share one destination row; lane g of the group owns 16-byte word
